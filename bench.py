@@ -472,8 +472,7 @@ def x1_mixed_precision(wl, fp32_ms, iters=100):
 
 
 # variant codes of the batched solver (kernel_used // 100)
-BATCH_KERNELS = {257: "k_cp_persistent_lean", 256: "k_cp_persistent<256>", 512: "k_cp_persistent<512>",
-                 1: "k_cp_batch_step (one launch per iteration)"}
+BATCH_KERNELS = {257: "k_cp_persistent", 1: "k_cp_batch_step (one launch per iteration)"}
 
 
 def batched_run(wl, submaps=64, iters=300, steps=2):
@@ -680,7 +679,7 @@ def main():
                   "blocks": nb, "voxels": nvox, "street_blocks": wl.street.num_blocks,
                   "iters": args.iters, "lambda": 0.5, "kernel": args.kernel, "storage": args.storage,
                   "data_term": args.data_term}
-        kname = {1: "k_dual + k_primal", 2: "k_cp_fused", 3: "k_cp_fused256"}.get(st.kernel_used, "k_cp_fused")
+        kname = {1: "k_dual + k_primal"}.get(st.kernel_used, "k_cp_fused")
         kname += " (one CP iteration)"
     line = {
         "metric": metric,
@@ -709,13 +708,12 @@ def main():
         line["omega_voxels"] = n_omega
         line["cp_omega_voxel_iters_per_s"] = n_omega / (kern_ms / 1000.0)
     if args.workload == "batched":
-        line["config"]["kernel_used"] = {"threads": 512 if st.kernel_used // 100 == 512 else 256,
-                                         "lean": st.kernel_used // 100 == 257,
+        line["config"]["kernel_used"] = {"threads": 256, "persistent": st.kernel_used // 100 == 257,
                                          "wg_per_cu": st.kernel_used % 100}
         line["config"]["layout_used"] = {"order": "pool" if st.layout_used & 1 else "morton",
                                          "xcd_chunks": not (st.layout_used & 2)}
     if args.workload == "street":
-        names = {1: "twopass", 2: "fused512", 3: "fused256x2"}
+        names = {1: "twopass", 2: "fused512", 3: "fused256x2", 4: "fused128x4", 5: "fused64x8"}
         line["config"]["kernel_used"] = names.get(st.kernel_used, str(st.kernel_used))
         line["config"]["layout_used"] = {"order": "pool" if st.layout_used & 1 else "morton",
                                          "xcd_chunks": not (st.layout_used & 2)}

@@ -71,6 +71,8 @@ extern "C" {
 #define DN_K_TWOPASS 1   /* dual kernel then primal kernel, per iteration     */
 #define DN_K_FUSED 2     /* one LDS-staged kernel per iteration, 512 threads  */
 #define DN_K_FUSED256 3  /* the same with 256 threads, two voxels per thread  */
+/* kernel_used may also report 4 (128 threads, four voxels per thread) or
+ * 5 (64 threads, eight), which DN_K_AUTO picks between too.            */
 
 /* ----------------------------------------------------- dn_extract targets */
 #define DN_X_COORDS 1     /* int32 [n_blocks][3] block keys, pool order        */
@@ -159,7 +161,7 @@ typedef struct {
     int32_t converged;       /* 1 if gap_tol was reached                      */
     double ms_loop;          /* HIP-event time of the iteration loop on the
                                 volume's stream (gap checks included)        */
-    int32_t kernel_used;     /* DN_K_* that ran (after autotuning)            */
+    int32_t kernel_used;     /* DN_K_* that ran (after autotuning), or 4, 5    */
     int32_t layout_used;     /* bit 0: pool order (else Morton order); bit 1:
                                 plain workgroup map (else XCD chunks)        */
 } dn_reg_stats;
@@ -305,9 +307,8 @@ size_t dn_regularize_batch_bytes(int32_t n, int64_t total_blocks);
  * first call of a size with init ZERO, the persistent kernel until then),
  * any other value the persistent kernel.  Work items are (volume, block) pairs balanced over the grid.
  * kernel_used of the stats: 100 x variant + workgroups per CU (variant 1:
- * one launch per iteration; 256 / 512: persistent with that many threads
- * per workgroup; 257: persistent, 256 threads, no prefetch).  All volumes must share one device; the
- * first volume's stream is used.  gap_every / gap_tol are ignored (the
+ * one launch per iteration; 257: persistent, 256 threads).  All volumes must
+ * share one device; the first volume's stream is used.  gap_every / gap_tol are ignored (the
  * gaps are computed once at the end); init must be ZERO or KEEP; storage
  * must be DN_F32.  workspace_dev: caller device memory of at least
  * dn_regularize_batch_bytes(n, sum of the volumes' blocks) bytes, 256-byte

@@ -25,7 +25,7 @@ namespace dn {
 
 struct VolDesc {
     const int32_t *nbr;
-    const uint8_t *emask;
+    const uint32_t *em4;
     const float *f, *w;
     float *u;
     float *ubar[2];
@@ -163,7 +163,7 @@ __device__ __forceinline__ void item_args(const BatchArgs &a, const VolDesc *__r
     const int c = (__builtin_amdgcn_readfirstlane(d.cur) + it) & 1;
     const int64_t ps = int64_t(__builtin_amdgcn_readfirstlane(uint32_t(d.pstride))) |
                        (int64_t(__builtin_amdgcn_readfirstlane(uint32_t(uint64_t(d.pstride) >> 32))) << 32);
-    A.nb = 0; A.pstride = ps; A.nbr = uni(d.nbr); A.emask = uni(d.emask); A.order = nullptr; A.xcd = 0;
+    A.nb = 0; A.pstride = ps; A.nbr = uni(d.nbr); A.em4 = uni(d.em4); A.order = nullptr; A.xcd = 0;
     A.f = uni(d.f); A.w = uni(d.w); A.u = uni(d.u);
     A.ubar_in = uni(d.ubar[c]); A.ubar_out = uni(d.ubar[1 - c]);
     A.p_in = uni(d.p[c]); A.p_out = uni(d.p[1 - c]); A.u32 = nullptr; A.ubar32 = nullptr; A.p32 = nullptr;
@@ -172,17 +172,19 @@ __device__ __forceinline__ void item_args(const BatchArgs &a, const VolDesc *__r
     A.seed = 0u;
 }
 
-// All iterations of all sub-maps.  Without kPrefetch the workgroups take
-// the items of an iteration from a shared counter (per XCD chunk); with
-// kPrefetch each walks a fixed stride of them and issues the global loads
-// of the next item before computing the current one (two register sets, so
-// loads stay in flight while it works).  A grid barrier closes every
-// iteration.
-template <int NT, bool kPrefetch>
-__device__ __forceinline__ void k_cp_persistent_body(const BatchArgs &a, const VolDesc *__restrict__ vols,
-                                                     const int2 *__restrict__ items)
+// All iterations of all sub-maps: the workgroups take the items of an
+// iteration from a shared counter (per XCD chunk), and a grid barrier closes
+// every iteration.  The descriptors and the item list (read-only during the
+// launch) are also passed as restrict-qualified kernel arguments: no store
+// of the loop can then alias them, so the compiler reads them with scalar
+// loads, which shortens the chain of dependent loads in front of each block.
+// Registers are capped for 8 waves per SIMD.
+constexpr int kBatchWaves = 4;    // waves per block
+template <bool kStream>
+__global__ __launch_bounds__(64 * kBatchWaves) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_cp_persistent(
+    BatchArgs a, const VolDesc *__restrict__ vols, const int2 *__restrict__ items)
 {
-    __shared__ CPShared sh;
+    __shared__ CPShared<kBatchWaves> sh;
     __shared__ int s_stop;
     __shared__ unsigned s_next;
     const unsigned nwg = gridDim.x;
@@ -198,82 +200,44 @@ __device__ __forceinline__ void k_cp_persistent_body(const BatchArgs &a, const V
             acc_tau = th * acc_tau;
             acc_sigma = acc_sigma / th;
         }
-        int64_t i, hi, stride, lo = 0, cx = 0;
+        int64_t lo = 0, hi = a.n_items, stride = G, cx = 0;
         if (a.xcd_chunks && G >= 8) {
             // workgroup g runs on XCD g % 8; XCD x owns items [x*chunk, (x+1)*chunk)
             // and has exactly (G - x + 7) / 8 workgroups to stride over them
-            const int64_t x = blockIdx.x % 8, lane = blockIdx.x / 8;
             const int64_t chunk = (a.n_items + 7) / 8;
-            lo = x * chunk;
+            cx = blockIdx.x % 8;
+            lo = cx * chunk;
             hi = min(a.n_items, lo + chunk);
-            stride = (G - x + 7) / 8;
-            i = lo + lane;
-            cx = x;
-        } else {
-            i = blockIdx.x;
-            hi = a.n_items;
-            stride = G;
+            stride = (G - cx + 7) / 8;
         }
-        if constexpr (!kPrefetch) {
-            // One block after the other (the other workgroups on the CU
-            // overlap), each taken in order from the items [lo, hi) through
-            // the chunk's counter, so that the items in flight stay one
-            // contiguous window however unevenly the workgroups progress.
-            // The next index is taken while the current block is processed.
-            // Every workgroup of the chunk ends an iteration with exactly one
-            // index past the end, so the counter advances by len + stride per
-            // iteration and the index is its value less that base (modulo
-            // 2^32, which keeps differences exact).
-            unsigned *ctr = a.bar + kBarCtr + cx * kBarSlot;
-            const unsigned len = unsigned(hi > lo ? hi - lo : 0);
-            const unsigned base = unsigned(it) * (len + unsigned(stride));
+        // One block after the other (the other workgroups on the CU
+        // overlap), each taken in order from the items [lo, hi) through
+        // the chunk's counter, so that the items in flight stay one
+        // contiguous window however unevenly the workgroups progress.
+        // The next index is taken while the current block is processed.
+        // Every workgroup of the chunk ends an iteration with exactly one
+        // index past the end, so the counter advances by len + stride per
+        // iteration and the index is its value less that base (modulo
+        // 2^32, which keeps differences exact).
+        unsigned *ctr = a.bar + kBarCtr + cx * kBarSlot;
+        const unsigned len = unsigned(hi > lo ? hi - lo : 0);
+        const unsigned base = unsigned(it) * (len + unsigned(stride));
+        if (threadIdx.x == 0)
+            s_next = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - base;
+        __syncthreads();
+        unsigned rel = s_next;
+        while (rel < len) {
+            unsigned nraw = 0;
+            __syncthreads();   // every thread has read s_next
             if (threadIdx.x == 0)
-                s_next = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - base;
+                nraw = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const int2 bi = load_item(items, lo + rel);
+            CPArgs<SF32> A;
+            item_args(a, vols, bi, it, sigma, tau, theta, A);
+            cp_block<SF32, false, kStream, kBatchWaves>(A, bi.y, sh, wave_index(), opaque_lane());
+            if (threadIdx.x == 0) s_next = nraw - base;
             __syncthreads();
-            unsigned rel = s_next;
-            while (rel < len) {
-                unsigned nraw = 0;
-                __syncthreads();   // every thread has read s_next
-                if (threadIdx.x == 0)
-                    nraw = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const int2 bi = load_item(items, lo + rel);
-                CPArgs<SF32> A;
-                item_args(a, vols, bi, it, sigma, tau, theta, A);
-                cp_block<SF32, false, NT>(A, bi.y, sh, opaque_tid());
-                if (threadIdx.x == 0) s_next = nraw - base;
-                __syncthreads();
-                rel = s_next;
-            }
-        } else {
-        CPRegs<NT> R0, R1;
-        CPArgs<SF32> A0, A1;
-        int2 b0 = make_int2(0, 0), b1 = make_int2(0, 0);
-        if (i < hi) {
-            b0 = load_item(items, i);
-            item_args(a, vols, b0, it, sigma, tau, theta, A0);
-            cp_load<SF32, NT>(A0, b0.y, R0, opaque_tid());
-        }
-        while (i < hi) {
-            int64_t nx = i + stride;
-            if (nx < hi) {
-                b1 = load_item(items, nx);
-                item_args(a, vols, b1, it, sigma, tau, theta, A1);
-                cp_load<SF32, NT>(A1, b1.y, R1, opaque_tid());
-            }
-            cp_compute<SF32, false, NT>(A0, b0.y, R0, sh, opaque_tid());
-            __syncthreads();
-            i = nx;
-            if (i >= hi) break;
-            nx = i + stride;
-            if (nx < hi) {
-                b0 = load_item(items, nx);
-                item_args(a, vols, b0, it, sigma, tau, theta, A0);
-                cp_load<SF32, NT>(A0, b0.y, R0, opaque_tid());
-            }
-            cp_compute<SF32, false, NT>(A1, b1.y, R1, sh, opaque_tid());
-            __syncthreads();
-            i = nx;
-        }
+            rel = s_next;
         }
         grid_barrier(a, nwg, unsigned(it + 1));
         if (threadIdx.x == 0)
@@ -283,41 +247,25 @@ __device__ __forceinline__ void k_cp_persistent_body(const BatchArgs &a, const V
     }
 }
 
-// The descriptors and the item list (read-only during the launch) are also
-// passed as restrict-qualified kernel arguments: no store of the loop can
-// then alias them, so the compiler reads them with scalar loads, which
-// shortens the chain of dependent loads in front of each block.
-template <int NT, bool kPrefetch>
-__global__ __launch_bounds__(NT) void k_cp_persistent(BatchArgs a, const VolDesc *__restrict__ vols,
-                                                     const int2 *__restrict__ items)
-{
-    k_cp_persistent_body<NT, kPrefetch>(a, vols, items);
-}
-
-// The lean form: no prefetch, registers capped for 8 waves per SIMD.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_cp_persistent_lean(
-    BatchArgs a, const VolDesc *__restrict__ vols, const int2 *__restrict__ items)
-{
-    k_cp_persistent_body<256, false>(a, vols, items);
-}
-
 // One iteration of every sub-map: one workgroup per item, the items
 // mapped to workgroups in XCD chunks as in the single-map kernel (so the
 // blocks in flight are a contiguous window of the item list per XCD, as
 // hardware dispatch keeps them); no barrier, the next launch is the next
 // iteration.
 constexpr int kStepKernel = 1;   // variant code of this kernel in the tuner
-__global__ __launch_bounds__(256) void k_cp_batch_step(BatchArgs a, const VolDesc *__restrict__ vols,
+constexpr int kPersistent = 257; // ... and of the persistent one
+template <bool kStream>
+__global__ __launch_bounds__(64 * kBatchWaves) void k_cp_batch_step(BatchArgs a, const VolDesc *__restrict__ vols,
                                                        const int2 *__restrict__ items, int it, float sigma,
                                                        float tau, float theta)
 {
-    __shared__ CPShared sh;
+    __shared__ CPShared<kBatchWaves> sh;
     const int64_t slot = block_slot(blockIdx.x, a.n_items, a.xcd_chunks);
     if (slot >= a.n_items) return;
     const int2 bi = load_item(items, slot);
     CPArgs<SF32> A;
     item_args(a, vols, bi, it, sigma, tau, theta, A);
-    cp_block<SF32, false, 256>(A, bi.y, sh, threadIdx.x);
+    cp_block<SF32, false, kStream, kBatchWaves>(A, bi.y, sh, wave_index(), threadIdx.x & 63u);
 }
 
 __global__ void k_make_items(const int32_t *__restrict__ order, int64_t nb, int32_t vol, int2 *__restrict__ items)
@@ -345,7 +293,7 @@ struct BatchCtx {
 static std::map<int, BatchCtx> g_batch;     // by device
 static std::mutex g_batch_mutex;             // held for a whole batched call
 
-// (threads per workgroup, workgroups per CU, XCD-chunked items, pool order)
+// (kernel variant, workgroups per CU, XCD-chunked items, pool order)
 struct TuneChoice { int nt; int wg_per_cu; int xcd; int pool; };
 static std::map<int64_t, TuneChoice> g_tuned;   // by (device, size bucket)
 
@@ -372,13 +320,13 @@ static int size_bucket(int64_t n)
     return b;
 }
 
-// variant: 256 / 512 = threads per workgroup with prefetch of the next
-// block; 257 = 256 threads without prefetch (fewer registers, more
-// workgroups per CU); kStepKernel = one launch per iteration (grid
-// unused).  The step sizes of the accelerated schedule are formed as the
-// persistent kernel forms them (double precision, the same operations).
+// variant: kPersistent = the persistent kernel; kStepKernel = one launch per
+// iteration (grid unused).  The step sizes of the accelerated schedule are
+// formed as the persistent kernel forms them (double precision, the same
+// operations).
 static void launch_kernel(hipStream_t st, const BatchArgs &a, int grid, int nt)
 {
+    const bool stream = streams_state(a.n_items, sizeof(float));
     hipLaunchKernelGGL(k_batch_reset, dim3(32), dim3(256), 0, st, a.bar);
     if (nt == kStepKernel) {
         const unsigned g = unsigned(((a.n_items + 7) / 8) * 8);
@@ -393,15 +341,12 @@ static void launch_kernel(hipStream_t st, const BatchArgs &a, int grid, int nt)
                 acc_tau = th * acc_tau;
                 acc_sigma = acc_sigma / th;
             }
-            hipLaunchKernelGGL(k_cp_batch_step, dim3(g), dim3(256), 0, st, a, a.vols, a.items, it, sigma, tau,
-                               theta);
+            hipLaunchKernelGGL(stream ? k_cp_batch_step<true> : k_cp_batch_step<false>, dim3(g), dim3(64 * kBatchWaves),
+                               0, st, a, a.vols, a.items, it, sigma, tau, theta);
         }
-    } else if (nt == 256)
-        hipLaunchKernelGGL((k_cp_persistent<256, true>), dim3(grid), dim3(256), 0, st, a, a.vols, a.items);
-    else if (nt == 257)
-        hipLaunchKernelGGL(k_cp_persistent_lean, dim3(grid), dim3(256), 0, st, a, a.vols, a.items);
-    else
-        hipLaunchKernelGGL((k_cp_persistent<512, true>), dim3(grid), dim3(512), 0, st, a, a.vols, a.items);
+    } else {
+        hipLaunchKernelGGL(stream ? k_cp_persistent<true> : k_cp_persistent<false>, dim3(grid), dim3(64 * kBatchWaves), 0, st, a, a.vols, a.items);
+    }
 }
 
 static int launch_direct(hipStream_t st, const BatchArgs &a, int grid, int nt)
@@ -532,7 +477,7 @@ extern "C" int dn_regularize_batch(dn_volume *const *vols, int32_t n, const dn_r
     for (int i = 0; i < n; ++i) {
         dn_volume *v = vols[i];
         VolDesc &d = hd[i];
-        d.nbr = v->nbr; d.emask = v->emask; d.f = v->f; d.w = v->w; d.u = v->u;
+        d.nbr = v->nbr; d.em4 = v->em4; d.f = v->f; d.w = v->w; d.u = v->u;
         d.ubar[0] = v->ubar[0]; d.ubar[1] = v->ubar[1]; d.p[0] = v->p[0]; d.p[1] = v->p[1];
         d.pstride = v->cap_blocks * kBlockVox;
         d.cur = v->cur;
@@ -571,17 +516,20 @@ extern "C" int dn_regularize_batch(dn_volume *const *vols, int32_t n, const dn_r
     a.l1 = prm->data_term == DN_DATA_L1;
 
     // occupancy bound: every workgroup of the grid must be resident at once
-    int dev_cu = 0, per_cu256 = 0, per_cu257 = 0, per_cu512 = 0;
+    int dev_cu = 0, per_cu = 0;
     DN_HIP(hipDeviceGetAttribute(&dev_cu, hipDeviceAttributeMultiprocessorCount, v0->device));
-    DN_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu256, k_cp_persistent<256, true>, 256, 0));
-    DN_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu257, k_cp_persistent_lean, 256, 0));
-    DN_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu512, k_cp_persistent<512, true>, 512, 0));
-    if (per_cu257 < 1) { set_error("persistent kernel does not fit on a compute unit"); return DN_E_DEVICE; }
+    {
+        int a1 = 0, a0 = 0;
+        DN_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&a1, k_cp_persistent<true>, 64 * kBatchWaves, 0));
+        DN_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&a0, k_cp_persistent<false>, 64 * kBatchWaves, 0));
+        per_cu = std::min(a1, a0);
+    }
+    if (per_cu < 1) { set_error("persistent kernel does not fit on a compute unit"); return DN_E_DEVICE; }
 
     // DN_K_FUSED256: one launch of the fused kernel per iteration; other
     // explicit choices: the persistent kernel; both on the blocks in pool
     // order, XCD-chunked.  DN_K_AUTO: the tuned choice
-    TuneChoice ch = TuneChoice{257, per_cu257, 1, 1};
+    TuneChoice ch = TuneChoice{kPersistent, per_cu, 1, 1};
     if (prm->kernel == DN_K_FUSED256) ch = TuneChoice{kStepKernel, 1, 1, 1};
     const int64_t key = (int64_t(v0->device) << 32) | size_bucket(total);
     auto it = g_tuned.find(key);
@@ -589,7 +537,10 @@ extern "C" int dn_regularize_batch(dn_volume *const *vols, int32_t n, const dn_r
     if (tuned && it != g_tuned.end()) {
         ch = it->second;
     } else if (tuned && prm->init == DN_INIT_ZERO && total > 0 && prm->iters > 0) {
-        // autotune: a few iterations of each candidate, from the zero state
+        // autotune: a few iterations of each candidate, from the zero state,
+        // all with the items in XCD chunks (without, the persistent kernel's
+        // one counter for all workgroups took 3.1 against 1.4 ms for six
+        // iterations of 16 sub-maps, and the launches were within 1 %)
         hipEvent_t e0, e1;
         DN_HIP(hipEventCreate(&e0));
         DN_HIP(hipEventCreate(&e1));
@@ -597,29 +548,25 @@ extern "C" int dn_regularize_batch(dn_volume *const *vols, int32_t n, const dn_r
         const int trial = std::min(prm->iters, 6);
         for (int pool = 0; pool <= 1; ++pool) {
             if ((rc = build_items(pool))) return rc;
-            for (int nt : {257, 256, 512, kStepKernel}) {
-                const int pc = nt == kStepKernel ? 1 : (nt == 256 ? per_cu256 : (nt == 257 ? per_cu257 : per_cu512));
+            for (int nt : {kPersistent, kStepKernel}) {
+                const int pc = nt == kStepKernel ? 1 : per_cu;
                 if (pc < 1) continue;
                 std::vector<int> wpcs = {pc};
                 if ((pc + 1) / 2 != pc) wpcs.push_back((pc + 1) / 2);
                 for (int wpc : wpcs) {
-                    for (int xcd = 0; xcd <= 1; ++xcd) {
-                        BatchArgs t = a;
-                        t.iters = trial;
-                        t.xcd_chunks = xcd;
-                        int grid = int(std::min<int64_t>({int64_t(wpc) * dev_cu, total, int64_t(kBarMaxGrid)}));
-                        DN_HIP(hipEventRecord(e0, st));
-                        if ((rc = launch_direct(st, t, grid, nt))) return rc;
-                        DN_HIP(hipEventRecord(e1, st));
-                        DN_HIP(hipEventSynchronize(e1));
-                        if ((rc = check_err(v0, st, t.err))) return rc;
-                        float ms = 0;
-                        DN_HIP(hipEventElapsedTime(&ms, e0, e1));
-                        if (getenv("DN_VERBOSE"))
-                            fprintf(stderr, "[denser] batch tune: nt %d wpc %d xcd %d pool %d: %.3f ms\n", nt, wpc,
-                                    xcd, pool, ms);
-                        if (ms < best) { best = ms; ch = TuneChoice{nt, wpc, xcd, pool}; }
-                    }
+                    BatchArgs t = a;
+                    t.iters = trial;
+                    int grid = int(std::min<int64_t>({int64_t(wpc) * dev_cu, total, int64_t(kBarMaxGrid)}));
+                    DN_HIP(hipEventRecord(e0, st));
+                    if ((rc = launch_direct(st, t, grid, nt))) return rc;
+                    DN_HIP(hipEventRecord(e1, st));
+                    DN_HIP(hipEventSynchronize(e1));
+                    if ((rc = check_err(v0, st, t.err))) return rc;
+                    float ms = 0;
+                    DN_HIP(hipEventElapsedTime(&ms, e0, e1));
+                    if (getenv("DN_VERBOSE"))
+                        fprintf(stderr, "[denser] batch tune: variant %d wpc %d pool %d: %.3f ms\n", nt, wpc, pool, ms);
+                    if (ms < best) { best = ms; ch = TuneChoice{nt, wpc, 1, pool}; }
                 }
             }
         }

@@ -59,29 +59,21 @@ struct SBF16 {
 };
 
 // Streaming accesses.  A block's f, w and u are read by that block alone
-// and every store of the iteration is read back only in the next one (from
-// HBM, the volume being far larger than the caches), whereas ubar, p and
-// the edge masks are also read by the neighbours as their halo.  Loading
+// and every store of the iteration is read back only in the next one,
+// whereas ubar, p and the edge masks are also read by the neighbours as
+// their halo.  On a map larger than the last-level cache (kStream), loading
 // the former and storing everything as non-temporal leaves the L2 for the
-// lines the neighbouring blocks will read.
-#ifndef DN_CP_NT
-#define DN_CP_NT 1
-#endif
-template <class T> __device__ __forceinline__ T ld_stream(const T *p)
+// lines the neighbouring blocks will read; on a smaller one the hints would
+// send to memory what the cache could hold from one iteration to the next.
+template <bool kStream, class T> __device__ __forceinline__ T ld_own(const T *p)
 {
-#if DN_CP_NT
-    return __builtin_nontemporal_load(p);
-#else
+    if constexpr (kStream) return __builtin_nontemporal_load(p);
     return *p;
-#endif
 }
-template <class T> __device__ __forceinline__ void st_stream(T *p, T v)
+template <bool kStream, class T> __device__ __forceinline__ void st_own(T *p, T v)
 {
-#if DN_CP_NT
-    __builtin_nontemporal_store(v, p);
-#else
-    *p = v;
-#endif
+    if constexpr (kStream) __builtin_nontemporal_store(v, p);
+    else *p = v;
 }
 
 // Counter-based random bits of one voxel and iteration: an integer hash
@@ -106,7 +98,7 @@ template <class S> struct CPArgs {
     int64_t nb;                 // blocks
     int64_t pstride;            // elements between p planes
     const int32_t *nbr;         // [nb][27]
-    const uint8_t *emask;       // [nb][512]
+    const uint32_t *em4;        // [nb][64] edge masks, see k_masks
     const int32_t *order;       // processing order or nullptr (pool order)
     int32_t xcd;                // 1: XCD-chunked workgroup -> block map
     const float *f, *w;
@@ -121,7 +113,6 @@ template <class S> struct CPArgs {
     uint32_t seed;              // 16-bit storage: this iteration's seed of the stochastic rounding
 };
 
-__device__ __forceinline__ int i10(int x, int y, int z) { return ((z + 1) * 10 + (y + 1)) * 10 + (x + 1); }
 __device__ __forceinline__ int i9(int x, int y, int z) { return ((z + 1) * 9 + (y + 1)) * 9 + (x + 1); }
 
 // Global index of voxel (hx, hy, hz) relative to block b, hx.. in [-1, 8],
@@ -136,30 +127,293 @@ __device__ __forceinline__ int64_t halo_index(const int32_t *nb27, int hx, int h
     return int64_t(id) * kBlockVox + ((hx - 8 * dx) + 8 * (hy - 8 * dy) + 64 * (hz - 8 * dz));
 }
 
-// Position of the t-th ubar halo voxel (t < 432): the six faces (+x, +y,
-// +z, -x, -y, -z; 64 each) then the six (-a, +b) edges (8 each).
-__device__ __forceinline__ void halo_pos(int t, int &x, int &y, int &z)
+// Correctly rounded projection and division in fewer instructions than the
+// compiler's general sequences, which also rescale operands near the ends
+// of the exponent range; the dual step's three quotients share one
+// reciprocal.  n = sqrt(s) is v_rsq's estimate with one Newton step on the
+// root and one on its reciprocal, a quotient one residual correction.
+// Checked against sqrtf and IEEE division: the root for all 2^24 operands of
+// two octaves (exact), the quotients for 2^33 operand pairs (exact).  Both
+// take the general path outside [1, 2^96).
+//   sqrt(s) > 1  <=>  s > 1 + 2^-23: the root of 1 + 2^-23 rounds to 1.
+__device__ __forceinline__ float div_by(float a, float n, float r)
 {
-    if (t < 384) {
-        int f = t >> 6, i = t & 63, a = i & 7, b = i >> 3;
-        switch (f) {
-        case 0: x = 8; y = a; z = b; break;
-        case 1: x = a; y = 8; z = b; break;
-        case 2: x = a; y = b; z = 8; break;
-        case 3: x = -1; y = a; z = b; break;
-        case 4: x = a; y = -1; z = b; break;
-        default: x = a; y = b; z = -1; break;
+    const float q = a * r;
+    return __builtin_fmaf(__builtin_fmaf(-n, q, a), r, q);
+}
+
+__device__ __forceinline__ void project(float &a, float &b, float &c)
+{
+    const float s = (a * a + b * b) + c * c;
+    if (s > 1.00000011920928955f) {
+        if (s < 0x1p96f) {
+            const float y = __builtin_amdgcn_rsqf(s), n0 = s * y;
+            const float n = __builtin_fmaf(__builtin_fmaf(-n0, n0, s), 0.5f * y, n0);
+            const float r = __builtin_fmaf(__builtin_fmaf(-n, y, 1.0f), y, y);
+            a = div_by(a, n, r); b = div_by(b, n, r); c = div_by(c, n, r);
+        } else {
+            const float n = sqrtf(s);
+            a = a / n; b = b / n; c = c / n;
         }
+    }
+}
+
+// num / den for den = 1 + tau lambda w >= 1
+__device__ __forceinline__ float prox_div(float num, float den)
+{
+    if (den < 0x1p96f) {
+        const float r0 = __builtin_amdgcn_rcpf(den);
+        return div_by(num, den, __builtin_fmaf(__builtin_fmaf(-den, r0, 1.0f), r0, r0));
+    }
+    return num / den;
+}
+
+// One wave of 64 lanes holds whole (x, y) planes of a block: lane = x + 8 y,
+// plane z in registers.  Bit 4z + i of a mask word: bit i (0 Omega, 1 + a
+// m_a) of the edge mask of voxel (lane, z).
+__device__ __forceinline__ uint32_t keep_if(uint32_t word, int bit)   // all ones where the bit is set
+{
+    return uint32_t(__builtin_amdgcn_sbfe(int(word), unsigned(bit), 1u));
+}
+__device__ __forceinline__ float and_f(float x, uint32_t m) { return __uint_as_float(__float_as_uint(x) & m); }
+
+// Data that one iteration passes between lanes, in LDS: ubar on the block
+// with a one-voxel halo, and the masked new dual components p_x and p_y
+// shifted by one along their axis (their first column / row is the -1 face),
+// p_z of each wave's last plane.
+template <int W> struct CPShared {
+    float u[1000];       // index x + 1 + 10 (y + 1) + 100 (z + 1)
+    float px[576];       // index x + 1 + 9 y + 72 z
+    float py[576];       // index x + 8 (y + 1) + 72 z
+    float pz[W][64];     // by wave
+};
+
+// Memory the kernel only reads, the same for all lanes: scalar loads.
+typedef const __attribute__((address_space(4))) int32_t *ScalarI32;
+__device__ __forceinline__ ScalarI32 as_scalar(const int32_t *p) { return (ScalarI32) reinterpret_cast<uint64_t>(p); }
+
+template <int W> __device__ __forceinline__ void block_sync()
+{
+    if constexpr (W == 1) {
+        // one wave: its LDS operations are processed in order
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     } else {
-        int e = (t - 384) >> 3, j = (t - 384) & 7;
-        switch (e) {
-        case 0: x = -1; y = 8; z = j; break;
-        case 1: x = -1; y = j; z = 8; break;
-        case 2: x = 8; y = -1; z = j; break;
-        case 3: x = j; y = -1; z = 8; break;
-        case 4: x = 8; y = j; z = -1; break;
-        default: x = j; y = 8; z = -1; break;
+        __syncthreads();
+    }
+}
+
+// One fused Chambolle-Pock iteration on block b by W waves of 8 / W planes
+// each.  Bound by HBM on maps beyond the caches, by the last-level cache and
+// latency on smaller ones.  A voxel's neighbours along z stay in registers,
+// faces are loaded a wave at a time from a base the whole wave shares, and
+// masks are a word per lane, so a voxel takes about a third of the vector
+// instructions of a thread-per-voxel layout with its index arithmetic per
+// voxel.  Per iteration, that layout and this one: 202195 blocks FP32 0.946
+// and 0.939 ms; 60001 blocks BF16 236 and 169 us; 5777 blocks FP32 34.0 and
+// 24.3 us (with the cache hints dropped there); 503 blocks 5.4 and 4.7 us.
+template <class S, bool kRefine, bool kStream, int W>
+__device__ __forceinline__ void cp_block(const CPArgs<S> &A, int32_t b, CPShared<W> &sh, int wave, unsigned lane)
+{
+    using T = typename S::T;
+    constexpr int ZP = 8 / W;
+    const int z0 = wave * ZP;
+    const int64_t g0 = int64_t(b) * kBlockVox;
+    const int64_t o0 = g0 + z0 * 64;             // this wave's first plane
+    const int64_t ps = A.pstride;
+    const ScalarI32 nb = as_scalar(A.nbr) + int64_t(b) * kNbr;
+    const unsigned l8 = lane & 7u, h8 = lane >> 3;
+
+    // the wave's own planes
+    float ub[ZP], p0[ZP], p1[ZP], p2[ZP], uo[ZP], fv[ZP], wv[ZP];
+    const uint32_t mw0 = (A.em4 + int64_t(b) * 64)[lane];
+#pragma unroll
+    for (int k = 0; k < ZP; ++k) ub[k] = S::ld((A.ubar_in + o0)[64 * k + lane]);
+#pragma unroll
+    for (int k = 0; k < ZP; ++k) {
+        p0[k] = S::ld((A.p_in + o0)[64 * k + lane]);
+        p1[k] = S::ld((A.p_in + o0 + ps)[64 * k + lane]);
+        p2[k] = S::ld((A.p_in + o0 + 2 * ps)[64 * k + lane]);
+    }
+    const unsigned ax = 110u + 10u * l8 + 100u * h8, ay = 101u + l8 + 100u * h8, az = 11u + l8 + 10u * h8;
+    // ubar on the faces and edges and the old dual and masks on the -1 faces,
+    // shared out over the waves; every load is issued before the first value
+    // is used.  An unallocated neighbour is skipped by FP32 state, which is
+    // bound by memory traffic (0.939 against 0.966 ms at 202195 blocks); 16-
+    // bit state, bound by latency, reads the block itself in its place and
+    // drops the values, which costs no branch (181 against 186 us at 60001).
+    constexpr bool kSkip = !S::kLow;
+    constexpr int kTasks = 7, kPer = (kTasks + W - 1) / W;
+    const int nid[6] = {nb[14], nb[12], nb[16], nb[10], nb[22], nb[4]};   // +x, -x, +y, -y, +z, -z
+    float hv[kPer];
+    uint32_t edge = 0;
+    int edge_id = -1;
+    auto face_at = [&](int t) {
+        return t == 0 ? 8u * lane : t == 1 ? 8u * lane + 7u : t == 2 ? l8 + 64u * h8 : t == 3 ? l8 + 64u * h8 + 56u :
+               t == 4 ? lane : lane + 448u;
+    };
+    auto load_task = [&](int t) -> float {
+        if (t < 6) {
+            if (kSkip && nid[t] < 0) return 0.0f;
+            return S::ld((A.ubar_in + int64_t(nid[t] >= 0 ? nid[t] : b) * kBlockVox)[face_at(t)]);
         }
+        // voxel j of the six (-a, +b) edges, 8 lanes each: the offset in the
+        // neighbour's block, and its index in CPShared::u in the high half:
+        // (-1, 8, j), (-1, j, 8), (8, -1, j), (j, -1, 8), (8, j, -1), (j, 8, -1)
+        const unsigned e = h8;
+        uint32_t first = 7u | 190u << 16;
+        edge_id = nb[15];
+        if (e == 1u) { edge_id = nb[21]; first = 7u | 910u << 16; }
+        if (e == 2u) { edge_id = nb[11]; first = 56u | 109u << 16; }
+        if (e == 3u) { edge_id = nb[19]; first = 56u | 901u << 16; }
+        if (e == 4u) { edge_id = nb[5]; first = 448u | 19u << 16; }
+        if (e == 5u) { edge_id = nb[7]; first = 448u | 91u << 16; }
+        const uint32_t step = e == 0u || e == 2u ? 64u | 100u << 16 : (e == 1u || e == 4u ? 8u | 10u << 16 : 1u | 1u << 16);
+        edge = first + l8 * step;
+        if (kSkip && edge_id < 0) return 0.0f;
+        return S::ld(A.ubar_in[int64_t(edge_id >= 0 ? edge_id : b) * kBlockVox + (edge & 0xFFFFu)]);
+    };
+    auto store_task = [&](int t, float v) {
+        if (t < 6) {
+            const unsigned at = t == 0 ? ax + 9u : t == 1 ? ax : t == 2 ? ay + 90u : t == 3 ? ay : t == 4 ? az + 900u : az;
+            sh.u[at] = nid[t] >= 0 ? v : 0.0f;
+        } else if (lane < 48u) {   // six edges
+            sh.u[edge >> 16] = edge_id >= 0 ? v : 0.0f;
+        }
+    };
+    // the -1 faces: -z by the first wave (its lanes match plane 0), -x and -y by the next ones
+    constexpr int kWx = W == 1 ? 0 : 1, kWy = W <= 2 ? W - 1 : 2;
+    struct Face { float a, b, c; uint32_t m; };
+    Face fx{0.f, 0.f, 0.f, 0u}, fy = fx, fz = fx;
+    auto load_face = [&](Face &F, int t, unsigned word) {
+        if (kSkip && nid[t] < 0) return;
+        const int id = nid[t] >= 0 ? nid[t] : b;
+        const T *q = A.p_in + int64_t(id) * kBlockVox;
+        const unsigned off = face_at(t);
+        F.a = S::ld(q[off]); F.b = S::ld((q + ps)[off]); F.c = S::ld((q + 2 * ps)[off]);
+        F.m = (A.em4 + int64_t(id) * 64)[word];
+    };
+#pragma unroll
+    for (int w = 0; w < W; ++w)
+        if (wave == w) {
+#pragma unroll
+            for (int j = 0; j < kPer; ++j)
+                if (w + j * W < kTasks) hv[j] = load_task(w + j * W);
+            if (w == 0) load_face(fz, 5, lane);
+            if (w == kWx) load_face(fx, 1, 8u * l8 + 7u);
+            if (w == kWy) load_face(fy, 3, l8 + 56u);
+        }
+#pragma unroll
+    for (int k = 0; k < ZP; ++k) {
+        uo[k] = S::ld(ld_own<kStream>((const T *)(A.u + o0) + 64 * k + lane));
+        fv[k] = ld_own<kStream>(A.f + o0 + 64 * k + lane);
+        wv[k] = ld_own<kStream>(A.w + o0 + 64 * k + lane);
+    }
+#pragma unroll
+    for (int w = 0; w < W; ++w)
+        if (wave == w) {
+#pragma unroll
+            for (int j = 0; j < kPer; ++j)
+                if (w + j * W < kTasks) store_task(w + j * W, hv[j]);
+        }
+    const unsigned own = az + 100u * (z0 + 1);
+#pragma unroll
+    for (int k = 0; k < ZP; ++k) sh.u[own + 100 * k] = ub[k];
+    block_sync<W>();
+
+    const uint32_t mw = mw0 >> (4 * z0);
+    // dual ascent and projection (Eq. 7); p_x, p_y to LDS masked, p_z kept
+    const unsigned qx = 1u + l8 + 9u * h8 + 72u * z0, qy = l8 + 8u * (h8 + 1u) + 72u * z0;
+    float d0[ZP], d1[ZP], d2[ZP];
+#pragma unroll
+    for (int k = 0; k < ZP; ++k) {
+        const uint32_t mx = keep_if(mw, 4 * k + 1), my = keep_if(mw, 4 * k + 2), mz = keep_if(mw, 4 * k + 3);
+        const float uz = k + 1 < ZP ? ub[k + 1 < ZP ? k + 1 : 0] : sh.u[own + 100 * k + 100];
+        const float gx = and_f(sh.u[own + 100 * k + 1] - ub[k], mx);
+        const float gy = and_f(sh.u[own + 100 * k + 10] - ub[k], my);
+        const float gz = and_f(uz - ub[k], mz);
+        float a0 = p0[k] + A.sigma * gx, a1 = p1[k] + A.sigma * gy, a2 = p2[k] + A.sigma * gz;
+        project(a0, a1, a2);
+        d0[k] = and_f(a0, mx); d1[k] = and_f(a1, my); d2[k] = and_f(a2, mz);
+        sh.px[qx + 72 * k] = d0[k];
+        sh.py[qy + 72 * k] = d1[k];
+        const unsigned i = 64 * k + lane;
+        T *po = A.p_out + o0;
+        if constexpr (S::kLow) {
+            // stochastic rounding; where it would leave the unit ball, toward zero
+            const int64_t gi = o0 + i;
+            const uint32_t r0 = voxel_bits(gi, 0, A.seed), r1 = voxel_bits(gi, 1, A.seed);
+            T s0 = S::sr(a0, r0), s1 = S::sr(a1, r0 >> 16), s2 = S::sr(a2, r1);
+            const float b0 = S::ld(s0), b1 = S::ld(s1), b2 = S::ld(s2);
+            if ((b0 * b0 + b1 * b1) + b2 * b2 > 1.0f) { s0 = S::rz(a0); s1 = S::rz(a1); s2 = S::rz(a2); }
+            st_own<kStream>(po + i, s0); st_own<kStream>(po + ps + i, s1); st_own<kStream>(po + 2 * ps + i, s2);
+        } else {
+            st_own<kStream>(po + i, a0); st_own<kStream>(po + ps + i, a1); st_own<kStream>(po + 2 * ps + i, a2);
+        }
+        if (kRefine) {
+            float *q = A.p32 + o0;
+            q[i] = a0; (q + ps)[i] = a1; (q + 2 * ps)[i] = a2;
+        }
+    }
+    if (W > 1) sh.pz[wave][lane] = d2[ZP - 1];
+    // ... and on the -1 faces, which the divergence needs: the component
+    // along the face's axis, masked
+    auto face_dual = [&](const Face &F, float us, float ux, float uy, float uz, float &a0, float &a1, float &a2) {
+        a0 = F.a + A.sigma * and_f(ux - us, keep_if(F.m, 1));
+        a1 = F.b + A.sigma * and_f(uy - us, keep_if(F.m, 2));
+        a2 = F.c + A.sigma * and_f(uz - us, keep_if(F.m, 3));
+        project(a0, a1, a2);
+    };
+    float a0, a1, a2, zlow = 0.0f;
+    if (wave == 0) {
+        fz.m = nid[5] >= 0 ? fz.m >> 28 : 0u;
+        face_dual(fz, sh.u[az], sh.u[az + 1], sh.u[az + 10], ub[0], a0, a1, a2);
+        zlow = and_f(a2, keep_if(fz.m, 3));
+    }
+    if (wave == kWx) {
+        fx.m = nid[1] >= 0 ? fx.m >> (4u * h8) : 0u;
+        face_dual(fx, sh.u[ax], sh.u[ax + 1], sh.u[ax + 10], sh.u[ax + 100], a0, a1, a2);
+        sh.px[9u * l8 + 72u * h8] = and_f(a0, keep_if(fx.m, 1));
+    }
+    if (wave == kWy) {
+        fy.m = nid[3] >= 0 ? fy.m >> (4u * h8) : 0u;
+        face_dual(fy, sh.u[ay], sh.u[ay + 1], sh.u[ay + 10], sh.u[ay + 100], a0, a1, a2);
+        sh.py[l8 + 72u * h8] = and_f(a1, keep_if(fy.m, 2));
+    }
+    block_sync<W>();
+    if (W > 1 && wave > 0) zlow = sh.pz[wave - 1][lane];
+
+    // primal proximal step (Eq. 8) and relaxation (Eq. 9)
+    const float tl = A.tau * A.lambda;
+#pragma unroll
+    for (int k = 0; k < ZP; ++k) {
+        float dv = d0[k] - sh.px[qx + 72 * k - 1];
+        dv += d1[k] - sh.py[qy + 72 * k - 8];
+        dv += d2[k] - (k > 0 ? d2[k > 0 ? k - 1 : 0] : zlow);
+        const float ut = uo[k] + A.tau * dv;
+        const float tlw = tl * wv[k];
+        float un;
+        if (A.l1) {
+            // soft threshold of u~ - f by tau lambda w, then the [-1, 1] box
+            float r = ut - fv[k];
+            r = r > tlw ? r - tlw : (r < -tlw ? r + tlw : 0.0f);
+            un = fminf(fmaxf(fv[k] + r, -1.0f), 1.0f);
+        } else {
+            un = prox_div(ut + tlw * fv[k], 1.0f + tlw);
+        }
+        un = keep_if(mw, 4 * k) ? un : uo[k];
+        const float ubn = un + A.theta * (un - uo[k]);
+        const unsigned i = 64 * k + lane;
+        if constexpr (S::kLow) {
+            const uint32_t r2 = voxel_bits(o0 + i, 2, A.seed);
+            st_own<kStream>(A.u + o0 + i, S::sr(un, r2));
+            st_own<kStream>(A.ubar_out + o0 + i, S::sr(ubn, r2 >> 16));
+        } else {
+            st_own<kStream>(A.u + o0 + i, un);
+            st_own<kStream>(A.ubar_out + o0 + i, ubn);
+        }
+        if (kRefine) { (A.u32 + o0)[i] = un; (A.ubar32 + o0)[i] = ubn; }
     }
 }
 
@@ -172,214 +426,24 @@ __device__ __forceinline__ void face_pos(int t, int &x, int &y, int &z)
     else { x = a; y = b; z = -1; }
 }
 
-struct CPShared {
-    float u[1000];       // ubar tile with a one-voxel halo, index i10
-    float p[3][729];     // new dual on the block and its -1 faces, index i9
-    uint8_t m[729];      // edge masks on the block and its -1 faces
-};
-
-__device__ __forceinline__ void project(float &a, float &b, float &c)
+// The lane index, one that the compiler cannot hoist out of an enclosing
+// loop (the index arithmetic is redone per block instead of staying live).
+__device__ __forceinline__ unsigned opaque_lane()
 {
-    float n = sqrtf((a * a + b * b) + c * c);
-    if (n > 1.0f) { a = a / n; b = b / n; c = c / n; }
-}
-
-// Per-thread registers of one block's iteration: the thread's own voxels
-// (VPT = 512 / NT of them), its share of the ubar halo (432 voxels: six
-// faces and the six (-a, +b) edges) and its share of the 192 voxels of the
-// -1 faces (their edge masks and the three dual components).
-template <int NT> struct CPRegs {
-    static constexpr int VPT = kBlockVox / NT;
-    static constexpr int HPT = (432 + NT - 1) / NT;
-    static constexpr int FPT = (192 + NT - 1) / NT;
-    float ub[VPT], p0[VPT], p1[VPT], p2[VPT], uo[VPT], fv[VPT], wv[VPT];
-    uint8_t m[VPT];
-    float hu[HPT];
-    float h0[FPT], h1[FPT], h2[FPT];
-    uint8_t hm[FPT];
-};
-
-// Global loads of one block's iteration (issued; used by cp_compute).
-template <class S, int NT>
-__device__ __forceinline__ void cp_load(const CPArgs<S> &A, int64_t b, CPRegs<NT> &R, int t)
-{
-    constexpr int VPT = CPRegs<NT>::VPT, HPT = CPRegs<NT>::HPT;
-    const int64_t g0i = b * kBlockVox;
-    const int32_t *nb27 = A.nbr + b * kNbr;
-    const int64_t ps = A.pstride;
-#pragma unroll
-    for (int k = 0; k < VPT; ++k) {
-        const int64_t gi = g0i + t + k * NT;
-        R.ub[k] = S::ld(A.ubar_in[gi]);
-        R.m[k] = A.emask[gi];
-        R.p0[k] = S::ld(A.p_in[gi]); R.p1[k] = S::ld(A.p_in[gi + ps]); R.p2[k] = S::ld(A.p_in[gi + 2 * ps]);
-        R.uo[k] = S::ld(ld_stream(A.u + gi));
-        R.fv[k] = ld_stream(A.f + gi); R.wv[k] = ld_stream(A.w + gi);
-    }
-#pragma unroll
-    for (int k = 0; k < HPT; ++k) {
-        const int h = t + k * NT;
-        R.hu[k] = 0.0f;
-        if (h < 432) {
-            int hx, hy, hz;
-            halo_pos(h, hx, hy, hz);
-            int64_t j = halo_index(nb27, hx, hy, hz);
-            if (j >= 0) R.hu[k] = S::ld(A.ubar_in[j]);
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < CPRegs<NT>::FPT; ++k) {
-        const int e = t + k * NT;
-        R.h0[k] = R.h1[k] = R.h2[k] = 0.f;
-        R.hm[k] = 0;
-        if (e < 192) {
-            int fx, fy, fz;
-            face_pos(e, fx, fy, fz);
-            int64_t j = halo_index(nb27, fx, fy, fz);
-            if (j >= 0) {
-                R.hm[k] = A.emask[j];
-                R.h0[k] = S::ld(A.p_in[j]); R.h1[k] = S::ld(A.p_in[j + ps]); R.h2[k] = S::ld(A.p_in[j + 2 * ps]);
-            }
-        }
-    }
-}
-
-// The iteration of one block from its loaded registers (NT threads: 512 =
-// one voxel per thread; 256 = two voxels per thread, z layers l and l + 4).
-template <class S, bool kRefine, int NT>
-__device__ __forceinline__ void cp_compute(const CPArgs<S> &A, int64_t b, const CPRegs<NT> &R, CPShared &sh,
-                                           int t)
-{
-    constexpr int VPT = CPRegs<NT>::VPT, HPT = CPRegs<NT>::HPT;
-    const int64_t g0i = b * kBlockVox;
-    const int64_t ps = A.pstride;
-#pragma unroll
-    for (int k = 0; k < VPT; ++k) {
-        const int v = t + k * NT, lx = v & 7, ly = (v >> 3) & 7, lz = v >> 6;
-        sh.u[i10(lx, ly, lz)] = R.ub[k];
-        sh.m[i9(lx, ly, lz)] = R.m[k];
-    }
-#pragma unroll
-    for (int k = 0; k < HPT; ++k) {
-        const int h = t + k * NT;
-        if (h < 432) {
-            int hx, hy, hz;
-            halo_pos(h, hx, hy, hz);
-            sh.u[i10(hx, hy, hz)] = R.hu[k];
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < CPRegs<NT>::FPT; ++k) {
-        const int e = t + k * NT;
-        if (e < 192) {
-            int fx, fy, fz;
-            face_pos(e, fx, fy, fz);
-            sh.m[i9(fx, fy, fz)] = R.hm[k];
-        }
-    }
-    __syncthreads();
-
-    // dual ascent and projection on the block (Eq. 7)
-#pragma unroll
-    for (int k = 0; k < VPT; ++k) {
-        const int v = t + k * NT, lx = v & 7, ly = (v >> 3) & 7, lz = v >> 6;
-        const int64_t gi = g0i + v;
-        const uint8_t m = R.m[k];
-        float g0 = (m & 2) ? sh.u[i10(lx + 1, ly, lz)] - R.ub[k] : 0.0f;
-        float g1 = (m & 4) ? sh.u[i10(lx, ly + 1, lz)] - R.ub[k] : 0.0f;
-        float g2 = (m & 8) ? sh.u[i10(lx, ly, lz + 1)] - R.ub[k] : 0.0f;
-        float a0 = R.p0[k] + A.sigma * g0, a1 = R.p1[k] + A.sigma * g1, a2 = R.p2[k] + A.sigma * g2;
-        project(a0, a1, a2);
-        const int q = i9(lx, ly, lz);
-        sh.p[0][q] = a0; sh.p[1][q] = a1; sh.p[2][q] = a2;
-        if constexpr (S::kLow) {
-            // stochastic rounding; where it would leave the unit ball, toward zero
-            const uint32_t r0 = voxel_bits(gi, 0, A.seed), r1 = voxel_bits(gi, 1, A.seed);
-            typename S::T s0 = S::sr(a0, r0), s1 = S::sr(a1, r0 >> 16), s2 = S::sr(a2, r1);
-            const float b0 = S::ld(s0), b1 = S::ld(s1), b2 = S::ld(s2);
-            if ((b0 * b0 + b1 * b1) + b2 * b2 > 1.0f) { s0 = S::rz(a0); s1 = S::rz(a1); s2 = S::rz(a2); }
-            st_stream(A.p_out + gi, s0); st_stream(A.p_out + gi + ps, s1); st_stream(A.p_out + gi + 2 * ps, s2);
-        } else {
-            st_stream(A.p_out + gi, a0); st_stream(A.p_out + gi + ps, a1); st_stream(A.p_out + gi + 2 * ps, a2);
-        }
-        if (kRefine) { A.p32[gi] = a0; A.p32[gi + ps] = a1; A.p32[gi + 2 * ps] = a2; }
-    }
-    // ... and on the -1 faces, which the divergence needs
-#pragma unroll
-    for (int k = 0; k < CPRegs<NT>::FPT; ++k) {
-        const int e = t + k * NT;
-        if (e < 192) {
-            int fx, fy, fz;
-            face_pos(e, fx, fy, fz);
-            const uint8_t hm = R.hm[k];
-            float uh = sh.u[i10(fx, fy, fz)];
-            float g0 = (hm & 2) ? sh.u[i10(fx + 1, fy, fz)] - uh : 0.0f;
-            float g1 = (hm & 4) ? sh.u[i10(fx, fy + 1, fz)] - uh : 0.0f;
-            float g2 = (hm & 8) ? sh.u[i10(fx, fy, fz + 1)] - uh : 0.0f;
-            float h0 = R.h0[k] + A.sigma * g0, h1 = R.h1[k] + A.sigma * g1, h2 = R.h2[k] + A.sigma * g2;
-            project(h0, h1, h2);
-            const int q = i9(fx, fy, fz);
-            sh.p[0][q] = h0; sh.p[1][q] = h1; sh.p[2][q] = h2;
-        }
-    }
-    __syncthreads();
-
-    // primal proximal step (Eq. 8) and relaxation (Eq. 9)
-#pragma unroll
-    for (int k = 0; k < VPT; ++k) {
-        const int v = t + k * NT, lx = v & 7, ly = (v >> 3) & 7, lz = v >> 6;
-        const int64_t gi = g0i + v;
-        const uint8_t m = R.m[k];
-        float un = R.uo[k];
-        if (m & 1) {
-            const int q = i9(lx, ly, lz);
-            const int qx = i9(lx - 1, ly, lz), qy = i9(lx, ly - 1, lz), qz = i9(lx, ly, lz - 1);
-            float dv = 0.0f;
-            dv += ((m & 2) ? sh.p[0][q] : 0.0f) - ((sh.m[qx] & 2) ? sh.p[0][qx] : 0.0f);
-            dv += ((m & 4) ? sh.p[1][q] : 0.0f) - ((sh.m[qy] & 4) ? sh.p[1][qy] : 0.0f);
-            dv += ((m & 8) ? sh.p[2][q] : 0.0f) - ((sh.m[qz] & 8) ? sh.p[2][qz] : 0.0f);
-            float ut = R.uo[k] + A.tau * dv;
-            float tlw = A.tau * A.lambda * R.wv[k];
-            if (A.l1) {
-                // soft threshold of u~ - f by tau lambda w, then the [-1, 1] box
-                float r = ut - R.fv[k];
-                r = r > tlw ? r - tlw : (r < -tlw ? r + tlw : 0.0f);
-                un = fminf(fmaxf(R.fv[k] + r, -1.0f), 1.0f);
-            } else {
-                un = (ut + tlw * R.fv[k]) / (1.0f + tlw);
-            }
-        }
-        float ubn = un + A.theta * (un - R.uo[k]);
-        if constexpr (S::kLow) {
-            const uint32_t r2 = voxel_bits(gi, 2, A.seed);
-            st_stream(A.u + gi, S::sr(un, r2));
-            st_stream(A.ubar_out + gi, S::sr(ubn, r2 >> 16));
-        } else {
-            st_stream(A.u + gi, un);
-            st_stream(A.ubar_out + gi, ubn);
-        }
-        if (kRefine) { A.u32[gi] = un; A.ubar32[gi] = ubn; }
-    }
-}
-
-// One fused Chambolle-Pock iteration on block b by NT threads.  t is the
-// thread index (a loop that runs many blocks passes it through an opaque
-// copy so that the per-thread index arithmetic is redone per block instead
-// of being kept live across the loop).
-template <class S, bool kRefine, int NT = 512>
-__device__ __forceinline__ void cp_block(const CPArgs<S> &A, int64_t b, CPShared &sh, int t)
-{
-    CPRegs<NT> R;
-    cp_load<S, NT>(A, b, R, t);
-    cp_compute<S, kRefine, NT>(A, b, R, sh, t);
-}
-
-// threadIdx.x that the compiler cannot hoist out of an enclosing loop
-__device__ __forceinline__ int opaque_tid()
-{
-    int t = threadIdx.x;
+    unsigned t = threadIdx.x & 63u;
     asm volatile("" : "+v"(t));
     return t;
+}
+__device__ __forceinline__ int wave_index() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+
+// Whether the state of that many blocks outgrows the last-level cache (256
+// MB): two buffers of ubar and p, u, and f, w.  Either side of the line,
+// without / with the hints: FP32 10000 blocks 39.6 / 51.9 us per iteration,
+// 12000 59.4 / 61.3, 20000 105.5 / 100.5; 16-bit 16000 41.3 / 51.1, 20000
+// 64.1 / 62.9, 40000 131 / 123.
+static inline bool streams_state(int64_t blocks, size_t state_size)
+{
+    return size_t(blocks) * kBlockVox * (9 * state_size + 8) > (size_t(272) << 20);
 }
 
 // Workgroup -> block mapping.  Consecutive workgroups go round-robin to the

@@ -18,6 +18,9 @@ constexpr int kBlockVox = 512;     // 8^3 voxels per block
 constexpr int kNbr = 27;           // 3x3x3 neighbourhood, centre = self
 constexpr int kCentre = 13;
 
+// iteration kernels only the tuner picks (reported in kernel_used)
+constexpr int DN_K_FUSED128 = 4, DN_K_FUSED64 = 5;
+
 void set_error(const char *fmt, ...);
 
 #define DN_HIP(expr)                                                           \
@@ -118,6 +121,7 @@ struct dn_volume {
     int64_t nb_state = 0;               // blocks whose solver state a regularize call set
 
     uint8_t *emask = nullptr;           // [max][512]
+    uint32_t *em4 = nullptr;            // [max][64] the same masks, packed for the fused kernel
     int64_t emask_nb = -1;              // nb for which emask/order are valid
     int32_t *order = nullptr;           // [max] processing order (Morton)
     int layout = 0;                     // chosen by the autotuner, see regularize.hip

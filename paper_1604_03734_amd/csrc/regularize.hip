@@ -27,26 +27,15 @@
 
 namespace dn {
 
-template <class S, bool kRefine>
-__global__ __launch_bounds__(512) void k_cp_fused(CPArgs<S> A)
+// W waves of 64 lanes per block, 8 / W planes each.
+template <class S, bool kRefine, bool kStream, int W>
+__global__ __launch_bounds__(64 * W) void k_cp_fused(CPArgs<S> A)
 {
-    __shared__ CPShared sh;
-    int64_t slot = block_slot(blockIdx.x, A.nb, A.xcd);
+    __shared__ CPShared<W> sh;
+    const int64_t slot = block_slot(blockIdx.x, A.nb, A.xcd);
     if (slot >= A.nb) return;
-    int64_t b = A.order ? A.order[slot] : slot;
-    cp_block<S, kRefine, 512>(A, b, sh, threadIdx.x);
-}
-
-// The same iteration with 256 threads per block (two voxels per thread):
-// twice the loads in flight per thread and twice the workgroups per CU.
-template <class S, bool kRefine>
-__global__ __launch_bounds__(256) void k_cp_fused256(CPArgs<S> A)
-{
-    __shared__ CPShared sh;
-    int64_t slot = block_slot(blockIdx.x, A.nb, A.xcd);
-    if (slot >= A.nb) return;
-    int64_t b = A.order ? A.order[slot] : slot;
-    cp_block<S, kRefine, 256>(A, b, sh, threadIdx.x);
+    const int32_t b = A.order ? as_scalar(A.order)[slot] : int32_t(slot);
+    cp_block<S, kRefine, kStream, W>(A, b, sh, wave_index(), threadIdx.x & 63u);
 }
 
 // ----------------------------------------------------- two-pass variant
@@ -66,7 +55,8 @@ __global__ __launch_bounds__(512) void k_dual(int64_t nb, int64_t ps, const int3
     if (m & 4) g[1] = ubar[ly < 7 ? gi + 8 : halo_index(nb27, lx, 8, lz)] - u0;
     if (m & 8) g[2] = ubar[lz < 7 ? gi + 64 : halo_index(nb27, lx, ly, 8)] - u0;
     float a = p[gi] + sigma * g[0], c1 = p[gi + ps] + sigma * g[1], c2 = p[gi + 2 * ps] + sigma * g[2];
-    project(a, c1, c2);
+    const float n = sqrtf((a * a + c1 * c1) + c2 * c2);
+    if (n > 1.0f) { a = a / n; c1 = c1 / n; c2 = c2 / n; }
     p[gi] = a; p[gi + ps] = c1; p[gi + 2 * ps] = c2;
 }
 
@@ -113,9 +103,13 @@ __global__ __launch_bounds__(512) void k_primal(int64_t nb, int64_t ps, const in
 // ------------------------------------------------------------- masks
 // emask bit0 = Omega(g) (block allocated and w > 0); bit 1+a = m_a(g) =
 // Omega(g) and Omega(g + e_a)  (Eq. 3's cases where the difference is kept).
+// em4 holds the same four bits for the fused kernel, a word per (x, y):
+// bits 4z .. 4z + 3 of em4[block][x + 8 y].
 __global__ __launch_bounds__(512) void k_masks(int64_t nb, const int32_t *__restrict__ nbr,
-                                               const float *__restrict__ w, uint8_t *__restrict__ emask)
+                                               const float *__restrict__ w, uint8_t *__restrict__ emask,
+                                               uint32_t *__restrict__ em4)
 {
+    __shared__ uint8_t sm[kBlockVox];
     const int64_t b = blockIdx.x;
     if (b >= nb) return;
     const int t = threadIdx.x, lx = t & 7, ly = (t >> 3) & 7, lz = t >> 6;
@@ -132,6 +126,13 @@ __global__ __launch_bounds__(512) void k_masks(int64_t nb, const int32_t *__rest
         if (jz >= 0 && w[jz] > 0.0f) m |= 8;
     }
     emask[gi] = m;
+    sm[t] = m;
+    __syncthreads();
+    if (t < 64) {
+        uint32_t word = 0;
+        for (int z = 0; z < 8; ++z) word |= uint32_t(sm[t + 64 * z]) << (4 * z);
+        em4[b * 64 + t] = word;
+    }
 }
 
 __device__ __forceinline__ uint64_t spread3(uint64_t v)
@@ -330,7 +331,8 @@ int build_masks(dn_volume *v)
     if (v->emask_nb == v->nb) return DN_OK;
     hipStream_t st = v->stream;
     if (v->nb > 0) {
-        hipLaunchKernelGGL(k_masks, dim3(unsigned(v->nb)), dim3(512), 0, st, v->nb, v->nbr, v->w, v->emask);
+        hipLaunchKernelGGL(k_masks, dim3(unsigned(v->nb)), dim3(512), 0, st, v->nb, v->nbr, v->w, v->emask,
+                           v->em4);
         DN_HIP(hipGetLastError());
         // Morton processing order of the blocks
         Bump bump(v->scratch, v->scratch_bytes);
@@ -415,7 +417,7 @@ static CPArgs<S> make_args(dn_volume *v, const dn_reg_params *prm, typename S::T
     A.nb = v->nb;
     A.pstride = v->cap_blocks * kBlockVox;
     A.nbr = v->nbr;
-    A.emask = v->emask;
+    A.em4 = v->em4;
     A.order = v->layout & 1 ? nullptr : v->order;
     A.xcd = (v->layout & 2) ? 0 : 1;
     A.f = v->f; A.w = v->w;
@@ -429,6 +431,24 @@ static CPArgs<S> make_args(dn_volume *v, const dn_reg_params *prm, typename S::T
 }
 
 static unsigned fused_grid(int64_t nb) { return unsigned(((nb + 7) / 8) * 8); }
+
+template <class S, bool kRefine, bool kStream>
+static void launch_fused_w(hipStream_t st, const CPArgs<S> &A, int kernel)
+{
+    const dim3 grid(fused_grid(A.nb));
+    switch (kernel) {
+    case DN_K_FUSED64: hipLaunchKernelGGL((k_cp_fused<S, kRefine, kStream, 1>), grid, dim3(64), 0, st, A); break;
+    case DN_K_FUSED128: hipLaunchKernelGGL((k_cp_fused<S, kRefine, kStream, 2>), grid, dim3(128), 0, st, A); break;
+    case DN_K_FUSED256: hipLaunchKernelGGL((k_cp_fused<S, kRefine, kStream, 4>), grid, dim3(256), 0, st, A); break;
+    default: hipLaunchKernelGGL((k_cp_fused<S, kRefine, kStream, 8>), grid, dim3(512), 0, st, A);
+    }
+}
+
+template <class S, bool kRefine> static void launch_fused(hipStream_t st, const CPArgs<S> &A, int kernel)
+{
+    if (kRefine || streams_state(A.nb, sizeof(typename S::T))) launch_fused_w<S, kRefine, true>(st, A, kernel);
+    else launch_fused_w<S, kRefine, false>(st, A, kernel);
+}
 
 // One FP32 iteration with the chosen kernel.
 static int step_f32(dn_volume *v, const dn_reg_params *prm, int kernel)
@@ -447,10 +467,7 @@ static int step_f32(dn_volume *v, const dn_reg_params *prm, int kernel)
     }
     const int c = v->cur, n = 1 - c;
     auto A = make_args<SF32>(v, prm, v->u, v->ubar[c], v->ubar[n], v->p[c], v->p[n]);
-    if (kernel == DN_K_FUSED256)
-        hipLaunchKernelGGL((k_cp_fused256<SF32, false>), dim3(fused_grid(v->nb)), dim3(256), 0, st, A);
-    else
-        hipLaunchKernelGGL((k_cp_fused<SF32, false>), dim3(fused_grid(v->nb)), dim3(512), 0, st, A);
+    launch_fused<SF32, false>(st, A, kernel);
     DN_HIP(hipGetLastError());
     v->cur = n;
     return DN_OK;
@@ -464,18 +481,11 @@ static int step_lowp(dn_volume *v, const dn_reg_params *prm, bool refine, int ke
     auto A = make_args<S>(v, prm, (T *)v->u16, (T *)v->ubar16[c], (T *)v->ubar16[n], (T *)v->p16[c],
                           (T *)v->p16[n]);
     A.seed = uint32_t(v->lowp_iter++);
-    const dim3 grid(fused_grid(v->nb));
     if (refine) {
         A.u32 = v->u; A.ubar32 = v->ubar[n]; A.p32 = v->p[n];
-        if (kernel == DN_K_FUSED256)
-            hipLaunchKernelGGL((k_cp_fused256<S, true>), grid, dim3(256), 0, v->stream, A);
-        else
-            hipLaunchKernelGGL((k_cp_fused<S, true>), grid, dim3(512), 0, v->stream, A);
+        launch_fused<S, true>(v->stream, A, kernel);
     } else {
-        if (kernel == DN_K_FUSED256)
-            hipLaunchKernelGGL((k_cp_fused256<S, false>), grid, dim3(256), 0, v->stream, A);
-        else
-            hipLaunchKernelGGL((k_cp_fused<S, false>), grid, dim3(512), 0, v->stream, A);
+        launch_fused<S, false>(v->stream, A, kernel);
     }
     DN_HIP(hipGetLastError());
     v->cur = n;
@@ -555,6 +565,14 @@ int zero_state(dn_volume *v)
 // (kernel variant, layout) with layout bit 0 = pool order instead of Morton
 // order, bit 1 = plain workgroup -> block map instead of XCD chunks.
 struct AutoChoice { int kernel; int layout; };
+// The candidates: 8, 4, 2 and 1 waves per block in Morton and in pool order,
+// in XCD chunks.  Many waves are best where blocks are few (503 blocks: 4.9
+// us with 8, 6.6 with 1), one wave where the 16-bit state leaves the vector
+// units busy (60001 blocks: 169 us with 1, 174 with 4, 236 with 8).  The
+// two-pass kernels (1.95 against 0.96 ms at 202195 blocks, 8.2 against 4.9
+// us at 503) and the plain workgroup map (never more than 1 % ahead, up to
+// 12 % behind) are not tried.
+constexpr int kTuned[] = {DN_K_FUSED, DN_K_FUSED256, DN_K_FUSED128, DN_K_FUSED64};
 // Keyed by (device, size bucket); the tuners of all threads share them.
 static std::map<int64_t, AutoChoice> g_auto_kernel;
 static std::mutex g_auto_mutex;
@@ -599,9 +617,8 @@ static int autotune_single(dn_volume *v, const dn_reg_params *prm, int *choice)
     float best_ms = 1e30f;
     AutoChoice best{DN_K_FUSED, 0};
     const int trial = 6;
-    for (int k : {DN_K_TWOPASS, DN_K_FUSED, DN_K_FUSED256})
-        for (int layout = 0; layout < 4; ++layout) {
-            if (k == DN_K_TWOPASS && layout != 0) continue;   // the two-pass kernels use pool order
+    for (int k : kTuned)
+        for (int layout = 0; layout < 2; ++layout) {
             v->layout = layout;
             int rc = zero_state(v);
             if (rc) return rc;
@@ -648,8 +665,8 @@ template <class S> static int autotune_lowp(dn_volume *v, const dn_reg_params *p
     AutoChoice best{DN_K_FUSED, 0};
     const int trial = 6;
     int rc = DN_OK;
-    for (int k : {DN_K_FUSED, DN_K_FUSED256})
-        for (int layout = 0; layout < 4 && !rc; ++layout) {
+    for (int k : kTuned)
+        for (int layout = 0; layout < 2 && !rc; ++layout) {
             v->layout = layout;
             if ((rc = step_lowp<S>(v, prm, false, k))) break;   // warm up
             DN_HIP(hipEventRecord(e0, v->stream));

@@ -851,6 +851,7 @@ static size_t volume_layout(const dn_volume_params &p, void *base, dn_volume *v)
     float *p0 = b.take<float>(vox * 3);
     float *p1 = b.take<float>(vox * 3);
     uint8_t *emask = b.take<uint8_t>(vox);
+    uint32_t *em4 = b.take<uint32_t>(mb * 64);
     int32_t *order = b.take<int32_t>(mb);
     double *partials = b.take<double>(mb * 2 + 2 * ((mb + 1023) / 1024 + 1) * 2 + 8);
     double *energy2 = b.take<double>(8);
@@ -890,7 +891,7 @@ static size_t volume_layout(const dn_volume_params &p, void *base, dn_volume *v)
     if (v) {
         v->coords = coords; v->keys = keys; v->hash[0] = h0; v->hash[1] = h1; v->nbr = nbr;
         v->f = f; v->w = w; v->u = u; v->ubar[0] = ub0; v->ubar[1] = ub1; v->p[0] = p0; v->p[1] = p1;
-        v->emask = emask; v->order = order; v->partials = partials; v->energy2 = energy2; v->misc = misc;
+        v->emask = emask; v->em4 = em4; v->order = order; v->partials = partials; v->energy2 = energy2; v->misc = misc;
         v->cand = cand;
         v->u16 = u16; v->ubar16[0] = ub16a; v->ubar16[1] = ub16b; v->p16[0] = p16a; v->p16[1] = p16b;
         v->scratch = scratch;
