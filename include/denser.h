@@ -195,6 +195,14 @@ int dn_volume_clear(dn_volume *vol);
 /* Change the stream subsequent calls are ordered on. */
 int dn_set_stream(dn_volume *vol, void *hip_stream);
 
+/* Optional: pinned host memory (DN_REPORT_BYTES, 8-byte aligned, the
+ * caller's, valid until the volume is destroyed or another buffer is set) to
+ * which kernels write the few words a call hands back, instead of a copy out
+ * of the arena per call.  NULL: back to copies.  DN_E_INVALID if the memory
+ * is not pinned.  Synchronises. */
+#define DN_REPORT_BYTES 64
+int dn_set_report_buffer(dn_volume *vol, void *pinned_host, size_t bytes);
+
 /* Number of allocated blocks (host value; no synchronisation needed). */
 int64_t dn_num_blocks(const dn_volume *vol);
 

@@ -17,6 +17,10 @@ namespace dn {
 constexpr int kBlockVox = 512;     // 8^3 voxels per block
 constexpr int kNbr = 27;           // 3x3x3 neighbourhood, centre = self
 constexpr int kCentre = 13;
+constexpr int kMaxNew = 4096;      // new keys a frame's fast insertion takes
+constexpr int kNewSet = 16384;     // slots of the set they are gathered in
+// words of dn_volume::misc
+constexpr int kMiscCells = 20, kMiscListed = 21, kMiscNew = 22, kMiscFull = 23, kMiscEnd = 24, kMiscObs = 25, kMiscReport = 8;   // 8 words
 
 // iteration kernels only the tuner picks (reported in kernel_used)
 constexpr int DN_K_FUSED128 = 4, DN_K_FUSED64 = 5;
@@ -77,7 +81,7 @@ struct InsertScratch {
     uint64_t *newraw, *sorted, *newk, *ksorted;
     int32_t *pos0, *pos1;               // candidate positions (order-keeping insertion)
     int32_t *ids0, *ids1;
-    uint32_t *home, *home2;
+    uint32_t *home;
     int64_t *dm, *runmax;
     void *tmp;
     size_t tmp_bytes;
@@ -101,6 +105,13 @@ struct dn_volume {
     uint64_t *keys = nullptr;    // [max] packed keys, pool order
     int32_t *hash[2] = {nullptr, nullptr};  // [slots][4], double buffered
     int cur_hash = 0;
+    uint32_t *hord_home[2] = {nullptr, nullptr};   // [max] the keys of each table in (home, key)
+    int32_t *hord_ids[2] = {nullptr, nullptr};     // order: home buckets and block ids
+    // new keys of one allocation call
+    uint64_t *new_set = nullptr;                   // [kNewSet] hash set, empty at rest
+    uint64_t *new_key = nullptr, *sort_key = nullptr;                       // [kMaxNew], as listed / in
+    uint32_t *new_home = nullptr, *new_slot = nullptr, *sort_home = nullptr;  // (home, key) order
+    int32_t *sort_id = nullptr;
     int32_t *nbr = nullptr;      // [max][27]
 
     // fused data
@@ -136,6 +147,9 @@ struct dn_volume {
     int64_t *misc = nullptr;            // small device counters (256 bytes)
     char *scratch = nullptr;            // per-call scratch, reused by every call
     size_t scratch_bytes = 0;
+    // the caller's pinned words that kernels report to (null: misc + kMiscReport,
+    // copied back): as the device and as the host addresses them
+    int64_t *report = nullptr, *report_host = nullptr;
     int64_t host_stage[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // host side of small read-backs
 };
 
@@ -153,6 +167,8 @@ int reduce_pairs(dn_volume *v, int64_t n);
 // volume.hip
 int volume_sync(dn_volume *v);
 int read_back(dn_volume *v, const void *dev, size_t bytes);   // into v->host_stage, synchronises
+int64_t *report(dn_volume *v);                                // up to 8 words a kernel writes ...
+int fetch_report(dn_volume *v, int words);                    // ... into v->host_stage, synchronises
 // extract.hip
 size_t extract_scratch(int64_t n_blocks);
 }  // namespace dn

@@ -33,6 +33,16 @@ int read_back(dn_volume *v, const void *dev, size_t bytes)
     return DN_OK;
 }
 
+int64_t *report(dn_volume *v) { return v->report ? v->report : v->misc + kMiscReport; }
+
+int fetch_report(dn_volume *v, int words)
+{
+    if (!v->report) return read_back(v, v->misc + kMiscReport, size_t(words) * 8);
+    DN_HIP(hipStreamSynchronize(v->stream));
+    memcpy(v->host_stage, v->report_host, size_t(words) * 8);
+    return DN_OK;
+}
+
 int volume_sync(dn_volume *v)
 {
     DN_HIP(hipStreamSynchronize(v->stream));
@@ -89,49 +99,77 @@ __device__ inline bool depth_ok(float d, double maxd)
 
 // Amanatides-Woo traversal of a -> b on the unit grid (ties x before y
 // before z, only axes with steps left towards the end cell); nothing is
-// visited if an end point lies beyond `limit` cells.  Shared by the depth
-// band, the laser band and the laser fusion walks.
+// visited if an end point lies beyond `limit` cells (at most 1e9, so that
+// cells and step counts fit 32 bits).  Shared by the depth band, the laser
+// band and the laser fusion walks.
+struct Walk {
+    int32_t k[3], e[3], step[3];     // cell, end cell
+    double tmax[3], tdel[3];         // an axis without steps left has tmax = infinity
+    // false: nothing to visit
+    __device__ __forceinline__ bool start(const double a[3], const double b[3], double limit)
+    {
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            if (!(fabs(a[i]) < limit && fabs(b[i]) < limit)) return false;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            k[i] = int32_t(floor(a[i]));
+            e[i] = int32_t(floor(b[i]));
+            const double dir = b[i] - a[i];
+            if (e[i] != k[i]) {
+                step[i] = e[i] > k[i] ? 1 : -1;
+                tmax[i] = (double(e[i] > k[i] ? k[i] + 1 : k[i]) - a[i]) / dir;
+                tdel[i] = double(step[i]) / dir;
+            } else {
+                step[i] = 0; tmax[i] = HUGE_VAL; tdel[i] = 0.0;
+            }
+        }
+        return true;
+    }
+    __device__ __forceinline__ int64_t cells() const
+    {
+        return int64_t(abs(e[0] - k[0])) + abs(e[1] - k[1]) + abs(e[2] - k[2]) + 1;
+    }
+    // On to the next cell; false at the end cell.  `at` receives the segment's
+    // parameter where it leaves the cell, `moved` the bits of the coordinate
+    // that changed.  No branches: lanes of a wave step along different axes.
+    __device__ __forceinline__ bool next(double &at, int32_t &moved)
+    {
+        const bool by = tmax[1] < tmax[0];
+        const double t = by ? tmax[1] : tmax[0];
+        const bool bz = tmax[2] < t;
+        at = bz ? tmax[2] : t;
+        const bool go = at < HUGE_VAL;
+        const bool sel[3] = {go && !by && !bz, by && !bz, bz};
+        moved = 0;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const int32_t kn = k[i] + (sel[i] ? step[i] : 0);
+            moved |= kn ^ k[i];
+            k[i] = kn;
+            tmax[i] += sel[i] ? tdel[i] : 0.0;
+            if (sel[i] && kn == e[i]) tmax[i] = HUGE_VAL;
+        }
+        return go;
+    }
+    __device__ __forceinline__ bool next()
+    {
+        double at;
+        int32_t moved;
+        return next(at, moved);
+    }
+};
+
 template <class Emit>
 __device__ int64_t walk_segment(const double a[3], const double b[3], double limit, Emit emit)
 {
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-        if (!(fabs(a[i]) < limit && fabs(b[i]) < limit)) return 0;
-    int64_t k[3], left[3];
-    int step[3];
-    double tmax[3], tdel[3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        k[i] = int64_t(floor(a[i]));
-        const int64_t e = int64_t(floor(b[i]));
-        const double dir = b[i] - a[i];
-        if (e > k[i]) {
-            step[i] = 1; left[i] = e - k[i];
-            tmax[i] = (double(k[i] + 1) - a[i]) / dir;
-            tdel[i] = 1.0 / dir;
-        } else if (e < k[i]) {
-            step[i] = -1; left[i] = k[i] - e;
-            tmax[i] = (double(k[i]) - a[i]) / dir;
-            tdel[i] = -1.0 / dir;
-        } else {
-            step[i] = 0; left[i] = 0; tmax[i] = 0.0; tdel[i] = 0.0;
-        }
-    }
+    Walk w;
+    if (!w.start(a, b, limit)) return 0;
     int64_t n = 0;
-    for (;;) {
-        emit(n, k[0], k[1], k[2]);
+    do {
+        emit(n, w.k[0], w.k[1], w.k[2]);
         ++n;
-        int c = -1;
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            if (left[i] == 0) continue;
-            if (c < 0 || tmax[i] < tmax[c]) c = i;
-        }
-        if (c < 0) break;
-        k[c] += step[c];
-        tmax[c] += tdel[c];
-        left[c] -= 1;
-    }
+    } while (w.next());
     return n;
 }
 
@@ -155,53 +193,26 @@ __device__ int dda_pixel(const Geo &g, int px, int py, float d, Emit emit)
         a[i] = pa / bs;
         b[i] = pb / bs;
     }
-    return int(walk_segment(a, b, 1e6, [&](int64_t j, int64_t x, int64_t y, int64_t z) {
-        emit(int(j), int32_t(x), int32_t(y), int32_t(z));
-    }));
+    return int(walk_segment(a, b, 1e6, [&](int64_t j, int32_t x, int32_t y, int32_t z) { emit(int(j), x, y, z); }));
 }
 
-__global__ void k_dda_count(Geo g, const float *__restrict__ depth, int32_t *__restrict__ counts)
-{
-    int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= int64_t(g.W) * g.H) return;
-    int px = int(i % g.W), py = int(i / g.W);
-    float d = depth[i];
-    int n = 0;
-    if (depth_ok(d, g.maxd)) n = dda_pixel(g, px, py, d, [](int, int32_t, int32_t, int32_t) {});
-    counts[i] = n;
-}
-
-__global__ void k_dda_emit(Geo g, const float *__restrict__ depth, const int32_t *__restrict__ offsets,
-                           uint64_t *__restrict__ out, int64_t total)
-{
-    int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= int64_t(g.W) * g.H) return;
-    int px = int(i % g.W), py = int(i / g.W);
-    float d = depth[i];
-    if (!depth_ok(d, g.maxd)) return;
-    int64_t base = offsets[i];
-    dda_pixel(g, px, py, d, [&](int j, int32_t x, int32_t y, int32_t z) {
-        if (base + j < total) out[base + j] = pack_key(x, y, z);
-    });
-}
+// The cells of one point's band, for the allocation kernel below.
+struct DepthBand {
+    Geo g;
+    const float *depth;
+    template <class Emit> __device__ int64_t operator()(int64_t i, Emit emit) const
+    {
+        const float d = depth[i];
+        if (!depth_ok(d, g.maxd)) return 0;
+        return dda_pixel(g, int(i % g.W), int(i / g.W), d,
+                         [&](int, int32_t x, int32_t y, int32_t z) { emit(pack_key(x, y, z)); });
+    }
+};
 
 __global__ void k_pack_coords(const int32_t *__restrict__ c3, int64_t n, uint64_t *__restrict__ out)
 {
     int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < n) out[i] = pack_key(c3[3 * i], c3[3 * i + 1], c3[3 * i + 2]);
-}
-
-// flag[i] = 1 if uniq[i] is not in the table (only i < *count is valid)
-__global__ void k_flag_new(const uint64_t *__restrict__ uniq, const int64_t *__restrict__ count,
-                           const int4 *__restrict__ slots, int64_t nslots, uint32_t cap,
-                           uint8_t *__restrict__ flag, int64_t n_max)
-{
-    int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n_max) return;
-    if (i >= *count) { flag[i] = 0; return; }
-    int32_t x, y, z;
-    unpack_key(uniq[i], x, y, z);
-    flag[i] = hash_lookup(slots, nslots, cap, x, y, z) < 0 ? 1 : 0;
 }
 
 // flag[i] = 1 when raw candidate i (repeats allowed) is not in the table.
@@ -235,18 +246,16 @@ struct FieldSet {
     float *a[16];
     int n;
 };
+__device__ __forceinline__ void zero_fields(const FieldSet &fs, int64_t first, int64_t i)   // 4 voxels
+{
+    for (int k = 0; k < fs.n; ++k)
+        reinterpret_cast<float4 *>(fs.a[k] + first * kBlockVox)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+}
+
 __global__ void k_zero_fields(FieldSet fs, int64_t first, int64_t count)
 {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= count * kBlockVox) return;
-    const int64_t off = first * kBlockVox + i;
-    for (int k = 0; k < fs.n; ++k) fs.a[k][off] = 0.f;
-}
-
-__global__ void k_zero_blocks(float *__restrict__ a, int64_t first, int64_t count)
-{
-    int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < count * kBlockVox) a[first * kBlockVox + i] = 0.0f;
+    if (i < count * (kBlockVox / 4)) zero_fields(fs, first, i);
 }
 
 __global__ void k_iota(int32_t *__restrict__ a, int64_t n)
@@ -281,14 +290,16 @@ __global__ void k_fill_empty(int4 *__restrict__ slots, int64_t n)
 }
 
 // Canonical slot of the i-th key in (bucket, key) order:
-// pos = max_{j<=i}(home_j - j) + i  (sequential linear probing, unrolled)
+// pos = max_{j<=i}(home_j - j) + i  (sequential linear probing, unrolled);
+// the last key's is the end of the occupied slots.
 __global__ void k_scatter_slots(const int64_t *__restrict__ runmax, const int32_t *__restrict__ ids,
                                 const int32_t *__restrict__ coords, int64_t n, int64_t nslots,
-                                int4 *__restrict__ slots, int32_t *__restrict__ overflow)
+                                int4 *__restrict__ slots, int32_t *__restrict__ overflow, int64_t *__restrict__ end)
 {
     int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i >= n) return;
     int64_t pos = runmax[i] + i;
+    if (i == n - 1) *end = pos;
     if (pos >= nslots) { atomicOr(overflow, 1); return; }
     int32_t id = ids[i];
     slots[pos] = make_int4(coords[4 * id], coords[4 * id + 1], coords[4 * id + 2], id);
@@ -329,7 +340,6 @@ InsertScratch carve_insert(Bump &b, int64_t n_cand, int64_t n_blocks)
     x.ids0 = b.take<int32_t>(size_t(n_blocks));
     x.ids1 = b.take<int32_t>(size_t(n_blocks));
     x.home = b.take<uint32_t>(size_t(n_blocks));
-    x.home2 = b.take<uint32_t>(size_t(n_blocks));
     x.dm = b.take<int64_t>(size_t(n_blocks));
     x.runmax = b.take<int64_t>(size_t(n_blocks));
     x.tmp_bytes = std::max(std::max(tmp_sort(size_t(n_cand), 12), tmp_light(size_t(n_cand))),
@@ -350,6 +360,392 @@ __global__ void k_gather_keys(const uint64_t *__restrict__ keys, const int32_t *
 {
     int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < n) out[i] = keys[pos[i]];
+}
+
+static FieldSet field_set(const dn_volume *v)
+{
+    FieldSet fs{};
+    float *fields[] = {v->f, v->w, v->u, v->ubar[0], v->ubar[1]};
+    for (float *a : fields) fs.a[fs.n++] = a;
+    for (int pp = 0; pp < 2; ++pp)
+        for (int a = 0; a < 3; ++a) fs.a[fs.n++] = v->p[pp] + size_t(a) * v->cap_blocks * kBlockVox;
+    return fs;
+}
+
+// -------------------------------------------------- allocation of one frame
+// A frame's band cells name few distinct blocks, and after the first frames
+// hardly any new one.  One kernel walks the bands; each workgroup keeps the
+// distinct keys of its points in an LDS set, and each of those is
+// looked up once; the unknown ones meet in a small set in global memory,
+// whose first inserter lists the key.  The host reads the counts (the call's
+// one wait); new blocks then take three more launches, none of which sorts
+// or scans more than the new keys and the list of occupied slots.  Bound by
+// latency: 12 frames of 1242 x 375 take 0.82 ms, 3.72 ms with a full sort of
+// the pool and four waits per frame; four of 320 x 96 0.30 ms, 1.18 before.
+// Points (threads) per workgroup: each workgroup adds to the same counters,
+// so on a large frame fewer, larger ones are quicker (1242 x 375: 256 points
+// 50 us, 512 30 us, 1024 28 us); a small frame needs them spread over the
+// chip.
+constexpr int64_t kBandSmall = int64_t(1) << 17;
+constexpr int kBandSet = 1024;          // slots of its LDS set
+constexpr int kBandList = 512;          // distinct keys it lists; more go on one by one
+constexpr uint64_t kNoKey = ~uint64_t(0);
+
+struct BandOut {
+    uint64_t *cand;                     // distinct keys of each workgroup (repeats between them)
+    int64_t cand_cap;
+    uint64_t *set;                      // [kNewSet], kNoKey at rest
+    uint64_t *new_key;                  // [kMaxNew]
+    uint32_t *new_home, *new_slot;
+    int64_t *misc;
+    int64_t *host;                      // report: total cells, listed keys, new keys, overflow, table end
+};
+
+__device__ __forceinline__ uint32_t key_mix(uint64_t k)
+{
+    return uint32_t((k * 0x9E3779B97F4A7C15ull) >> 32);
+}
+
+// A key that its workgroup met first: look it up; if it is in no block yet,
+// list it once for all workgroups.  Probing is bounded: a set that fills up
+// sends the frame to the general path.
+__device__ void band_key(const BandOut &o, uint64_t key, const int4 *slots, int64_t nslots, uint32_t cap)
+{
+    int32_t x, y, z;
+    unpack_key(key, x, y, z);
+    if (hash_lookup(slots, nslots, cap, x, y, z) >= 0) return;
+    unsigned long long *set = reinterpret_cast<unsigned long long *>(o.set);
+    uint32_t h = key_mix(key) & (kNewSet - 1);
+    for (int probe = 0; probe < 64; ++probe, h = (h + 1) & (kNewSet - 1)) {
+        const unsigned long long old = atomicCAS(set + h, (unsigned long long)kNoKey, (unsigned long long)key);
+        if (old == key) return;
+        if (old != kNoKey) continue;
+        const unsigned long long at = atomicAdd(reinterpret_cast<unsigned long long *>(o.misc + kMiscNew), 1ull);
+        if (at < kMaxNew) {
+            o.new_key[at] = key;
+            o.new_home[at] = bucket_of(x, y, z, cap);
+            o.new_slot[at] = h;
+        } else {
+            atomicOr(reinterpret_cast<unsigned long long *>(o.misc + kMiscFull), 1ull);
+        }
+        return;
+    }
+    atomicOr(reinterpret_cast<unsigned long long *>(o.misc + kMiscFull), 1ull);
+}
+
+// The last workgroup's done count shares a word with the cells.
+constexpr int kDoneShift = 40;
+
+template <class Band, int kBandPoints>
+__global__ __launch_bounds__(kBandPoints) void k_band(Band band, int64_t n, const int4 *__restrict__ slots,
+                                                      int64_t nslots, uint32_t cap, BandOut o)
+{
+    __shared__ unsigned long long set[kBandSet];
+    __shared__ uint64_t list[kBandList];
+    __shared__ unsigned n_list;
+    __shared__ unsigned long long cells, base;
+    const int tid = threadIdx.x;
+    for (int k = tid; k < kBandSet; k += kBandPoints) set[k] = kNoKey;
+    if (tid == 0) { n_list = 0; cells = 0; }
+    __syncthreads();
+    unsigned long long mine = 0;
+    const int64_t i = int64_t(blockIdx.x) * kBandPoints + tid;
+    unsigned long long *listed_all = reinterpret_cast<unsigned long long *>(o.misc + kMiscListed);
+    if (i < n)
+        mine = (unsigned long long)band(i, [&](uint64_t key) {
+            uint32_t h = key_mix(key) & (kBandSet - 1);
+            for (int probe = 0; probe < 32; ++probe, h = (h + 1) & (kBandSet - 1)) {
+                unsigned long long old = set[h];
+                if (old == kNoKey) old = atomicCAS(set + h, (unsigned long long)kNoKey, (unsigned long long)key);
+                if (old == key) return;
+                if (old == kNoKey) break;
+            }
+            // first met here (or the set is crowded: a repeat does no harm)
+            const unsigned at = atomicAdd(&n_list, 1u);
+            if (at < kBandList) {
+                list[at] = key;
+            } else {
+                const unsigned long long to = atomicAdd(listed_all, 1ull);
+                if (to < (unsigned long long)o.cand_cap) o.cand[to] = key;
+                band_key(o, key, slots, nslots, cap);
+            }
+        });
+    for (int d = 32; d > 0; d >>= 1) mine += __shfl_xor(mine, d, 64);
+    if ((tid & 63) == 0 && mine) atomicAdd(&cells, mine);
+    __syncthreads();
+    const unsigned listed = min(n_list, unsigned(kBandList));
+    if (listed) {
+        if (tid == 0) base = atomicAdd(listed_all, (unsigned long long)listed);
+        for (unsigned k = tid; k < listed; k += kBandPoints) band_key(o, list[k], slots, nslots, cap);
+        __syncthreads();
+        for (unsigned k = tid; k < listed; k += kBandPoints)
+            if (base + k < (unsigned long long)o.cand_cap) o.cand[base + k] = list[k];
+    }
+    // The last workgroup hands the counts to the host and clears them.  The
+    // counts are atomics of device scope, complete before their workgroup's
+    // cells are added; a release fence per workgroup, which would write back
+    // the L2 each time, cost 100 us a frame.
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (tid != 0) return;
+    const unsigned long long one = 1ull << kDoneShift;
+    const unsigned long long before = atomicAdd(reinterpret_cast<unsigned long long *>(o.misc + kMiscCells), cells + one);
+    if ((before >> kDoneShift) + 1ull != gridDim.x) return;
+    const int which[4] = {kMiscListed, kMiscNew, kMiscFull, kMiscEnd};
+    o.host[0] = int64_t((before + cells) & (one - 1ull));
+    for (int k = 0; k < 4; ++k)
+        o.host[1 + k] = __hip_atomic_load(o.misc + which[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int k = 0; k < 3; ++k) o.misc[which[k]] = 0;
+    o.misc[kMiscCells] = 0;
+    __threadfence_system();
+}
+
+// A new volume's counters (all 32 words) and its set of new keys.
+__global__ void k_init_misc(int64_t *__restrict__ misc, uint64_t *__restrict__ set)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < 32) misc[i] = 0;
+    if (i < kNewSet) set[i] = kNoKey;
+}
+
+__global__ void k_fill_keys(uint64_t *__restrict__ a, int64_t n)
+{
+    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (i < n) a[i] = kNoKey;
+}
+
+// Append n <= kMaxNew listed keys to the pool in ascending order, list them
+// in (home bucket, key) order too, empty their slots of the set, and (the
+// workgroups past the first `rank_groups`) empty the table to be built.  A
+// key's place in either order is the number of keys before it: 16 lanes
+// count for each.
+__global__ __launch_bounds__(256) void k_append_ranked(const uint64_t *__restrict__ key, const uint32_t *__restrict__ home,
+                                                       const uint32_t *__restrict__ slot, int n, int rank_groups,
+                                                       int64_t nb_old, uint64_t *__restrict__ set,
+                                                       int32_t *__restrict__ coords, uint64_t *__restrict__ keys,
+                                                       uint32_t *__restrict__ s_home, uint64_t *__restrict__ s_key,
+                                                       int32_t *__restrict__ s_id, int4 *__restrict__ table,
+                                                       int64_t nslots)
+{
+    if (int(blockIdx.x) >= rank_groups) {
+        const int64_t stride = int64_t(gridDim.x - rank_groups) * 256;
+        for (int64_t i = int64_t(blockIdx.x - rank_groups) * 256 + threadIdx.x; i < nslots; i += stride)
+            table[i] = make_int4(0, 0, 0, -1);
+        return;
+    }
+    const int sub = threadIdx.x & 15, i = int(blockIdx.x) * 16 + (threadIdx.x >> 4);
+    if (i >= n) return;
+    const uint64_t k = key[i];
+    const uint32_t h = home[i];
+    int by_key = 0, by_home = 0;
+    for (int j = sub; j < n; j += 16) {
+        const uint64_t kj = key[j];
+        const uint32_t hj = home[j];
+        by_key += kj < k;
+        by_home += hj < h || (hj == h && kj < k);
+    }
+    for (int d = 8; d > 0; d >>= 1) {
+        by_key += __shfl_xor(by_key, d, 16);
+        by_home += __shfl_xor(by_home, d, 16);
+    }
+    if (sub != 0) return;
+    const int64_t b = nb_old + by_key;
+    int32_t x, y, z;
+    unpack_key(k, x, y, z);
+    keys[b] = k;
+    reinterpret_cast<int4 *>(coords)[b] = make_int4(x, y, z, 0);
+    s_home[by_home] = h;
+    s_key[by_home] = k;
+    s_id[by_home] = int32_t(b);
+    set[slot[i]] = kNoKey;
+}
+
+// The canonical table of the old blocks (listed in (home, key) order) and n
+// new ones, by one workgroup: merge the two lists (each key's place is its
+// own rank plus the number of the other list's keys before it), then each
+// key's slot as in k_scatter_slots.  Bound by the latency of its few
+// dependent steps: both lists and the merged one stay in LDS where they fit,
+// and go through global memory up to kMergeBlocks, where one workgroup is
+// quicker than the launches of a device-wide sort or scan.
+constexpr int64_t kMergeBlocks = 65536;
+template <bool kLds>
+__global__ __launch_bounds__(1024) void k_merge_table(const uint32_t *__restrict__ o_home, const int32_t *__restrict__ o_ids,
+                                                      int nb_old, const uint32_t *__restrict__ s_home,
+                                                      const uint64_t *__restrict__ s_key,
+                                                      const int32_t *__restrict__ s_id, int n,
+                                                      const uint64_t *__restrict__ keys, uint32_t *g_home,
+                                                      int32_t *g_ids, const int32_t *__restrict__ coords,
+                                                      int4 *__restrict__ table, int64_t nslots,
+                                                      int64_t *__restrict__ end, int32_t *__restrict__ overflow)
+{
+    extern __shared__ uint32_t lds[];
+    __shared__ int wave_max[16];
+    uint32_t *nh = lds;                                              // [n]
+    uint32_t *oh = lds + n;                                          // [nb_old], kLds
+    uint32_t *m_home = kLds ? oh + nb_old : g_home;                  // [nb_old + n]
+    int32_t *m_ids = kLds ? reinterpret_cast<int32_t *>(m_home + nb_old + n) : g_ids;
+    const int t = threadIdx.x;
+    for (int k = t; k < n; k += 1024) nh[k] = s_home[k];
+    if constexpr (kLds)
+        for (int k = t; k < nb_old; k += 1024) oh[k] = o_home[k];
+    if (t == 0) *overflow = 0;
+    const uint32_t *oldh = kLds ? oh : o_home;
+    __syncthreads();
+    // the first position of a list whose bucket is h or more
+    auto lower = [](const uint32_t *a, int len, uint32_t h) {
+        int lo = 0, hi = len;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (a[mid] < h) lo = mid + 1;
+            else hi = mid;
+        }
+        return lo;
+    };
+    for (int i = t; i < nb_old; i += 1024) {
+        const uint32_t h = oldh[i];
+        const int id = o_ids[i];
+        int c = lower(nh, n, h);
+        if (c < n && nh[c] == h) {
+            const uint64_t k = keys[id];
+            while (c < n && nh[c] == h && s_key[c] < k) ++c;
+        }
+        m_home[i + c] = h;
+        m_ids[i + c] = id;
+    }
+    for (int r = t; r < n; r += 1024) {
+        const uint32_t h = nh[r];
+        int c = lower(oldh, nb_old, h);
+        if (c < nb_old && oldh[c] == h) {
+            const uint64_t k = s_key[r];
+            while (c < nb_old && oldh[c] == h && keys[o_ids[c]] < k) ++c;
+        }
+        m_home[r + c] = h;
+        m_ids[r + c] = s_id[r];
+    }
+    __syncthreads();
+    const int nb = nb_old + n;
+    if constexpr (kLds)
+        for (int i = t; i < nb; i += 1024) {
+            g_home[i] = m_home[i];
+            g_ids[i] = m_ids[i];
+        }
+    // tiles of 1024 keys, the running maximum carried from one to the next;
+    // the first tiles' coordinates are on their way before the scan starts
+    constexpr int kAhead = 4;
+    int4 ahead[kAhead];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k)
+        if (k * 1024 + t < nb) ahead[k] = reinterpret_cast<const int4 *>(coords)[m_ids[k * 1024 + t]];
+    int carry = INT32_MIN;
+    for (int i0 = 0; i0 < nb; i0 += 1024) {
+        const int i = i0 + t;
+        int4 q = ahead[0];
+#pragma unroll
+        for (int k = 1; k < kAhead; ++k) ahead[k - 1] = ahead[k];
+        int run = INT32_MIN, id = 0;
+        if (i < nb) {
+            id = m_ids[i];
+            run = int(m_home[i]) - i;
+        }
+        if (i + kAhead * 1024 < nb)
+            ahead[kAhead - 1] = reinterpret_cast<const int4 *>(coords)[m_ids[i + kAhead * 1024]];
+        for (int d = 1; d < 64; d <<= 1) {
+            const int other = __shfl_up(run, d, 64);
+            if ((t & 63) >= d) run = max(run, other);
+        }
+        if ((t & 63) == 63) wave_max[t >> 6] = run;
+        __syncthreads();
+        int top = carry;
+        for (int w = 0; w < 16; ++w) {
+            if (w == (t >> 6)) run = max(run, top);
+            top = max(top, wave_max[w]);
+        }
+        carry = top;
+        __syncthreads();
+        if (i >= nb) continue;
+        const int64_t pos = int64_t(run) + i;
+        if (i == nb - 1) *end = pos;
+        if (pos < nslots) table[pos] = make_int4(q.x, q.y, q.z, id);
+        else *overflow = 1;
+    }
+}
+
+// Neighbours of the n new blocks, both ways, and their zeroed fields (the
+// workgroups past the first `nbr_groups`).
+__global__ __launch_bounds__(256) void k_commit_new(const int32_t *__restrict__ coords, int64_t nb_old, int64_t n,
+                                                    const int4 *__restrict__ slots, int64_t nslots, uint32_t cap,
+                                                    int nbr_groups, int32_t *__restrict__ nbr, FieldSet fs)
+{
+    if (int(blockIdx.x) >= nbr_groups) {
+        const int64_t i = int64_t(blockIdx.x - nbr_groups) * 256 + threadIdx.x;
+        if (i < n * (kBlockVox / 4)) zero_fields(fs, nb_old, i);
+        return;
+    }
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (i >= n * kNbr) return;
+    const int64_t b = nb_old + i / kNbr;
+    const int o = int(i % kNbr);
+    const int dx = o % 3 - 1, dy = (o / 3) % 3 - 1, dz = o / 9 - 1;
+    const int32_t id = o == kCentre ? int32_t(b)
+                                    : hash_lookup(slots, nslots, cap, coords[4 * b] + dx, coords[4 * b + 1] + dy,
+                                                  coords[4 * b + 2] + dz);
+    nbr[b * kNbr + o] = id;
+    if (id >= 0 && id < nb_old) nbr[int64_t(id) * kNbr + (kNbr - 1 - o)] = int32_t(b);
+}
+
+// Empty the set of new keys after a frame that did not consume it.
+static int reset_new_set(dn_volume *v)
+{
+    hipLaunchKernelGGL(k_fill_keys, dim3(grid1(kNewSet)), dim3(256), 0, v->stream, v->new_set, int64_t(kNewSet));
+    DN_HIP(hipGetLastError());
+    return DN_OK;
+}
+
+// The n_new <= kMaxNew keys that k_band listed become blocks.
+static int insert_listed(dn_volume *v, int64_t n_new, int64_t table_end, int32_t *n_new_out)
+{
+    hipStream_t st = v->stream;
+    const int64_t nb_old = v->nb, nb_new = nb_old + n_new;
+    const int other = 1 - v->cur_hash;
+    int4 *dst = reinterpret_cast<int4 *>(v->hash[other]);
+    int32_t *d_ovf = reinterpret_cast<int32_t *>(v->misc + 2);
+    const int rank_groups = int((n_new + 15) / 16);
+    const int clear_groups = int(std::min<int64_t>(1024, (v->hash_slots + 1023) / 1024));
+    hipLaunchKernelGGL(k_append_ranked, dim3(unsigned(rank_groups + clear_groups)), dim3(256), 0, st, v->new_key,
+                       v->new_home, v->new_slot, int(n_new), rank_groups, nb_old, v->new_set, v->coords, v->keys,
+                       v->sort_home, v->sort_key, v->sort_id, dst, v->hash_slots);
+    const size_t lds_all = (size_t(n_new) + size_t(nb_old) + 2 * size_t(nb_new)) * 4;
+    const bool in_lds = lds_all <= (size_t(60) << 10);
+    const size_t lds = in_lds ? lds_all : size_t(n_new) * 4;
+    hipLaunchKernelGGL(in_lds ? k_merge_table<true> : k_merge_table<false>, dim3(1), dim3(1024), lds, st, v->hord_home[v->cur_hash], v->hord_ids[v->cur_hash],
+                       int(nb_old), v->sort_home, v->sort_key, v->sort_id, int(n_new), v->keys, v->hord_home[other],
+                       v->hord_ids[other], v->coords, dst, v->hash_slots, v->misc + kMiscEnd, d_ovf);
+    DN_HIP(hipGetLastError());
+    // each key moves the end of the occupied slots by one at most: only near
+    // the end of the tail does the table have to be checked before it is used
+    if (std::max<int64_t>(table_end, int64_t(v->hash_cap) - 1) + n_new >= v->hash_slots) {
+        int rc = read_back(v, d_ovf, sizeof(int32_t));
+        if (rc) return rc;
+        if (int32_t(v->host_stage[0] & 0xFFFFFFFF) != 0) {
+            // the old table stays, and with it the end of its slots
+            const int64_t keep = table_end;
+            DN_HIP(hipMemcpyAsync(v->misc + kMiscEnd, &keep, sizeof(keep), hipMemcpyHostToDevice, st));
+            DN_HIP(hipStreamSynchronize(st));
+            set_error("hash table full: %lld keys do not fit 2^%d buckets + %d tail slots", (long long)nb_new,
+                      v->prm.hash_cap_log2, v->prm.hash_tail);
+            return DN_E_CAPACITY;
+        }
+    }
+    v->cur_hash = other;
+    v->nb = nb_new;
+    v->emask_nb = -1;
+    v->state_storage = DN_F32;
+    const int nbr_groups = int(grid1(n_new * kNbr));
+    hipLaunchKernelGGL(k_commit_new, dim3(unsigned(nbr_groups) + grid1(n_new * (kBlockVox / 4))), dim3(256), 0, st,
+                       v->coords, nb_old, n_new, dst, v->hash_slots, v->hash_cap, nbr_groups, v->nbr, field_set(v));
+    DN_HIP(hipGetLastError());
+    if (n_new_out) *n_new_out = int32_t(n_new);
+    return DN_OK;
 }
 
 // Insert a packed candidate list (device, n_cand entries, repeats allowed).
@@ -424,39 +820,40 @@ static int insert_packed(dn_volume *v, uint64_t *cand, int64_t n_cand, int32_t *
     hipLaunchKernelGGL(k_iota, dim3(grid1(nb_new)), dim3(256), 0, st, x.ids0, nb_new);
     DN_HIP(hipGetLastError());
     const int hbits = bits_for(v->hash_cap - 1);
+    const int other = 1 - v->cur_hash;
     tbytes = x.tmp_bytes;
     DN_HIP(rocprim::radix_sort_pairs(x.tmp, tbytes, v->keys, x.ksorted, x.ids0, x.ids1, size_t(nb_new), 0, 63, st));
     hipLaunchKernelGGL(k_bucket_of_keys, dim3(grid1(nb_new)), dim3(256), 0, st, x.ksorted, nb_new, v->hash_cap, x.home);
     DN_HIP(hipGetLastError());
     tbytes = x.tmp_bytes;
-    DN_HIP(rocprim::radix_sort_pairs(x.tmp, tbytes, x.home, x.home2, x.ids1, x.ids0, size_t(nb_new), 0, hbits, st));
-    hipLaunchKernelGGL(k_home_minus_rank, dim3(grid1(nb_new)), dim3(256), 0, st, x.home2, nb_new, x.dm);
+    DN_HIP(rocprim::radix_sort_pairs(x.tmp, tbytes, x.home, v->hord_home[other], x.ids1, v->hord_ids[other],
+                                     size_t(nb_new), 0, hbits, st));
+    hipLaunchKernelGGL(k_home_minus_rank, dim3(grid1(nb_new)), dim3(256), 0, st, v->hord_home[other], nb_new, x.dm);
     DN_HIP(hipGetLastError());
     tbytes = x.tmp_bytes;
     DN_HIP(rocprim::inclusive_scan(x.tmp, tbytes, x.dm, x.runmax, size_t(nb_new), rocprim::maximum<int64_t>(), st));
-    int other = 1 - v->cur_hash;
     int4 *dst = reinterpret_cast<int4 *>(v->hash[other]);
     int32_t *d_ovf = reinterpret_cast<int32_t *>(d_nraw + 2);
     hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(1), 0, st, d_ovf);
     hipLaunchKernelGGL(k_fill_empty, dim3(grid1(v->hash_slots)), dim3(256), 0, st, dst, v->hash_slots);
     DN_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_scatter_slots, dim3(grid1(nb_new)), dim3(256), 0, st, x.runmax, x.ids0, v->coords, nb_new,
-                       v->hash_slots, dst, d_ovf);
+    hipLaunchKernelGGL(k_scatter_slots, dim3(grid1(nb_new)), dim3(256), 0, st, x.runmax, v->hord_ids[other], v->coords,
+                       nb_new, v->hash_slots, dst, d_ovf, v->misc + kMiscEnd);
     DN_HIP(hipGetLastError());
     if ((rc = read_back(v, d_ovf, sizeof(int32_t)))) return rc;
     if (int32_t(v->host_stage[0] & 0xFFFFFFFF) != 0) {
+        // the old table stays; its end is unknown now, so the next frame's is checked
+        const int64_t unknown = v->hash_slots;
+        DN_HIP(hipMemcpyAsync(v->misc + kMiscEnd, &unknown, sizeof(unknown), hipMemcpyHostToDevice, st));
+        DN_HIP(hipStreamSynchronize(st));
         set_error("hash table full: %lld keys do not fit 2^%d buckets + %d tail slots", (long long)nb_new,
                   v->prm.hash_cap_log2, v->prm.hash_tail);
         return DN_E_CAPACITY;
     }
     // 5) commit: new table, zeroed fields of the new blocks, neighbours
     v->cur_hash = other;
-    FieldSet fs{};
-    float *fields[] = {v->f, v->w, v->u, v->ubar[0], v->ubar[1]};
-    for (float *a : fields) fs.a[fs.n++] = a;
-    for (int pp = 0; pp < 2; ++pp)
-        for (int a = 0; a < 3; ++a) fs.a[fs.n++] = v->p[pp] + size_t(a) * v->cap_blocks * kBlockVox;
-    hipLaunchKernelGGL(k_zero_fields, dim3(grid1(n_new * kBlockVox)), dim3(256), 0, st, fs, nb_old, n_new);
+    hipLaunchKernelGGL(k_zero_fields, dim3(grid1(n_new * (kBlockVox / 4))), dim3(256), 0, st, field_set(v), nb_old,
+                       n_new);
     DN_HIP(hipGetLastError());
     v->nb = nb_new;
     v->emask_nb = -1;
@@ -469,46 +866,60 @@ static int insert_packed(dn_volume *v, uint64_t *cand, int64_t n_cand, int32_t *
 }
 
 // ---------------------------------------------------------------- fusion
-constexpr int kMiscFuseCount = 16;      // v->misc slot of the in-view block count
-constexpr int64_t kFuseGrid = 4096;     // workgroups striding over the in-view list
-
-// Eq. 1 for one voxel (k in 0..511, x fastest) of block b: project its
+// Eq. 1 for voxels k0, k0 + step, ... (x fastest) of block b: project the
 // centre, take the depth of the pixel it falls in, and average the
 // truncated signed distance in with weight 1.  Voxels behind the camera,
 // outside the image, with an invalid depth or more than mu behind the
 // observed surface keep their values; free space in front of the surface
 // is updated with the truncated value 1.
-__device__ inline void fuse_voxel(const Geo &g, const float *__restrict__ depth, const int32_t *__restrict__ coords,
-                                  int64_t b, int k, float *__restrict__ f, float *__restrict__ w)
+template <int N>
+__device__ inline void fuse_voxels(const Geo &g, const float *__restrict__ depth, const int32_t *__restrict__ coords,
+                                   int64_t b, int k0, int step, float *__restrict__ f, float *__restrict__ w)
 {
-    const int vx = k & 7, vy = (k >> 3) & 7, vz = (k >> 6) & 7;
-    double d0 = (double(8 * coords[4 * b + 0] + vx) + 0.5) * g.s - g.T[3];
-    double d1 = (double(8 * coords[4 * b + 1] + vy) + 0.5) * g.s - g.T[7];
-    double d2 = (double(8 * coords[4 * b + 2] + vz) + 0.5) * g.s - g.T[11];
-    double xc = (g.T[0] * d0 + g.T[4] * d1) + g.T[8] * d2;
-    double yc = (g.T[1] * d0 + g.T[5] * d1) + g.T[9] * d2;
-    double zc = (g.T[2] * d0 + g.T[6] * d1) + g.T[10] * d2;
-    if (!(zc > 0.0)) return;
-    double X = g.fx * (xc / zc) + g.cx;
-    double Y = g.fy * (yc / zc) + g.cy;
-    double px = X + 0.5, py = Y + 0.5;
-    if (!(px >= 0.0 && px < double(g.W) && py >= 0.0 && py < double(g.H))) return;
-    int ix = int(floor(px)), iy = int(floor(py));
-    float d = depth[int64_t(iy) * g.W + ix];
-    if (!depth_ok(d, g.maxd)) return;
-    double eta = double(d) - zc;
-    if (eta < -g.mu) return;
-    double psi = eta / g.mu;
-    if (psi > 1.0) psi = 1.0;
-    const int64_t i = b * kBlockVox + k;
-    float wo = w[i];
-    float wn = wo + 1.0f;
-    f[i] = (float(psi) + wo * f[i]) / wn;
-    w[i] = wn;
+    const int4 c = reinterpret_cast<const int4 *>(coords)[b];
+    // every load is issued before its value is known to matter: the map's
+    // overlap the projection, the voxels' depths each other
+    float fo[N], wo[N], d[N];
+    double zc[N];
+    bool in[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const int64_t i = b * kBlockVox + k0 + j * step;
+        fo[j] = f[i];
+        wo[j] = w[i];
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const int k = k0 + j * step;
+        const int vx = k & 7, vy = (k >> 3) & 7, vz = (k >> 6) & 7;
+        double d0 = (double(8 * c.x + vx) + 0.5) * g.s - g.T[3];
+        double d1 = (double(8 * c.y + vy) + 0.5) * g.s - g.T[7];
+        double d2 = (double(8 * c.z + vz) + 0.5) * g.s - g.T[11];
+        double xc = (g.T[0] * d0 + g.T[4] * d1) + g.T[8] * d2;
+        double yc = (g.T[1] * d0 + g.T[5] * d1) + g.T[9] * d2;
+        zc[j] = (g.T[2] * d0 + g.T[6] * d1) + g.T[10] * d2;
+        double X = g.fx * (xc / zc[j]) + g.cx;
+        double Y = g.fy * (yc / zc[j]) + g.cy;
+        double px = X + 0.5, py = Y + 0.5;
+        in[j] = zc[j] > 0.0 && px >= 0.0 && px < double(g.W) && py >= 0.0 && py < double(g.H);
+        const int ix = int(floor(px)), iy = int(floor(py));
+        d[j] = depth[in[j] ? int64_t(iy) * g.W + ix : 0];
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const double eta = double(d[j]) - zc[j];
+        if (!in[j] || !depth_ok(d[j], g.maxd) || eta < -g.mu) continue;
+        double psi = eta / g.mu;
+        if (psi > 1.0) psi = 1.0;
+        const int64_t i = b * kBlockVox + k0 + j * step;
+        const float wn = wo[j] + 1.0f;
+        f[i] = (float(psi) + wo[j] * fo[j]) / wn;
+        w[i] = wn;
+    }
 }
 
 // Visibility culling for fusion: can any voxel centre of the block pass
-// the camera tests of fuse_voxel?  The centres span a box whose image in
+// the camera tests of fuse_voxels?  The centres span a box whose image in
 // camera coordinates is a parallelepiped (the pose is affine), so depth
 // ranges over the corners' depths; if all corners lie in front of the
 // camera the box projects into the convex hull of the projected corners.
@@ -516,61 +927,52 @@ __device__ inline void fuse_voxel(const Geo &g, const float *__restrict__ depth,
 // absorb rounding differences from the per-voxel evaluation, and a box
 // reaching behind the camera counts as visible.  A block is skipped only if
 // every centre is behind the camera, beyond max_depth + mu (where no valid
-// depth can put it within mu of a surface) or outside the image.
-__device__ inline bool block_in_view(const Geo &g, const int32_t *c)
+// depth can put it within mu of a surface) or outside the image (all corners
+// past one of its sides, tested without the division by their depths).
+__device__ inline bool block_in_view(const Geo &g, const int4 c)
 {
-    double zmin = 1e300, zmax = -1e300, xmin = 1e300, xmax = -1e300, ymin = 1e300, ymax = -1e300;
-    double xs[8], ys[8], zs[8];
+    double zmin = 1e300, zmax = -1e300;
+    int left = 0, right = 0, up = 0, down = 0;
     for (int k = 0; k < 8; ++k) {
-        double d0 = (double(8 * c[0] + ((k & 1) ? 7 : 0)) + 0.5) * g.s - g.T[3];
-        double d1 = (double(8 * c[1] + ((k & 2) ? 7 : 0)) + 0.5) * g.s - g.T[7];
-        double d2 = (double(8 * c[2] + ((k & 4) ? 7 : 0)) + 0.5) * g.s - g.T[11];
-        xs[k] = (g.T[0] * d0 + g.T[4] * d1) + g.T[8] * d2;
-        ys[k] = (g.T[1] * d0 + g.T[5] * d1) + g.T[9] * d2;
-        zs[k] = (g.T[2] * d0 + g.T[6] * d1) + g.T[10] * d2;
-        zmin = fmin(zmin, zs[k]);
-        zmax = fmax(zmax, zs[k]);
+        const double d0 = (double(8 * c.x + ((k & 1) ? 7 : 0)) + 0.5) * g.s - g.T[3];
+        const double d1 = (double(8 * c.y + ((k & 2) ? 7 : 0)) + 0.5) * g.s - g.T[7];
+        const double d2 = (double(8 * c.z + ((k & 4) ? 7 : 0)) + 0.5) * g.s - g.T[11];
+        const double x = (g.T[0] * d0 + g.T[4] * d1) + g.T[8] * d2;
+        const double y = (g.T[1] * d0 + g.T[5] * d1) + g.T[9] * d2;
+        const double z = (g.T[2] * d0 + g.T[6] * d1) + g.T[10] * d2;
+        zmin = fmin(zmin, z);
+        zmax = fmax(zmax, z);
+        // X + 1/2 = fx x / z + cx + 1/2 against -1 and W + 1, times z
+        const double X = g.fx * x + (g.cx + 0.5) * z, Y = g.fy * y + (g.cy + 0.5) * z;
+        left += X < -z;
+        right += X >= (double(g.W) + 1.0) * z;
+        up += Y < -z;
+        down += Y >= (double(g.H) + 1.0) * z;
     }
     const double eps = 1e-6;
     if (zmax <= -eps || zmin > g.maxd + g.mu + eps) return false;
     if (zmin <= eps) return true;
-    for (int k = 0; k < 8; ++k) {
-        double X = g.fx * (xs[k] / zs[k]) + g.cx + 0.5, Y = g.fy * (ys[k] / zs[k]) + g.cy + 0.5;
-        xmin = fmin(xmin, X); xmax = fmax(xmax, X);
-        ymin = fmin(ymin, Y); ymax = fmax(ymax, Y);
-    }
-    return xmax >= -1.0 && xmin < double(g.W) + 1.0 && ymax >= -1.0 && ymin < double(g.H) + 1.0;
+    return left < 8 && right < 8 && up < 8 && down < 8;
 }
 
-// The blocks in view, appended to `list` (one atomic per wavefront; the
-// order of the list varies, the fused values do not: every voxel is
-// updated by one thread).
-__global__ void k_cull(Geo g, const int32_t *__restrict__ coords, int64_t nb, int32_t *__restrict__ list,
-                       int32_t *__restrict__ count)
+// Eq. 1 over the blocks in view.  Bound by launches and latency: a frame
+// touches a few MB.  The `share` workgroups of a group of 64 blocks each
+// test the whole group (a lane per block, every wave for itself) and take
+// every share-th visible one; testing again costs less than a launch of its
+// own with a list and a counter to clear (10.3 us a frame; in three launches
+// 12.0 us and two launch gaps).
+__global__ __launch_bounds__(256) void k_fuse(Geo g, const float *__restrict__ depth,
+                                              const int32_t *__restrict__ coords, int64_t nb, int share,
+                                              float *__restrict__ f, float *__restrict__ w)
 {
-    int64_t b = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    bool vis = b < nb && block_in_view(g, coords + 4 * b);
-    uint64_t m = __ballot(vis);
-    if (m == 0) return;
-    const int lane = __lane_id(), leader = __ffsll((unsigned long long)m) - 1;
-    int base = 0;
-    if (lane == leader) base = atomicAdd(count, __popcll(m));
-    base = __shfl(base, leader);
-    if (vis) list[base + __popcll(m & ((uint64_t(1) << lane) - 1))] = int32_t(b);
-}
-
-// Eq. 1 over the blocks in view: workgroups stride over the list (its
-// length is read on the device, so the grid is sized from the pool).
-__global__ __launch_bounds__(256) void k_fuse_list(Geo g, const float *__restrict__ depth,
-                                                   const int32_t *__restrict__ coords,
-                                                   const int32_t *__restrict__ list, const int32_t *__restrict__ count,
-                                                   float *__restrict__ f, float *__restrict__ w)
-{
-    const int32_t n = *count;
-    for (int32_t j = blockIdx.x; j < n; j += gridDim.x) {
-        const int64_t b = list[j];
-        fuse_voxel(g, depth, coords, b, threadIdx.x, f, w);
-        fuse_voxel(g, depth, coords, b, threadIdx.x + 256, f, w);
+    const int64_t group = int64_t(blockIdx.x) / share;
+    const int mine = int(blockIdx.x) % share;
+    const int64_t mb = group * 64 + (threadIdx.x & 63);
+    uint64_t m = __ballot(mb < nb && block_in_view(g, reinterpret_cast<const int4 *>(coords)[min(mb, nb - 1)]));
+    for (int k = 0, turn = mine; m; ++k, m &= m - 1) {
+        if (k != turn) continue;
+        turn += share;
+        fuse_voxels<2>(g, depth, coords, group * 64 + __ffsll((unsigned long long)m) - 1, threadIdx.x, 256, f, w);
     }
 }
 
@@ -638,23 +1040,14 @@ __device__ int64_t laser_band(const LGeo &g, const float *p, Emit emit)
     return walk_segment(a, b, 1e9, emit);
 }
 
-__global__ void k_laser_cand_count(LGeo g, const float *__restrict__ pts, int64_t n, int32_t *__restrict__ counts)
-{
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    counts[i] = int32_t(laser_band(g, pts + 3 * i, [](int64_t, int64_t, int64_t, int64_t) {}));
-}
-
-__global__ void k_laser_cand_emit(LGeo g, const float *__restrict__ pts, int64_t n, const int32_t *__restrict__ offsets,
-                                  uint64_t *__restrict__ out, int64_t total)
-{
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int64_t base = offsets[i];
-    laser_band(g, pts + 3 * i, [&](int64_t j, int64_t x, int64_t y, int64_t z) {
-        if (base + j < total) out[base + j] = pack_key(int32_t(x), int32_t(y), int32_t(z));
-    });
-}
+struct LaserBand {
+    LGeo g;
+    const float *pts;
+    template <class Emit> __device__ int64_t operator()(int64_t i, Emit emit) const
+    {
+        return laser_band(g, pts + 3 * i, [&](int64_t, int32_t x, int32_t y, int32_t z) { emit(pack_key(x, y, z)); });
+    }
+};
 
 // The observations of one return: emit(j, voxel index, psi) for each visited
 // voxel of an allocated block with eta >= -mu; returns their number.
@@ -671,13 +1064,13 @@ __device__ int64_t laser_obs(const LGeo &g, const float *p, const int4 *slots, i
 #pragma unroll
     for (int i = 0; i < 3; ++i) { a[i] = pa[i] / g.s; b[i] = pb[i] / g.s; }
     int64_t m = 0;
-    int64_t kb[3] = {INT64_MIN, 0, 0};
+    int32_t kb[3] = {INT32_MIN, 0, 0};
     int32_t id = -1;
-    walk_segment(a, b, 1e9, [&](int64_t, int64_t x, int64_t y, int64_t z) {
-        const int64_t bx = x >> 3, by = y >> 3, bz = z >> 3;   // floor division
+    walk_segment(a, b, 1e9, [&](int64_t, int32_t x, int32_t y, int32_t z) {
+        const int32_t bx = x >> 3, by = y >> 3, bz = z >> 3;   // floor division
         if (bx != kb[0] || by != kb[1] || bz != kb[2]) {
             kb[0] = bx; kb[1] = by; kb[2] = bz;
-            id = hash_lookup(slots, nslots, cap, int32_t(bx), int32_t(by), int32_t(bz));
+            id = hash_lookup(slots, nslots, cap, bx, by, bz);
         }
         if (id < 0) return;
         const double gg[3] = {double(x), double(y), double(z)};
@@ -716,6 +1109,172 @@ __global__ void k_laser_obs_emit(LGeo g, const float *__restrict__ pts, int64_t 
             vals[base + j] = psi;
         }
     });
+}
+
+// Fusion of a scan into a map of up to kAccumBlocks blocks: every voxel has
+// an accumulator in the scratch, a count of its observations and the sum of
+// 1 - psi over those in the band (in free space psi = 1).  The sum is a
+// 64-bit fixed-point number, scaled so that all n returns in one voxel still
+// fit: the result does not depend on the order of the additions, and its
+// rounding (2^-45 per observation for 65536 returns) is far below the
+// float32 result's.  Bound by latency along each ray: one lane walks a ray
+// and looks a block up when it enters it, in LDS, where a map of up to
+// kSeenAll blocks lies whole (a larger one's table keeps the blocks that its
+// workgroup met: neighbouring rays pass the same ones, but each costs one
+// wait for memory), and lanes in the same voxel add to its count once.
+// Against two walks with a lookup in memory per block and a sort of all
+// observations, 65536 returns into 1400 blocks: 0.90 ms a scan before
+// (allocation included), 0.21 ms now.
+constexpr int64_t kAccumBlocks = 16384;
+constexpr int kSeen = 8192, kSeenAll = kSeen / 2;   // entries of the table
+constexpr double kSeenRange = 500.0;                // blocks from the sensor that its tags tell apart
+
+__global__ void k_laser_clear(uint32_t *__restrict__ cnt, unsigned long long *__restrict__ sum, int64_t nvox,
+                              int64_t *__restrict__ total)
+{
+    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;   // 4 voxels
+    if (i == 0) *total = 0;
+    if (4 * i >= nvox) return;
+    reinterpret_cast<uint4 *>(cnt)[i] = make_uint4(0, 0, 0, 0);
+    reinterpret_cast<ulonglong2 *>(sum)[2 * i] = make_ulonglong2(0, 0);
+    reinterpret_cast<ulonglong2 *>(sum)[2 * i + 1] = make_ulonglong2(0, 0);
+}
+
+template <bool kAll>
+__global__ __launch_bounds__(256) void k_laser_accumulate(LGeo g, const float *__restrict__ pts, int64_t n,
+                                                          const int4 *__restrict__ slots, int64_t nslots, uint32_t cap,
+                                                          const int4 *__restrict__ coords, int nb, double scale,
+                                                          uint32_t *__restrict__ cnt,
+                                                          unsigned long long *__restrict__ sum,
+                                                          int64_t *__restrict__ total)
+{
+    __shared__ unsigned long long seen[kSeen];      // block relative to the sensor's (high half) and its id
+    __shared__ unsigned long long s_total;
+    const int tid = threadIdx.x, lane = tid & 63;
+    constexpr unsigned long long kNone = ~0ull;
+    const int32_t sx = int32_t(floor(g.T[3] / (8.0 * g.s))), sy = int32_t(floor(g.T[7] / (8.0 * g.s))),
+                  sz = int32_t(floor(g.T[11] / (8.0 * g.s)));
+    // the block's tag, ~0 out of the table's range; its place in the table
+    auto tag_of = [&](int32_t bx, int32_t by, int32_t bz) {
+        const uint32_t rx = uint32_t(bx) - uint32_t(sx) + 512u, ry = uint32_t(by) - uint32_t(sy) + 512u,
+                       rz = uint32_t(bz) - uint32_t(sz) + 512u;
+        return (rx | ry | rz) < 1024u ? rx << 20 | ry << 10 | rz : ~0u;
+    };
+    auto place = [](uint32_t tag) { return (tag * 2654435761u) >> 19; };
+    static_assert(kSeen == 1 << 13, "place() gives 13 bits");
+    for (int k = tid; k < kSeen; k += 256) seen[k] = kNone;
+    if (tid == 0) s_total = 0;
+    __syncthreads();
+    if constexpr (kAll) {
+        for (int k = tid; k < nb; k += 256) {
+            const int4 c = coords[k];
+            const uint32_t tag = tag_of(c.x, c.y, c.z);
+            if (tag == ~0u) continue;
+            for (uint32_t h = place(tag);; h = (h + 1) & (kSeen - 1))
+                if (atomicCAS(seen + h, kNone, (unsigned long long)tag << 32 | uint32_t(k)) == kNone) break;
+        }
+        __syncthreads();
+    }
+    const int64_t i = int64_t(blockIdx.x) * 256 + tid;
+    double r = 0.0, d[3], pa[3], pb[3], a[3], b[3], D[3] = {0.0, 0.0, 0.0};
+    Walk w{};
+    bool alive = i < n && laser_ray(pts + 3 * i, g.maxd, r, d);
+    if (alive) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) D[q] = (g.T[4 * q + 0] * d[0] + g.T[4 * q + 1] * d[1]) + g.T[4 * q + 2] * d[2];
+        ray_point(g.T, d, 0.0, pa);
+        ray_point(g.T, d, r + g.mu, pb);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) { a[q] = pa[q] / g.s; b[q] = pb[q] / g.s; }
+        alive = w.start(a, b, 1e9);
+    }
+    // gridDim.y workgroups share a ray by step numbers; each walks up to its own
+    int steps = 0;
+    if (alive) {
+        const int64_t all = w.cells();
+        const int64_t first = all * blockIdx.y / gridDim.y, end = all * (blockIdx.y + 1) / gridDim.y;
+        steps = int(end - first);
+        for (int64_t k = 0; k < first; ++k) w.next();
+        alive = steps > 0;
+    }
+    // Up to the parameter `safe` a cell's centre, at most 0.87 s from the
+    // ray, is more than mu in front of the surface: psi = 1 without its
+    // distance.
+    const double safe = (r - g.mu - 2.0 * g.s) / (r + g.mu);
+    double now = 2.0;                    // the parameter at which the ray entered the cell (2: unknown)
+    int32_t id = -1, moved = ~7;         // ~7: not in this block yet
+    unsigned mine = 0;
+    while (__any(alive)) {
+        uint32_t vox = 0;
+        bool hit = false;
+        if (alive) {
+            if ((moved & ~7) != 0) {
+                const int32_t bx = w.k[0] >> 3, by = w.k[1] >> 3, bz = w.k[2] >> 3;   // floor division
+                const uint32_t tag = tag_of(bx, by, bz);
+                if constexpr (kAll) {
+                    id = -1;
+                    for (uint32_t h = place(tag);; h = (h + 1) & (kSeen - 1)) {
+                        const unsigned long long e = seen[h];
+                        if (uint32_t(e >> 32) == tag) id = int32_t(uint32_t(e));
+                        if (e == kNone || id >= 0) break;
+                    }
+                } else if (tag != ~0u) {
+                    unsigned long long *at = seen + place(tag);
+                    const unsigned long long e = *at;
+                    if (uint32_t(e >> 32) == tag) {
+                        id = int32_t(uint32_t(e));
+                    } else {
+                        id = hash_lookup(slots, nslots, cap, bx, by, bz);
+                        *at = (unsigned long long)tag << 32 | uint32_t(id);
+                    }
+                } else {
+                    id = hash_lookup(slots, nslots, cap, bx, by, bz);
+                }
+            }
+            if (id >= 0) {
+                vox = uint32_t(id) * uint32_t(kBlockVox) + uint32_t((w.k[0] & 7) + 8 * (w.k[1] & 7) + 64 * (w.k[2] & 7));
+                hit = true;
+                if (!(now < safe)) {
+                    double rho = 0.0;
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) rho += ((double(w.k[q]) + 0.5) * g.s - g.T[4 * q + 3]) * D[q];
+                    const double eta = r - rho;
+                    hit = eta >= -g.mu;
+                    if (hit && eta < g.mu) atomicAdd(sum + vox, (unsigned long long)rint((1.0 - eta / g.mu) * scale));
+                }
+                if (hit) ++mine;
+            }
+            alive = w.next(now, moved) && --steps > 0;
+        }
+        // one addition per run of neighbouring lanes in the same voxel
+        const uint64_t hits = __ballot(hit);
+        if (hits == 0) continue;
+        const uint32_t before = __shfl_up(vox, 1, 64);
+        const bool head = hit && (lane == 0 || !((hits >> (lane - 1)) & 1ull) || before != vox);
+        const uint64_t ends = (__ballot(head) | ~hits) >> lane >> 1;      // where a run after this lane ends
+        if (head) atomicAdd(cnt + vox, ends ? uint32_t(__ffsll((unsigned long long)ends)) : uint32_t(64 - lane));
+    }
+    if (mine) atomicAdd(&s_total, (unsigned long long)mine);
+    __syncthreads();
+    if (tid == 0 && s_total) atomicAdd(reinterpret_cast<unsigned long long *>(total), s_total);
+}
+
+// Apply the accumulators (unless the scan has more observations than the
+// volume takes) and hand their number to the host.
+__global__ void k_laser_apply_sums(const uint32_t *__restrict__ cnt, const unsigned long long *__restrict__ sum,
+                                   int64_t nvox, double inv_scale, const int64_t *__restrict__ total, int64_t most,
+                                   int64_t *host, float *__restrict__ f, float *__restrict__ w)
+{
+    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    const int64_t m = *total;
+    if (i == 0) *host = m;
+    if (m > most || i >= nvox) return;
+    const uint32_t c = cnt[i];
+    if (c == 0) return;
+    const double w0 = w[i], wn = w0 + double(c);
+    const double psi = double(c) - double(sum[i]) * inv_scale;
+    f[i] = float((w0 * double(f[i]) + psi) / wn);
+    w[i] = float(wn);
 }
 
 // One scan's update of each observed voxel, from the per-voxel sums and
@@ -764,22 +1323,6 @@ static LaserScratch carve_laser(Bump &b, int64_t n, int64_t m)
     x.v_in = b.take<double>(size_t(m));
     x.v_out = b.take<double>(size_t(m));
     x.tmp_bytes = std::max(std::max(tmp_light(size_t(n)), tmp_light(size_t(m))), tmp_sort(size_t(m), 12));
-    x.tmp = b.take<char>(x.tmp_bytes);
-    return x;
-}
-
-// Scratch of the band count of one frame (or scan) of n points.
-struct FrameScratch {
-    int32_t *counts, *offs;
-    void *tmp;
-    size_t tmp_bytes;
-};
-static FrameScratch carve_frame(Bump &b, int64_t n)
-{
-    FrameScratch x;
-    x.counts = b.take<int32_t>(size_t(n));
-    x.offs = b.take<int32_t>(size_t(n) + 2);
-    x.tmp_bytes = tmp_light(size_t(n));
     x.tmp = b.take<char>(x.tmp_bytes);
     return x;
 }
@@ -842,6 +1385,11 @@ static size_t volume_layout(const dn_volume_params &p, void *base, dn_volume *v)
     uint64_t *keys = b.take<uint64_t>(mb);
     int32_t *h0 = b.take<int32_t>(slots * 4);
     int32_t *h1 = b.take<int32_t>(slots * 4);
+    uint32_t *oh0 = b.take<uint32_t>(mb), *oh1 = b.take<uint32_t>(mb);
+    int32_t *oi0 = b.take<int32_t>(mb), *oi1 = b.take<int32_t>(mb);
+    uint64_t *nset = b.take<uint64_t>(kNewSet), *nkey = b.take<uint64_t>(kMaxNew), *skey = b.take<uint64_t>(kMaxNew);
+    uint32_t *nhome = b.take<uint32_t>(kMaxNew), *nslot = b.take<uint32_t>(kMaxNew), *shome = b.take<uint32_t>(kMaxNew);
+    int32_t *sid = b.take<int32_t>(kMaxNew);
     int32_t *nbr = b.take<int32_t>(mb * kNbr);
     float *f = b.take<float>(vox);
     float *w = b.take<float>(vox);
@@ -870,11 +1418,6 @@ static size_t volume_layout(const dn_volume_params &p, void *base, dn_volume *v)
     auto upd = [&](size_t n) { need = std::max(need, n); };
     {
         Bump m(nullptr, 0);
-        carve_frame(m, p.max_points);
-        upd(m.off);
-    }
-    {
-        Bump m(nullptr, 0);
         carve_insert(m, std::max<int64_t>(p.max_candidates, 1), p.max_blocks);
         upd(m.off);
     }
@@ -886,13 +1429,15 @@ static size_t volume_layout(const dn_volume_params &p, void *base, dn_volume *v)
         carve_laser(m, p.max_points, p.max_observations);
         upd(m.off);
     }
-    upd(size_t(p.max_blocks) * sizeof(int32_t));   // the blocks in view of a fused frame
     char *scratch = b.take<char>(need);
     if (v) {
         v->coords = coords; v->keys = keys; v->hash[0] = h0; v->hash[1] = h1; v->nbr = nbr;
         v->f = f; v->w = w; v->u = u; v->ubar[0] = ub0; v->ubar[1] = ub1; v->p[0] = p0; v->p[1] = p1;
         v->emask = emask; v->em4 = em4; v->order = order; v->partials = partials; v->energy2 = energy2; v->misc = misc;
         v->cand = cand;
+        v->hord_home[0] = oh0; v->hord_home[1] = oh1; v->hord_ids[0] = oi0; v->hord_ids[1] = oi1;
+        v->new_set = nset; v->new_key = nkey; v->sort_key = skey; v->new_home = nhome; v->new_slot = nslot;
+        v->sort_home = shome; v->sort_id = sid;
         v->u16 = u16; v->ubar16[0] = ub16a; v->ubar16[1] = ub16b; v->p16[0] = p16a; v->p16[1] = p16b;
         v->scratch = scratch;
         v->scratch_bytes = need;
@@ -923,9 +1468,6 @@ static int verify_tmp_bounds(dn_volume *v)
     size_t t = 0;
     int32_t *i32 = nullptr; int64_t *i64 = nullptr; uint64_t *u64 = nullptr; uint32_t *u32 = nullptr;
     uint8_t *u8 = nullptr; double *f64 = nullptr;
-    DN_HIP(rocprim::exclusive_scan(nullptr, t, i32, i32, 0, np, rocprim::plus<int32_t>(), st));
-    q.push_back({"point scan", t, tmp_light(np)});
-    t = 0;
     DN_HIP(rocprim::select(nullptr, t, u64, u8, u64, i64, nc, st));
     q.push_back({"candidate selection", t, tmp_light(nc)});
     t = 0;
@@ -978,10 +1520,11 @@ static int verify_tmp_bounds(dn_volume *v)
     return DN_OK;
 }
 
-// Band cells of n points (depth pixels or laser returns): count, scan, check
-// the limit, emit into v->cand; then the shared insertion.
-template <class Count, class Emit>
-static int alloc_points(dn_volume *v, int64_t n, Count count, Emit emit, int32_t *n_new_out)
+// Allocation for n points (depth pixels or laser returns): walk their
+// bands, check the limits, turn the new keys into blocks.  A frame with more
+// new keys than k_band lists, or a pool past kMergeBlocks, takes the general
+// insertion of the listed keys.
+template <class Band> static int alloc_points(dn_volume *v, int64_t n, const Band &band, int32_t *n_new_out)
 {
     if (n_new_out) *n_new_out = 0;
     v->cand_n = 0;
@@ -991,28 +1534,31 @@ static int alloc_points(dn_volume *v, int64_t n, Count count, Emit emit, int32_t
         return DN_E_CAPACITY;
     }
     hipStream_t st = v->stream;
-    Bump bump(v->scratch, v->scratch_bytes);
-    FrameScratch x = carve_frame(bump, n);
-    if (!bump.fits()) { set_error("scratch too small for %lld points", (long long)n); return DN_E_CAPACITY; }
-    count(x.counts);
+    BandOut o{v->cand, v->prm.max_candidates, v->new_set, v->new_key, v->new_home, v->new_slot, v->misc, report(v)};
+    const int4 *slots = reinterpret_cast<const int4 *>(v->hash[v->cur_hash]);
+    if (n <= kBandSmall)
+        hipLaunchKernelGGL((k_band<Band, 256>), dim3(grid1(n, 256)), dim3(256), 0, st, band, n, slots, v->hash_slots,
+                           v->hash_cap, o);
+    else
+        hipLaunchKernelGGL((k_band<Band, 1024>), dim3(grid1(n, 1024)), dim3(1024), 0, st, band, n, slots,
+                           v->hash_slots, v->hash_cap, o);
     DN_HIP(hipGetLastError());
-    size_t tbytes = x.tmp_bytes;
-    DN_HIP(rocprim::exclusive_scan(x.tmp, tbytes, x.counts, x.offs, 0, size_t(n), rocprim::plus<int32_t>(), st));
-    int32_t pair[2];
-    DN_HIP(hipMemcpyAsync(reinterpret_cast<char *>(v->host_stage), x.offs + n - 1, 4, hipMemcpyDeviceToHost, st));
-    DN_HIP(hipMemcpyAsync(reinterpret_cast<char *>(v->host_stage) + 4, x.counts + n - 1, 4, hipMemcpyDeviceToHost, st));
-    DN_HIP(hipStreamSynchronize(st));
-    memcpy(pair, v->host_stage, 8);
-    const int64_t total = int64_t(pair[0]) + pair[1];
-    if (total == 0) return DN_OK;
+    int rc = fetch_report(v, 5);
+    if (rc) return rc;
+    const int64_t total = v->host_stage[0], listed = v->host_stage[1], n_new = v->host_stage[2], end = v->host_stage[4];
+    const bool full = v->host_stage[3] != 0;
     if (total > v->prm.max_candidates) {
+        if ((n_new > 0 || full) && (rc = reset_new_set(v))) return rc;
         set_error("%lld band cells exceed the volume's max_candidates %lld", (long long)total,
                   (long long)v->prm.max_candidates);
         return DN_E_CAPACITY;
     }
-    emit(x.offs, total);
-    DN_HIP(hipGetLastError());
-    return insert_packed(v, v->cand, total, n_new_out);
+    v->cand_n = listed;
+    if (n_new == 0 && !full) return DN_OK;
+    if (!full && v->nb + n_new <= v->cap_blocks && v->nb + n_new <= kMergeBlocks)
+        return insert_listed(v, n_new, end, n_new_out);
+    if ((rc = reset_new_set(v))) return rc;
+    return insert_packed(v, v->cand, listed, n_new_out);
 }
 
 }  // namespace dn
@@ -1060,9 +1606,8 @@ int dn_volume_create(const dn_volume_params *p, void *arena, size_t arena_bytes,
     int rc = verify_tmp_bounds(v);
     if (rc) return fail(rc);
     hipStream_t st = v->stream;
-    const int64_t vox = int64_t(v->cap_blocks) * kBlockVox;
-    hipLaunchKernelGGL(k_zero_blocks, dim3(grid1(vox)), dim3(256), 0, st, v->f, int64_t(0), v->cap_blocks);
-    hipLaunchKernelGGL(k_zero_blocks, dim3(grid1(vox)), dim3(256), 0, st, v->w, int64_t(0), v->cap_blocks);
+    // (a block's fields are zeroed when it is allocated)
+    hipLaunchKernelGGL(k_init_misc, dim3(grid1(kNewSet)), dim3(256), 0, st, v->misc, v->new_set);
     hipLaunchKernelGGL(k_fill_empty, dim3(grid1(v->hash_slots)), dim3(256), 0, st,
                        reinterpret_cast<int4 *>(v->hash[0]), v->hash_slots);
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
@@ -1087,11 +1632,6 @@ int dn_volume_clear(dn_volume *v)
     hipLaunchKernelGGL(k_fill_empty, dim3(grid1(v->hash_slots)), dim3(256), 0, st,
                        reinterpret_cast<int4 *>(v->hash[v->cur_hash]), v->hash_slots);
     DN_HIP(hipGetLastError());
-    if (v->nb > 0) {
-        hipLaunchKernelGGL(k_zero_blocks, dim3(grid1(v->nb * kBlockVox)), dim3(256), 0, st, v->f, int64_t(0), v->nb);
-        hipLaunchKernelGGL(k_zero_blocks, dim3(grid1(v->nb * kBlockVox)), dim3(256), 0, st, v->w, int64_t(0), v->nb);
-        DN_HIP(hipGetLastError());
-    }
     v->nb = 0;
     v->nb_state = 0;
     v->emask_nb = -1;
@@ -1104,6 +1644,27 @@ int dn_set_stream(dn_volume *v, void *hip_stream)
 {
     DN_REQUIRE(v, "null volume");
     v->stream = static_cast<hipStream_t>(hip_stream);
+    return DN_OK;
+}
+
+int dn_set_report_buffer(dn_volume *v, void *pinned, size_t bytes)
+{
+    DN_REQUIRE(v, "null volume");
+    DN_HIP(hipStreamSynchronize(v->stream));
+    if (!pinned) {
+        v->report = v->report_host = nullptr;
+        return DN_OK;
+    }
+    DN_REQUIRE(bytes >= DN_REPORT_BYTES && (reinterpret_cast<uintptr_t>(pinned) & 7) == 0,
+               "the report buffer must hold DN_REPORT_BYTES, 8-byte aligned");
+    void *dev = nullptr;
+    if (hipHostGetDevicePointer(&dev, pinned, 0) != hipSuccess || !dev) {
+        (void)hipGetLastError();
+        set_error("the report buffer is not pinned host memory");
+        return DN_E_INVALID;
+    }
+    v->report = static_cast<int64_t *>(dev);
+    v->report_host = static_cast<int64_t *>(pinned);
     return DN_OK;
 }
 
@@ -1122,17 +1683,7 @@ int dn_alloc_blocks(dn_volume *v, const float *depth, const dn_intrinsics *K, co
     Geo g;
     int rc = make_geo(v, K, T, g);
     if (rc) return rc;
-    hipStream_t st = v->stream;
-    const int64_t npx = int64_t(g.W) * g.H;
-    return alloc_points(
-        v, npx,
-        [&](int32_t *counts) {
-            hipLaunchKernelGGL(k_dda_count, dim3(grid1(npx)), dim3(256), 0, st, g, depth, counts);
-        },
-        [&](const int32_t *offs, int64_t total) {
-            hipLaunchKernelGGL(k_dda_emit, dim3(grid1(npx)), dim3(256), 0, st, g, depth, offs, v->cand, total);
-        },
-        n_new_out);
+    return alloc_points(v, int64_t(g.W) * g.H, DepthBand{g, depth}, n_new_out);
 }
 
 static int insert_keys(dn_volume *v, const int32_t *coords, int64_t n, int32_t *n_new_out, bool keep_order)
@@ -1168,13 +1719,10 @@ int dn_fuse_depth(dn_volume *v, const float *depth, const dn_intrinsics *K, cons
     int rc = make_geo(v, K, T, g);
     if (rc) return rc;
     if (v->nb == 0) return DN_OK;
-    int32_t *list = reinterpret_cast<int32_t *>(v->scratch);
-    int32_t *count = reinterpret_cast<int32_t *>(v->misc + kMiscFuseCount);
-    hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(1), 0, v->stream, count);
-    hipLaunchKernelGGL(k_cull, dim3(grid1(v->nb)), dim3(256), 0, v->stream, g, v->coords, v->nb, list, count);
-    DN_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_fuse_list, dim3(unsigned(std::min<int64_t>(v->nb, kFuseGrid))), dim3(256), 0, v->stream,
-                       g, depth, v->coords, list, count, v->f, v->w);
+    // a workgroup for each block of a small map's groups, fewer where most groups are out of view
+    const int share = v->nb <= 16384 ? 32 : 4;
+    hipLaunchKernelGGL(k_fuse, dim3(grid1(v->nb, 64) * unsigned(share)), dim3(256), 0, v->stream, g, depth, v->coords,
+                       v->nb, share, v->f, v->w);
     DN_HIP(hipGetLastError());
     v->emask_nb = -1;
     return DN_OK;
@@ -1197,16 +1745,7 @@ int dn_alloc_laser(dn_volume *v, const float *pts, int64_t n, const double T[16]
     LGeo g;
     int rc = make_lgeo(v, T, g);
     if (rc) return rc;
-    hipStream_t st = v->stream;
-    return alloc_points(
-        v, n,
-        [&](int32_t *counts) {
-            hipLaunchKernelGGL(k_laser_cand_count, dim3(grid1(n)), dim3(256), 0, st, g, pts, n, counts);
-        },
-        [&](const int32_t *offs, int64_t total) {
-            hipLaunchKernelGGL(k_laser_cand_emit, dim3(grid1(n)), dim3(256), 0, st, g, pts, n, offs, v->cand, total);
-        },
-        n_new_out);
+    return alloc_points(v, n, LaserBand{g, pts}, n_new_out);
 }
 
 int dn_fuse_laser(dn_volume *v, const float *pts, int64_t n, const double T[16])
@@ -1225,6 +1764,35 @@ int dn_fuse_laser(dn_volume *v, const float *pts, int64_t n, const double T[16])
     hipStream_t st = v->stream;
     const int4 *slots = reinterpret_cast<const int4 *>(v->hash[v->cur_hash]);
     Bump bump(v->scratch, v->scratch_bytes);
+    const int64_t nvox = v->nb * int64_t(kBlockVox);
+    uint32_t *cnt = bump.take<uint32_t>(size_t(nvox));
+    unsigned long long *sum = bump.take<unsigned long long>(size_t(nvox));
+    if (v->nb <= kAccumBlocks && bump.fits()) {
+        // sums of at most n terms in [0, 2], each 2^bits per unit
+        int bits = 61;
+        while (bits > 0 && (n >> (61 - bits)) > 0) --bits;
+        const double scale = std::ldexp(1.0, bits), inv = std::ldexp(1.0, -bits);
+        int64_t *total = v->misc + kMiscObs;
+        hipLaunchKernelGGL(k_laser_clear, dim3(grid1(nvox / 4)), dim3(256), 0, st, cnt, sum, nvox, total);
+        // (the whole map in the table: every block that a ray can reach has a tag)
+        const bool all = v->nb <= kSeenAll && (g.maxd + g.mu) / (8.0 * g.s) <= kSeenRange;
+        hipLaunchKernelGGL(all ? k_laser_accumulate<true> : k_laser_accumulate<false>, dim3(grid1(n), 2), dim3(256), 0,
+                           st, g, pts, n, slots, v->hash_slots, v->hash_cap, reinterpret_cast<const int4 *>(v->coords),
+                           int(v->nb), scale, cnt, sum, total);
+        hipLaunchKernelGGL(k_laser_apply_sums, dim3(grid1(nvox)), dim3(256), 0, st, cnt, sum, nvox, inv, total,
+                           v->prm.max_observations, report(v), v->f, v->w);
+        DN_HIP(hipGetLastError());
+        if ((rc = fetch_report(v, 1))) return rc;
+        const int64_t m = v->host_stage[0];
+        if (m > v->prm.max_observations) {
+            set_error("%lld laser observations exceed the volume's max_observations %lld", (long long)m,
+                      (long long)v->prm.max_observations);
+            return DN_E_CAPACITY;
+        }
+        if (m > 0) v->emask_nb = -1;
+        return DN_OK;
+    }
+    bump = Bump(v->scratch, v->scratch_bytes);
     LaserScratch x = carve_laser(bump, n, v->prm.max_observations);
     if (!bump.fits()) { set_error("scratch too small for the laser observations"); return DN_E_CAPACITY; }
     hipLaunchKernelGGL(k_laser_obs_count, dim3(grid1(n)), dim3(256), 0, st, g, pts, n, slots, v->hash_slots,

@@ -93,6 +93,7 @@ def lib():
         "dn_warm_start_bytes": (sz, [i64]),
         "dn_volume_destroy": (None, [P]),
         "dn_set_stream": (i32, [P, P]),
+        "dn_set_report_buffer": (i32, [P, P, sz]),
         "dn_volume_clear": (i32, [P]),
         "dn_num_blocks": (i64, [P]),
         "dn_sync": (i32, [P]),
@@ -228,12 +229,14 @@ class Volume:
         check(lib().dn_volume_create(ctypes.byref(self.params), ctypes.c_void_p(addr), self.arena_bytes,
                                      _stream_handle(self.stream), ctypes.byref(h)))
         self.handle = h
+        self._report = torch.empty(64, dtype=torch.uint8, pin_memory=True)
+        check(lib().dn_set_report_buffer(h, ctypes.c_void_p(self._report.data_ptr()), 64))
 
     def close(self):
         if getattr(self, "handle", None):
             lib().dn_volume_destroy(self.handle)
             self.handle = None
-        self._arena = None
+        self._arena = self._report = None
 
     def __del__(self):
         try:
