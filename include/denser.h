@@ -387,12 +387,10 @@ int dn_net_forward(const float *tiles_dev, int64_t n, const float *params_dev, f
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation): the
- * forward pass of dn_net_forward with no workspace argument.  Its scratch
- * is a static device array inside the library (one per GPU, about 3.4 MB,
- * held until the process ends), so it takes at most DN_NET_STATIC_TILES
- * tiles per call (else DN_E_CAPACITY) and calls that overlap on one GPU
- * race (they share that array).  Same arguments and result as
- * dn_net_forward; enqueue only. */
+ * forward pass of dn_net_forward with no workspace argument, at most
+ * DN_NET_STATIC_TILES tiles per call (else DN_E_CAPACITY).  Same arguments
+ * and result as dn_net_forward; enqueue only, no scratch, so calls may
+ * overlap. */
 #define DN_NET_STATIC_TILES 32
 int dn_net_forward_static(const float *tiles_dev, int64_t n, const float *params_dev, float *out_dev,
                           void *hip_stream);

@@ -2,29 +2,25 @@
 // (an 8^3 block plus a one-voxel halo), 2 -> 16 -> 16 -> 1 channels, ReLU,
 // "same" zero padding inside the tile.
 //
-// Training path (forward, input gradient, weight gradient): one implicit
-// GEMM launch per layer on v_mfma_f32_16x16x16_bf16 (bfloat16 operands,
-// float32 accumulation; one MFMA = 16 voxels x 16 output channels x 16 input
-// channels of one tap), activations stored channel-last in bfloat16,
-// [tile][1000][16], unused channels zero.
+// Forward pass of given tiles: k_net_tiles, one launch on
+// v_mfma_f32_16x16x16_bf16 (bfloat16 operands, float32 accumulation; one
+// MFMA = 16 voxels x 16 output channels x 16 input channels of one tap).
 //
-// Inference path (warm start): one fused launch per axis, k_net_fwd, on
-// v_mfma_f32_16x16x32_bf16 with all activations in LDS and the weights in
-// registers.  Its layer loops read one 1 KiB activation operand from LDS per
+// Inference path (warm start) and the forward half of a training step: one
+// fused launch, k_net_fwd, on v_mfma_f32_16x16x32_bf16 with all activations
+// in LDS and the weights in registers.  Its layer loops read one 1 KiB activation operand from LDS per
 // MFMA; at the measured ~140 B/clk of 16-byte LDS reads per CU that bounds
 // it near half the matrix peak.
 #include <cstring>
 
 #include <algorithm>
 #include <cmath>
-#include <mutex>
 #include <vector>
 
 #include "dn_internal.h"
 
 namespace dn {
 
-typedef short v4s __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int kT = 1000;      // voxels of a 10^3 tile
@@ -51,116 +47,6 @@ __device__ __forceinline__ uint16_t f2bf(float x)
     return uint16_t(u >> 16);
 }
 __device__ __forceinline__ float bf2f(uint16_t v) { return __uint_as_float(uint32_t(v) << 16); }
-
-// voxel v of a tile -> coordinates; neighbour through tap t (offset -1..1)
-__device__ __forceinline__ int tap_neighbour(int v, int t)
-{
-    int x = v % 10, y = (v / 10) % 10, z = v / 100;
-    x += t % 3 - 1; y += (t / 3) % 3 - 1; z += t / 9 - 1;
-    if (x < 0 || x > 9 || y < 0 || y > 9 || z < 0 || z > 9) return -1;
-    return (z * 10 + y) * 10 + x;
-}
-
-__device__ __forceinline__ void load_tile(uint16_t *dst, const uint16_t *src)
-{
-    const uint4 *s = reinterpret_cast<const uint4 *>(src);
-    uint4 *d = reinterpret_cast<uint4 *>(dst);
-    for (int i = threadIdx.x; i < kT * kC / 8; i += blockDim.x) d[i] = s[i];
-}
-
-// One convolution layer on one tile per workgroup (256 threads = 4 waves).
-//   Y[v][co] = bias[co] + sum_t sum_ci W[t][co][ci] X[v + off(t)][ci]
-// then optional ReLU, optional gate (multiply by [G[v][co] > 0], the ReLU
-// derivative of the backward pass), stored as bfloat16 (Y) and/or channel 0
-// as float (Yf).  With Wlo the weights are the pair Wp + Wlo (a second
-// bfloat16 holding what the first rounded off).
-__global__ __launch_bounds__(256) void k_conv(const uint16_t *__restrict__ X, int64_t n,
-                                              const uint16_t *__restrict__ Wp, const uint16_t *__restrict__ Wlo,
-                                              const float *__restrict__ bias, int relu,
-                                              const uint16_t *__restrict__ gate, uint16_t *__restrict__ Y,
-                                              float *__restrict__ Yf)
-{
-    __shared__ __align__(16) uint16_t sx[kT * kC];
-    __shared__ __align__(16) uint16_t sw[kWPack];
-    __shared__ __align__(16) uint16_t swl[kWPack];
-    const int64_t tile = blockIdx.x;
-    if (tile >= n) return;
-    load_tile(sx, X + tile * kT * kC);
-    {
-        const uint4 *s = reinterpret_cast<const uint4 *>(Wp);
-        uint4 *d = reinterpret_cast<uint4 *>(sw);
-        for (int i = threadIdx.x; i < kWPack / 8; i += blockDim.x) d[i] = s[i];
-        if (Wlo) {
-            const uint4 *sl = reinterpret_cast<const uint4 *>(Wlo);
-            uint4 *dl = reinterpret_cast<uint4 *>(swl);
-            for (int i = threadIdx.x; i < kWPack / 8; i += blockDim.x) dl[i] = sl[i];
-        }
-    }
-    __syncthreads();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int i = lane & 15, kg = lane >> 4;
-    const float bv = bias ? bias[i] : 0.0f;
-    for (int mt = wave; mt < kMT; mt += 4) {
-        const int v = mt * 16 + i;
-        v4f acc = {0.f, 0.f, 0.f, 0.f};
-        for (int t = 0; t < kTaps; ++t) {
-            v4s a = {0, 0, 0, 0};
-            if (v < kT) {
-                int nvx = tap_neighbour(v, t);
-                if (nvx >= 0) a = *reinterpret_cast<const v4s *>(&sx[nvx * kC + 4 * kg]);
-            }
-            v4s b = *reinterpret_cast<const v4s *>(&sw[(t * kC + i) * kC + 4 * kg]);
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
-            if (Wlo) {
-                v4s bl = *reinterpret_cast<const v4s *>(&swl[(t * kC + i) * kC + 4 * kg]);
-                acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, bl, acc, 0, 0, 0);
-            }
-        }
-        for (int r = 0; r < 4; ++r) {
-            const int vo = mt * 16 + 4 * kg + r;
-            if (vo >= kT) continue;
-            float y = acc[r] + bv;
-            if (relu) y = y > 0.f ? y : 0.f;
-            const int64_t o = (tile * kT + vo) * kC + i;
-            if (gate) {
-                uint16_t g = gate[o];
-                if ((g & 0x8000u) || (g & 0x7FFFu) == 0) y = 0.f;
-            }
-            if (Y) Y[o] = f2bf(y);
-            if (Yf && i == 0) Yf[tile * kT + vo] = y;
-        }
-    }
-}
-
-// Pack the float parameters into bfloat16 [tap][co][ci] layers, zero padded
-// to 16x16; lo = 1 gives the low part bfloat16(W - bfloat16(W)) (layer 1
-// runs on the pair hi + lo).
-__global__ void k_pack(const float *__restrict__ W, int cout, int cin, int lo, uint16_t *__restrict__ out)
-{
-    int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= kWPack) return;
-    int t = k / (kC * kC), a = (k / kC) % kC, b = k % kC;
-    float val = 0.f;
-    if (a < cout && b < cin) val = W[(a * cin + b) * kTaps + t];
-    if (lo) val -= bf2f(f2bf(val));
-    out[k] = f2bf(val);
-}
-
-// float tiles [n][2][1000] -> bfloat16 [n][1000][16]
-__global__ void k_tiles_to_bf16(const float *__restrict__ tiles, int64_t n, uint16_t *__restrict__ X)
-{
-    int64_t k = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (k >= n * kT) return;
-    int64_t tile = k / kT;
-    int v = int(k % kT);
-    uint16_t out[16];
-    out[0] = f2bf(tiles[tile * 2 * kT + v]);
-    out[1] = f2bf(tiles[tile * 2 * kT + kT + v]);
-    for (int c = 2; c < 16; ++c) out[c] = 0;
-    uint4 *d = reinterpret_cast<uint4 *>(X + k * kC);
-    d[0] = *reinterpret_cast<uint4 *>(&out[0]);
-    d[1] = *reinterpret_cast<uint4 *>(&out[8]);
-}
 
 __device__ __forceinline__ int64_t halo_vox(const int32_t *nb27, int hx, int hy, int hz)
 {
@@ -364,9 +250,6 @@ constexpr int kLaneW = (2 * kL1M + kL2M + kL3M) * 64 * 8;
 // weights, activations of n tiles and, for training, their gradients and
 // the weight-gradient partial sums.
 struct NetWS {
-    // forward (dn_net_forward)
-    uint16_t *wpack, *x0, *h1, *h2;
-    float *r;
     // training step (dn_net_loss_grad)
     uint16_t *lanew, *lanef, *gates, *x1cf, *h1cf, *h2cf, *d3cf, *d2cf, *d1cf;
     float *rc, *d3, *parts;
@@ -379,11 +262,11 @@ static NetWS carve_net(Bump &b, int64_t n, bool training)
     NetWS x{};
     if (!training) {
         const size_t act = size_t(n) * kT * kC;
-        x.wpack = b.take<uint16_t>(size_t(4) * kWPack);
-        x.x0 = b.take<uint16_t>(act);
-        x.h1 = b.take<uint16_t>(act);
-        x.h2 = b.take<uint16_t>(act);
-        x.r = b.take<float>(size_t(n) * kT);
+        // the forward pass keeps its activations in LDS; the size callers
+        // allocate by stays what it was
+        b.take<uint16_t>(size_t(4) * kWPack);
+        for (int k = 0; k < 3; ++k) b.take<uint16_t>(act);
+        b.take<float>(size_t(n) * kT);
         return x;
     }
     x.lanew = b.take<uint16_t>(size_t(kLaneW));
@@ -1395,73 +1278,162 @@ __global__ __launch_bounds__(512) void k_wgrad_mfma(const uint16_t *__restrict__
     }
 }
 
-static int pack_all(hipStream_t st, const float *params, uint16_t *wp)
+// Forward pass of n given tiles, every layer as 27 products of 16 voxels x 16
+// output channels x 16 input channels (v_mfma_f32_16x16x16_bf16), one per
+// tap in order (layer 1 its weights' high and low parts), so each output is
+// the same sum in the same order whatever the batch.  One workgroup takes a
+// tile at a time; all activations lie in LDS on the zero-bordered 12^3 grid,
+// where every tap is a fixed offset, and the weights are rounded and packed
+// there once per workgroup: one launch and no scratch.  Bound by the latency
+// of a tile up to one tile per compute unit, then by the LDS operand reads.
+// With a launch per layer, index arithmetic per tap and five launches to pack
+// the weights and the tiles, 32 tiles took 172 us and 1024 357; now 25 and 88.
+typedef short v4s __attribute__((ext_vector_type(4)));
+constexpr int kFwdWaves = 16, kFwdRows = (kMT + kFwdWaves - 1) / kFwdWaves;   // row tiles per wave
+constexpr int kFwdTap2 = kC * kC + 4, kFwdTap1 = kC * 4 + 4;
+struct FwdLds {
+    alignas(16) uint16_t h1[kPadVox * kC], h2[kPadVox * kC];     // [padded voxel][channel]
+    // weights by tap, the taps 2 (mod 64) LDS banks apart so that packing
+    // them in parameter order (taps fastest) meets no bank twice
+    alignas(16) uint16_t w2[kTaps * kFwdTap2];                   // [tap][output][input channel]
+    alignas(16) uint16_t w1[kTaps * kFwdTap1], w1l[kTaps * kFwdTap1];   // [tap][output][4 inputs, 2 used], high, low parts
+    alignas(16) uint16_t w3[kTaps * kC];                         // [tap][input channel]
+    uint32_t x0[kPadVox];                                        // the two input channels
+};
+__global__ __launch_bounds__(64 * kFwdWaves) void k_net_tiles(const float *__restrict__ tiles, int64_t n,
+                                                              const float *__restrict__ params,
+                                                              float *__restrict__ out)
 {
-    hipLaunchKernelGGL(k_pack, dim3(grid1(kWPack)), dim3(256), 0, st, params + kW1, 16, 2, 0, wp);
-    hipLaunchKernelGGL(k_pack, dim3(grid1(kWPack)), dim3(256), 0, st, params + kW2, 16, 16, 0, wp + kWPack);
-    hipLaunchKernelGGL(k_pack, dim3(grid1(kWPack)), dim3(256), 0, st, params + kW3, 1, 16, 0, wp + 2 * kWPack);
-    hipLaunchKernelGGL(k_pack, dim3(grid1(kWPack)), dim3(256), 0, st, params + kW1, 16, 2, 1, wp + 3 * kWPack);
-    DN_HIP(hipGetLastError());
-    return DN_OK;
-}
-
-// Forward of n tiles already in ws.x0 (packed weights in ws.wpack): h1, h2
-// (bfloat16) and the residual r (float) of every tile voxel.
-static int forward_tiles(hipStream_t st, const float *params, int64_t n, const NetWS &ws)
-{
-    if (n <= 0) return DN_OK;
-    const uint16_t *wp = ws.wpack;
-    uint16_t *x0 = ws.x0, *h1 = ws.h1, *h2 = ws.h2;
-    hipLaunchKernelGGL(k_conv, dim3(unsigned(n)), dim3(256), 0, st, x0, n, wp, wp + 3 * kWPack, params + kB1, 1,
-                       (const uint16_t *)nullptr, h1, (float *)nullptr);
-    hipLaunchKernelGGL(k_conv, dim3(unsigned(n)), dim3(256), 0, st, h1, n, wp + kWPack, (const uint16_t *)nullptr,
-                       params + kB2, 1, (const uint16_t *)nullptr, h2, (float *)nullptr);
-    hipLaunchKernelGGL(k_conv, dim3(unsigned(n)), dim3(256), 0, st, h2, n, wp + 2 * kWPack, (const uint16_t *)nullptr,
-                       params + kB3, 0, (const uint16_t *)nullptr, (uint16_t *)nullptr, ws.r);
-    DN_HIP(hipGetLastError());
-    return DN_OK;
-}
-
-// One forward pass of n tiles in the given workspace (sized by the caller).
-static int forward_into(const float *tiles, int64_t n, const float *params, float *out, void *workspace,
-                        size_t workspace_bytes, hipStream_t st)
-{
-    Bump bump(workspace, workspace_bytes);
-    const NetWS ws = carve_net(bump, n, false);
-    if (!bump.fits()) { set_error("network workspace too small"); return DN_E_CAPACITY; }
-    int rc;
-    if ((rc = pack_all(st, params, ws.wpack))) return rc;
-    hipLaunchKernelGGL(k_tiles_to_bf16, dim3(grid1(n * kT)), dim3(256), 0, st, tiles, n, ws.x0);
-    DN_HIP(hipGetLastError());
-    if ((rc = forward_tiles(st, params, n, ws))) return rc;
-    DN_HIP(hipMemcpyAsync(out, ws.r, size_t(n) * kT * 4, hipMemcpyDeviceToDevice, st));
-    return DN_OK;
-}
-
-// Scratch of dn_net_forward_static: a file-scope device array, one copy per
-// GPU, held until the process ends.  In host code its name is only a
-// stand-in; the address each device's copy has is looked up once per device
-// (with that device current) and kept.
-constexpr size_t kNetStaticBytes = size_t(DN_NET_STATIC_TILES) * (size_t(kT) * kC * 2 * 3 + size_t(kT) * 4 + 1024) +
-                                   size_t(4) * kWPack * 2 + 4096;
-static __device__ __align__(256) unsigned char scratch[kNetStaticBytes];
-constexpr int kMaxDevices = 64;
-static void *g_scratch_ptr[kMaxDevices] = {};
-static std::mutex g_scratch_mutex;
-
-static int static_scratch(void **out)
-{
-    int dev = 0;
-    DN_HIP(hipGetDevice(&dev));
-    DN_REQUIRE(dev >= 0 && dev < kMaxDevices, "device index %d out of range", dev);
-    std::lock_guard<std::mutex> lk(g_scratch_mutex);
-    if (!g_scratch_ptr[dev]) {
-        void *p = nullptr;
-        DN_HIP(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
-        DN_REQUIRE(p && (reinterpret_cast<uintptr_t>(p) & 255) == 0, "static scratch misaligned");
-        g_scratch_ptr[dev] = p;
+    __shared__ FwdLds sh;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    constexpr int kThreads = 64 * kFwdWaves;
+    // a thread's voxel of the tile, if it has one, and its input, loaded a tile ahead
+    float nf = 0.f, nw = 0.f;
+    auto fetch = [&](int64_t tile) {
+        if (tid < kT) {
+            nf = tiles[tile * 2 * kT + tid];
+            nw = tiles[tile * 2 * kT + kT + tid];
+        }
+    };
+    static_assert(kThreads >= kT, "one voxel per thread");
+    if (blockIdx.x < n) fetch(blockIdx.x);
+    for (int k = tid; k < kPadVox * kC / 8; k += kThreads) {
+        reinterpret_cast<uint4 *>(sh.h1)[k] = make_uint4(0, 0, 0, 0);
+        reinterpret_cast<uint4 *>(sh.h2)[k] = make_uint4(0, 0, 0, 0);
     }
-    *out = g_scratch_ptr[dev];
+    for (int k = tid; k < kPadVox; k += kThreads) sh.x0[k] = 0u;
+    for (int k = tid; k < kTaps * kC * kC; k += kThreads) {      // parameter order: coalesced reads
+        const int t = k % kTaps, ci = (k / kTaps) % kC, co = k / (kTaps * kC);
+        sh.w2[t * kFwdTap2 + co * kC + ci] = f2bf(params[kW2 + k]);
+    }
+    for (int k = tid; k < kTaps * kC * 2; k += kThreads) {
+        const int t = k % kTaps, ci = (k / kTaps) % 2, co = k / (kTaps * 2);
+        const float w = params[kW1 + k];
+        const int at = t * kFwdTap1 + co * 4 + ci;
+        sh.w1[at] = f2bf(w);
+        sh.w1l[at] = f2bf(w - bf2f(f2bf(w)));
+        sh.w1[at + 2] = 0;
+        sh.w1l[at + 2] = 0;
+    }
+    for (int k = tid; k < kTaps * kC; k += kThreads) sh.w3[(k % kTaps) * kC + k / kTaps] = f2bf(params[kW3 + k]);
+    const int i = lane & 15, kg = lane >> 4;
+    const float b1 = params[kB1 + i], b2 = params[kB2 + i], b3 = params[kB3];
+    // the wave's row tiles: wave, wave + 16, ...; this lane's row (an operand)
+    // and its four rows of the result, on the padded grid
+    int row[kFwdRows], res[kFwdRows][4];
+#pragma unroll
+    for (int q = 0; q < kFwdRows; ++q) {
+        const int mt = wave + q * kFwdWaves;
+        auto padded = [](int v) { return v < kT ? pad_index(v % 10, (v / 10) % 10, v / 100) : -1; };
+        const int v = padded(mt * 16 + i);
+        row[q] = v < 0 ? pad_index(0, 0, 0) : v;         // (a row past the tile: computed, not stored)
+        for (int r = 0; r < 4; ++r) res[q][r] = padded(mt * 16 + 4 * kg + r);
+    }
+    const v4s zero = {0, 0, 0, 0};
+    const int own = tid < kT ? pad_index(tid % 10, (tid / 10) % 10, tid / 100) : 0;
+    for (int64_t tile = blockIdx.x; tile < n; tile += gridDim.x) {
+        if (tid < kT) sh.x0[own] = uint32_t(f2bf(nf)) | (uint32_t(f2bf(nw)) << 16);
+        __syncthreads();
+        if (tile + gridDim.x < n) fetch(tile + gridDim.x);
+        v4f acc[kFwdRows];
+        auto clear = [&]() {
+#pragma unroll
+            for (int q = 0; q < kFwdRows; ++q) acc[q] = v4f{0.f, 0.f, 0.f, 0.f};
+        };
+        auto store = [&](uint16_t *h, float bias) {
+#pragma unroll
+            for (int q = 0; q < kFwdRows; ++q)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float y = acc[q][r] + bias;
+                    y = y > 0.f ? y : 0.f;
+                    if (res[q][r] >= 0) h[res[q][r] * kC + i] = f2bf(y);
+                }
+        };
+        // (the taps of a (y, z) pair unrolled, the nine pairs not: the
+        // operands of a whole layer would not fit the registers)
+        auto layer = [&](auto product) {
+            clear();
+#pragma unroll 1
+            for (int pair = 0; pair < 9; ++pair) {
+                const int at = 12 * (pair % 3 - 1) + 144 * (pair / 3 - 1) - 1;
+#pragma unroll
+                for (int kx = 0; kx < 3; ++kx) product(3 * pair + kx, at + kx);
+            }
+        };
+        layer([&](int t, int off) {
+            v4s bh = zero, bl = zero;
+            if (kg == 0) {
+                bh = *reinterpret_cast<const v4s *>(&sh.w1[t * kFwdTap1 + i * 4]);
+                bl = *reinterpret_cast<const v4s *>(&sh.w1l[t * kFwdTap1 + i * 4]);
+            }
+#pragma unroll
+            for (int q = 0; q < kFwdRows; ++q) {
+                const uint32_t x = kg == 0 ? sh.x0[row[q] + off] : 0u;
+                const v4s a = {short(x & 0xFFFFu), short(x >> 16), 0, 0};
+                acc[q] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, bh, acc[q], 0, 0, 0);
+                acc[q] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, bl, acc[q], 0, 0, 0);
+            }
+        });
+        store(sh.h1, b1);
+        __syncthreads();
+        layer([&](int t, int off) {
+            const v4s b = *reinterpret_cast<const v4s *>(&sh.w2[t * kFwdTap2 + i * kC + 4 * kg]);
+#pragma unroll
+            for (int q = 0; q < kFwdRows; ++q) {
+                const v4s a = *reinterpret_cast<const v4s *>(&sh.h1[(row[q] + off) * kC + 4 * kg]);
+                acc[q] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[q], 0, 0, 0);
+            }
+        });
+        store(sh.h2, b2);
+        __syncthreads();
+        layer([&](int t, int off) {
+            const v4s b = i == 0 ? *reinterpret_cast<const v4s *>(&sh.w3[t * kC + 4 * kg]) : zero;
+#pragma unroll
+            for (int q = 0; q < kFwdRows; ++q) {
+                const v4s a = *reinterpret_cast<const v4s *>(&sh.h2[(row[q] + off) * kC + 4 * kg]);
+                acc[q] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[q], 0, 0, 0);
+            }
+        });
+        if (i == 0)
+#pragma unroll
+            for (int q = 0; q < kFwdRows; ++q)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (res[q][r] >= 0) out[tile * kT + (wave + q * kFwdWaves) * 16 + 4 * kg + r] = acc[q][r] + b3;
+        // the next tile's x0 is not read before the next barrier, and no wave
+        // writes h1 or h2 again before all have passed two
+    }
+}
+
+static int forward_tiles(const float *tiles, int64_t n, const float *params, float *out, hipStream_t st)
+{
+    int dev = 0, cus = 0;
+    DN_HIP(hipGetDevice(&dev));
+    DN_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    hipLaunchKernelGGL(k_net_tiles, dim3(unsigned(std::min<int64_t>(n, std::max(cus, 1)))), dim3(64 * kFwdWaves), 0, st,
+                       tiles, n, params, out);
+    DN_HIP(hipGetLastError());
     return DN_OK;
 }
 
@@ -1499,7 +1471,7 @@ int dn_net_forward(const float *tiles, int64_t n, const float *params, float *ou
         set_error("workspace of %zu bytes is short: %zu needed (dn_net_bytes)", workspace_bytes, dn_net_bytes(n, 0));
         return DN_E_CAPACITY;
     }
-    return forward_into(tiles, n, params, out, workspace, workspace_bytes, static_cast<hipStream_t>(stream));
+    return forward_tiles(tiles, n, params, out, static_cast<hipStream_t>(stream));
 }
 
 int dn_net_forward_static(const float *tiles, int64_t n, const float *params, float *out, void *stream)
@@ -1511,10 +1483,7 @@ int dn_net_forward_static(const float *tiles, int64_t n, const float *params, fl
         return DN_E_CAPACITY;
     }
     if (n == 0) return DN_OK;
-    void *ws = nullptr;
-    int rc = static_scratch(&ws);
-    if (rc) return rc;
-    return forward_into(tiles, n, params, out, ws, kNetStaticBytes, static_cast<hipStream_t>(stream));
+    return forward_tiles(tiles, n, params, out, static_cast<hipStream_t>(stream));
 }
 
 int dn_net_loss_grad(const float *tiles, int64_t n, const float *params, const float *targets, const float *mask,
