@@ -137,7 +137,6 @@ struct dn_volume {
     int32_t *order = nullptr;           // [max] processing order (Morton)
     int layout = 0;                     // chosen by the autotuner, see regularize.hip
     double *partials = nullptr;         // [max][2]
-    double *energy2 = nullptr;          // [2] device
 
     // caller-owned arena: everything above lives in it, then
     void *arena = nullptr;

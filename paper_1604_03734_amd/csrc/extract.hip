@@ -9,88 +9,160 @@ namespace dn {
 
 static inline unsigned grid1(int64_t n, int bs = 256) { return unsigned((n + bs - 1) / bs); }
 
-__device__ __forceinline__ int64_t nb_index(const int32_t *nb27, int hx, int hy, int hz)
-{
-    int dx = hx < 0 ? -1 : (hx > 7 ? 1 : 0);
-    int dy = hy < 0 ? -1 : (hy > 7 ? 1 : 0);
-    int dz = hz < 0 ? -1 : (hz > 7 ? 1 : 0);
-    int32_t id = nb27[(dz + 1) * 9 + (dy + 1) * 3 + (dx + 1)];
-    if (id < 0) return -1;
-    return int64_t(id) * kBlockVox + ((hx - 8 * dx) + 8 * (hy - 8 * dy) + 64 * (hz - 8 * dz));
-}
+// One workgroup of 256 threads takes a block, two voxels per thread (v and
+// v + 256).  u on the block and its +1 faces, edges and corner is staged in
+// LDS, and for each of its 81 rows along x which voxels are observed (bits 0
+// to 8) and which have u < 0 (bits 16 to 24): a voxel's neighbours are then
+// a fixed offset or a shift away, without a neighbour lookup and two loads
+// per corner.
+constexpr int kTile = 729;                 // index x + 9 y + 81 z, 0..8 each
+__device__ __forceinline__ int tile_at(int v) { return (v & 7) + 9 * ((v >> 3) & 7) + 81 * (v >> 6); }
 
-// Number of crossings of voxel g (0..3): axes a with both g and g + e_a
-// observed and u(g) < 0 differing from u(g + e_a) < 0.
-__device__ __forceinline__ int crossing_bits(const int32_t *nb27, const float *u, const uint8_t *emask,
-                                             int64_t gi, int lx, int ly, int lz, float u0[4])
+struct Tile {
+    float u[kTile];
+    uint32_t row[81];                      // index y + 9 z
+    uint8_t x8[81];                        // the row's voxel at x = 8: observed, u < 0
+};
+
+__device__ __forceinline__ void load_tile(Tile &sh, int64_t b, const int32_t *__restrict__ nbr,
+                                          const uint32_t *__restrict__ em4, const float *__restrict__ u, int t)
 {
-    uint8_t m = emask[gi];
-    int bits = 0;
-    u0[0] = u[gi];
-    if (!(m & 1)) return 0;
-    const int off[3][3] = {{1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
-    for (int a = 0; a < 3; ++a) {
-        if (!(m & (2 << a))) continue;
-        int64_t j = nb_index(nb27, lx + off[a][0], ly + off[a][1], lz + off[a][2]);
-        float u1 = u[j];
-        u0[1 + a] = u1;
-        if ((u0[0] < 0.0f) != (u1 < 0.0f)) bits |= 1 << a;
+    const int i = t & 63, p = i & 7, q = i >> 3;
+    // the bits of a wave whose lanes are x + 8 k: row k of them
+    auto rows = [&](uint32_t c, int at) {
+        const uint64_t o = __ballot(c & 1u), n = __ballot(c & 2u);
+        if (i < 8) sh.row[at] = uint32_t(o >> (8 * i)) & 255u | (uint32_t(n >> (8 * i)) & 255u) << 16;
+    };
+    auto get = [&](int at, int64_t block, int v) {
+        const float x = u[block * kBlockVox + v];
+        sh.u[at] = x;
+        return ((em4[block * 64 + (v & 63)] >> (4 * (v >> 6))) & 1u) | (x < 0.0f ? 2u : 0u);
+    };
+    rows(get(tile_at(t), b, t), i + 9 * (t >> 6));
+    rows(get(tile_at(t + 256), b, t + 256), i + 9 * (t >> 6) + 36);
+    // by wave: the +x, +y and +z faces; then the edges along z, y and x (8
+    // lanes each) and the corner
+    int x, y, z;
+    if (t < 64) { x = 8; y = p; z = q; }
+    else if (t < 128) { x = p; y = 8; z = q; }
+    else if (t < 192) { x = p; y = q; z = 8; }
+    else if (i < 8) { x = 8; y = 8; z = p; }
+    else if (i < 16) { x = 8; y = p; z = 8; }
+    else if (i < 24) { x = p; y = 8; z = 8; }
+    else { x = 8; y = 8; z = 8; }
+    uint32_t c = 0;
+    if (t < 217) {
+        const int at = x + 9 * y + 81 * z;
+        const int32_t id = nbr[b * kNbr + 13 + (x >> 3) + 3 * (y >> 3) + 9 * (z >> 3)];
+        if (id >= 0) c = get(at, id, (x & 7) + 8 * (y & 7) + 64 * (z & 7));
+        else sh.u[at] = 0.0f;
+        if (x == 8) sh.x8[y + 9 * z] = uint8_t(c);
     }
-    return bits;
+    if (t >= 64 && t < 128) rows(c, 8 + 9 * i);
+    if (t >= 128 && t < 192) rows(c, i + 72);
+    if (t >= 192) {
+        const uint64_t o = __ballot(c & 1u), n = __ballot(c & 2u);
+        if (i == 0) sh.row[80] = uint32_t(o >> 16) & 255u | (uint32_t(n >> 16) & 255u) << 16;
+    }
+    __syncthreads();
+    if (t < 81) sh.row[t] |= (sh.x8[t] & 1u) << 8 | (sh.x8[t] >> 1) << 24;
+    __syncthreads();
 }
 
-__global__ __launch_bounds__(512) void k_surface_count(int64_t nb, const int32_t *__restrict__ nbr,
-                                                       const uint8_t *__restrict__ emask,
+// Observed (bits 0, 1) and negative (16, 17) of voxel v + (0 or 1, dy, dz).
+__device__ __forceinline__ uint32_t pair_at(const Tile &sh, int v, int dy, int dz)
+{
+    return sh.row[((v >> 3) & 7) + dy + 9 * ((v >> 6) + dz)] >> (v & 7);
+}
+
+// Exclusive prefix, in voxel order, of the counts (below 16) of the
+// workgroup's two voxels per thread, and their total.
+__device__ __forceinline__ int prefix_counts(int c0, int c1, int &p0, int &p1, int *wave_sum /* [8] */)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint64_t below = (uint64_t(1) << lane) - 1;
+    auto prefix = [&](int c, int &sum) {
+        int p = 0;
+        sum = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint64_t m = __ballot((c >> k) & 1);
+            p += __popcll(m & below) << k;
+            sum += __popcll(m) << k;
+        }
+        return p;
+    };
+    int s0, s1;
+    p0 = prefix(c0, s0);
+    p1 = prefix(c1, s1);
+    if (lane == 0) {
+        wave_sum[wave] = s0;
+        wave_sum[4 + wave] = s1;
+    }
+    __syncthreads();
+    int total = 0;
+    for (int k = 0; k < 8; ++k) {
+        if (k == wave) p0 += total;
+        if (k == 4 + wave) p1 += total;
+        total += wave_sum[k];
+    }
+    return total;
+}
+
+// Zero crossings of voxel v: axes a with both v and v + e_a observed and
+// u(v) < 0 differing from u(v + e_a) < 0.
+__device__ __forceinline__ int crossing_bits(const Tile &sh, int v)
+{
+    const uint32_t c = pair_at(sh, v, 0, 0), y = pair_at(sh, v, 1, 0), z = pair_at(sh, v, 0, 1);
+    // bit 0: both observed and different signs
+    const uint32_t ox = c & (c >> 1) & ((c >> 16) ^ (c >> 17)), oy = c & y & ((c ^ y) >> 16), oz = c & z & ((c ^ z) >> 16);
+    return int((ox & 1u) | (oy & 1u) << 1 | (oz & 1u) << 2);
+}
+
+__global__ __launch_bounds__(256) void k_surface_count(const int32_t *__restrict__ nbr, const uint32_t *__restrict__ em4,
                                                        const float *__restrict__ u, int64_t *__restrict__ counts)
 {
-    __shared__ int wsum[8];
+    __shared__ Tile sh;
+    __shared__ int wave_sum[8];
     const int64_t b = blockIdx.x;
     const int t = threadIdx.x;
-    float uu[4];
-    int bits = crossing_bits(nbr + b * kNbr, u, emask, b * kBlockVox + t, t & 7, (t >> 3) & 7, t >> 6, uu);
-    int c = __popc(bits);
-    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
-    if ((t & 63) == 0) wsum[t >> 6] = c;
-    __syncthreads();
-    if (t == 0) {
-        int s = 0;
-        for (int i = 0; i < 8; ++i) s += wsum[i];
-        counts[b] = s;
-    }
+    load_tile(sh, b, nbr, em4, u, t);
+    int p0, p1;
+    const int n = prefix_counts(__popc(crossing_bits(sh, t)), __popc(crossing_bits(sh, t + 256)), p0, p1, wave_sum);
+    if (t == 0) counts[b] = n;
 }
 
-__global__ __launch_bounds__(512) void k_surface_write(int64_t nb, const int32_t *__restrict__ coords,
-                                                       const int32_t *__restrict__ nbr,
-                                                       const uint8_t *__restrict__ emask,
-                                                       const float *__restrict__ u,
-                                                       const int64_t *__restrict__ offsets, double s,
-                                                       float *__restrict__ out)
+__global__ __launch_bounds__(256) void k_surface_write(const int32_t *__restrict__ coords,
+                                                       const int32_t *__restrict__ nbr, const uint32_t *__restrict__ em4,
+                                                       const float *__restrict__ u, const int64_t *__restrict__ offsets,
+                                                       double s, float *__restrict__ out)
 {
-    __shared__ int scan[512];
-    const int64_t b = blockIdx.x;
-    const int t = threadIdx.x, lx = t & 7, ly = (t >> 3) & 7, lz = t >> 6;
-    float uu[4];
-    int bits = crossing_bits(nbr + b * kNbr, u, emask, b * kBlockVox + t, lx, ly, lz, uu);
-    // exclusive scan of the per-voxel counts in voxel order (Hillis-Steele)
-    scan[t] = __popc(bits);
-    __syncthreads();
-    for (int d = 1; d < 512; d <<= 1) {
-        int v = t >= d ? scan[t - d] : 0;
-        __syncthreads();
-        scan[t] += v;
-        __syncthreads();
-    }
-    int64_t pos = offsets[b] + scan[t] - __popc(bits);
-    const int l[3] = {lx, ly, lz};
-    for (int a = 0; a < 3; ++a) {
-        if (!(bits & (1 << a))) continue;
-        double u0 = uu[0], u1 = uu[1 + a];
-        double tt = u0 / (u0 - u1);
-        for (int i = 0; i < 3; ++i) {
-            double c = (double(8 * coords[4 * b + i] + l[i]) + 0.5) * s;
-            out[3 * pos + i] = float(c + (i == a ? tt * s : 0.0));
+    __shared__ Tile sh;
+    __shared__ int wave_sum[8];
+    const int64_t b = blockIdx.x, first = offsets[b];
+    if (offsets[b + 1] == first) return;
+    const int t = threadIdx.x;
+    load_tile(sh, b, nbr, em4, u, t);
+    const int bits[2] = {crossing_bits(sh, t), crossing_bits(sh, t + 256)};
+    int p[2];
+    prefix_counts(__popc(bits[0]), __popc(bits[1]), p[0], p[1], wave_sum);
+    const int4 c4 = reinterpret_cast<const int4 *>(coords)[b];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int v = t + 256 * j, at = tile_at(v);
+        const int step[3] = {1, 9, 81};
+        int64_t pos = first + p[j];
+        const double centre[3] = {(double(8 * c4.x + (v & 7)) + 0.5) * s, (double(8 * c4.y + ((v >> 3) & 7)) + 0.5) * s,
+                                  (double(8 * c4.z + (v >> 6)) + 0.5) * s};
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            if (!(bits[j] & (1 << a))) continue;
+            const double u0 = sh.u[at], u1 = sh.u[at + step[a]];
+            const double tt = u0 / (u0 - u1);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) out[3 * pos + i] = float(centre[i] + (i == a ? tt * s : 0.0));
+            ++pos;
         }
-        ++pos;
     }
 }
 
@@ -109,185 +181,253 @@ __global__ __launch_bounds__(512) void k_surface_write(int64_t nb, const int32_t
 // sum(positive offsets) - n_pos * sum(negative offsets).  Double precision
 // throughout; the output rounds to float.  Order: pool id, voxel,
 // tetrahedron, triangle.
-__constant__ int kTetAxes[6][2] = {{0, 1}, {0, 2}, {1, 0}, {1, 2}, {2, 0}, {2, 1}};
+//
+// A cube's signs decide its triangles, so a block first lists them (cube,
+// tetrahedron, which of two) in order in LDS, then every thread computes
+// triangles of the list: all lanes work, where a thread per voxel left seven
+// of eight idle beside the few on the surface, and no array is indexed by a
+// variable outside LDS.  5777 blocks, 1.28 million triangles: area 190 -> 40
+// us, writing 222 -> 39 (the triangles alone are 46 MB), counting 55 -> 11.
 
-struct Cube {
-    double u[8];
-};
-
-__device__ __forceinline__ bool cube_load(const int32_t *nb27, const float *u, const uint8_t *emask, int lx, int ly,
-                                          int lz, Cube &c)
-{
-    for (int k = 0; k < 8; ++k) {
-        const int64_t j = nb_index(nb27, lx + (k & 1), ly + ((k >> 1) & 1), lz + ((k >> 2) & 1));
-        if (j < 0 || !(emask[j] & 1)) return false;
-        c.u[k] = double(u[j]);
+// The tetrahedra's corners (a nibble each, first to last), by tables that the
+// compiler fills.
+struct MeshTables {
+    uint16_t corners[6];
+    uint8_t count[256];        // triangles of a cube by its corners' signs
+    uint32_t edges[16][2];     // by the tetrahedron's signs and which triangle: 3 edges (two nibbles each)
+    constexpr MeshTables() : corners{}, count{}, edges{}
+    {
+        const int axes[6][2] = {{0, 1}, {0, 2}, {1, 0}, {1, 2}, {2, 0}, {2, 1}};
+        for (int t = 0; t < 6; ++t) {
+            const int k1 = 1 << axes[t][0], k2 = k1 | (1 << axes[t][1]);
+            corners[t] = uint16_t(k1 << 4 | k2 << 8 | 7 << 12);
+        }
+        for (int m = 0; m < 256; ++m) {
+            int n = 0;
+            for (int t = 0; t < 6; ++t) {
+                int neg = 0;
+                for (int q = 0; q < 4; ++q) neg += (m >> ((corners[t] >> (4 * q)) & 7)) & 1;
+                n += neg == 2 ? 2 : (neg == 1 || neg == 3 ? 1 : 0);
+            }
+            count[m] = uint8_t(n);
+        }
+        for (int m = 0; m < 16; ++m) {
+            int ng[4] = {}, ps[4] = {}, nn = 0, np = 0;
+            for (int q = 0; q < 4; ++q) {
+                if ((m >> q) & 1) ng[nn++] = q;
+                else ps[np++] = q;
+            }
+            auto edge = [](int a, int b) { return uint32_t(a | b << 4); };
+            if (nn == 1) edges[m][0] = edge(ng[0], ps[0]) | edge(ng[0], ps[1]) << 8 | edge(ng[0], ps[2]) << 16;
+            if (nn == 3) edges[m][0] = edge(ps[0], ng[0]) | edge(ps[0], ng[1]) << 8 | edge(ps[0], ng[2]) << 16;
+            if (nn == 2) {
+                edges[m][0] = edge(ng[0], ps[0]) | edge(ng[0], ps[1]) << 8 | edge(ng[1], ps[1]) << 16;
+                edges[m][1] = edge(ng[0], ps[0]) | edge(ng[1], ps[1]) << 8 | edge(ng[1], ps[0]) << 16;
+            }
+        }
     }
-    return true;
+};
+static __constant__ MeshTables kMesh{};
+
+// The signs of the cube at voxel v (bit k: u < 0 at corner k); 0 (no
+// triangle) unless all eight corners are observed.
+__device__ __forceinline__ uint32_t cube_signs(const Tile &sh, int v)
+{
+    const uint32_t a = pair_at(sh, v, 0, 0), b = pair_at(sh, v, 1, 0), c = pair_at(sh, v, 0, 1), d = pair_at(sh, v, 1, 1);
+    if ((a & b & c & d & 3u) != 3u) return 0u;
+    return ((a >> 16) & 3u) | ((b >> 16) & 3u) << 2 | ((c >> 16) & 3u) << 4 | ((d >> 16) & 3u) << 6;
 }
 
-__device__ __forceinline__ int cube_count(const Cube &c)
+__device__ __forceinline__ int tet_signs(uint32_t corners, uint32_t neg)
 {
-    int n = 0;
-    for (int tt = 0; tt < 6; ++tt) {
-        const int a0 = kTetAxes[tt][0], a1 = kTetAxes[tt][1];
-        const int kk[4] = {0, 1 << a0, (1 << a0) | (1 << a1), 7};
-        int nneg = 0;
-        for (int q = 0; q < 4; ++q) nneg += c.u[kk[q]] < 0.0;
-        n += (nneg == 1 || nneg == 3) ? 1 : (nneg == 2 ? 2 : 0);
+    return int((neg & 1u) | ((neg >> ((corners >> 4) & 7u)) & 1u) << 1 | ((neg >> ((corners >> 8) & 7u)) & 1u) << 2 |
+               ((neg >> 7) & 1u) << 3);
+}
+
+struct MeshShared {
+    Tile tile;
+    uint16_t list[kBlockVox * 12];         // voxel | tetrahedron << 9 | triangle << 12
+    uint32_t edges[16][2];
+    uint16_t corners[6];
+    uint8_t count[256];
+    int wave_sum[8];
+};
+
+// The block's triangles, listed in order; returns their number.
+__device__ __forceinline__ int list_triangles(MeshShared &sh, int64_t b, const int32_t *__restrict__ nbr,
+                                              const uint32_t *__restrict__ em4, const float *__restrict__ u, int t)
+{
+    sh.count[t] = kMesh.count[t];
+    if (t < 32) sh.edges[t >> 1][t & 1] = kMesh.edges[t >> 1][t & 1];
+    if (t < 6) sh.corners[t] = kMesh.corners[t];
+    load_tile(sh.tile, b, nbr, em4, u, t);
+    const uint32_t neg[2] = {cube_signs(sh.tile, t), cube_signs(sh.tile, t + 256)};
+    int p[2];
+    const int n = prefix_counts(sh.count[neg[0]], sh.count[neg[1]], p[0], p[1], sh.wave_sum);
+    for (int j = 0; j < 2; ++j) {
+        if (sh.count[neg[j]] == 0) continue;
+        int at = p[j];
+        for (int tt = 0; tt < 6; ++tt) {
+            const int k = __popc(tet_signs(sh.corners[tt], neg[j]));
+            if (k == 0 || k == 4) continue;
+            const int e = (t + 256 * j) | tt << 9;
+            sh.list[at++] = uint16_t(e);
+            if (k == 2) sh.list[at++] = uint16_t(e | 1 << 12);
+        }
     }
+    __syncthreads();
     return n;
 }
 
-// Visit the cube's triangles in order: fn(A, B, C) with the oriented
-// vertices (world metres).
+// Triangle e of the list: fn(A, B, C, area) with the oriented vertices.
 template <class F>
-__device__ __forceinline__ void cube_triangles(const Cube &c, const int32_t *c4, int lx, int ly, int lz, double s,
-                                               F fn)
+__device__ __forceinline__ void triangle(const MeshShared &sh, int e, const int4 c4, double s, F fn)
 {
-    const int l[3] = {lx, ly, lz};
-    auto pos = [&](int k, int comp) {
-        return (double(8 * c4[comp] + l[comp] + ((k >> comp) & 1)) + 0.5) * s;
-    };
-    auto edge = [&](int ki, int kj, double out[3]) {
+    const int entry = sh.list[e], v = entry & 511, at = tile_at(v);
+    const uint32_t corners = sh.corners[(entry >> 9) & 7];
+    auto corner_at = [&](int k) { return at + (k & 1) + 9 * ((k >> 1) & 1) + 81 * (k >> 2); };
+    int r[3] = {0, 0, 0};
+    const int m = tet_signs(corners, cube_signs(sh.tile, v));
+    const int nneg = __popc(m);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int comp = 0; comp < 3; ++comp)
+            r[comp] += ((m >> q) & 1 ? nneg - 4 : nneg) * int((corners >> (4 * q + comp)) & 1u);
+    const uint32_t edges = sh.edges[m][entry >> 12];
+    const int base[3] = {8 * c4.x + (v & 7), 8 * c4.y + ((v >> 3) & 7), 8 * c4.z + (v >> 6)};
+    double P[3][3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        int ki = int(corners >> (4 * ((edges >> (8 * k)) & 15u))) & 7;
+        int kj = int(corners >> (4 * ((edges >> (8 * k + 4)) & 15u))) & 7;
         if (ki > kj) { const int x = ki; ki = kj; kj = x; }
-        const double t = c.u[ki] / (c.u[ki] - c.u[kj]);
+        const double ui = sh.tile.u[corner_at(ki)], uj = sh.tile.u[corner_at(kj)];
+        const double tt = ui / (ui - uj);
+#pragma unroll
         for (int comp = 0; comp < 3; ++comp) {
-            const double pi = pos(ki, comp), pj = pos(kj, comp);
-            out[comp] = pi + t * (pj - pi);
-        }
-    };
-    for (int tt = 0; tt < 6; ++tt) {
-        const int a0 = kTetAxes[tt][0], a1 = kTetAxes[tt][1];
-        const int kk[4] = {0, 1 << a0, (1 << a0) | (1 << a1), 7};
-        int neg[4], nneg = 0;
-        for (int q = 0; q < 4; ++q) { neg[q] = c.u[kk[q]] < 0.0; nneg += neg[q]; }
-        if (nneg == 0 || nneg == 4) continue;
-        double r[3] = {0.0, 0.0, 0.0};
-        for (int q = 0; q < 4; ++q)
-            for (int comp = 0; comp < 3; ++comp) {
-                const double oc = double((kk[q] >> comp) & 1);
-                r[comp] += neg[q] ? -double(4 - nneg) * oc : double(nneg) * oc;
-            }
-        auto tri = [&](int e0a, int e0b, int e1a, int e1b, int e2a, int e2b) {
-            double A[3], B[3], C[3];
-            edge(kk[e0a], kk[e0b], A);
-            edge(kk[e1a], kk[e1b], B);
-            edge(kk[e2a], kk[e2b], C);
-            const double ab[3] = {B[0] - A[0], B[1] - A[1], B[2] - A[2]};
-            const double ac[3] = {C[0] - A[0], C[1] - A[1], C[2] - A[2]};
-            const double nx = ab[1] * ac[2] - ab[2] * ac[1];
-            const double ny = ab[2] * ac[0] - ab[0] * ac[2];
-            const double nz = ab[0] * ac[1] - ab[1] * ac[0];
-            const bool flip = (nx * r[0] + ny * r[1]) + nz * r[2] < 0.0;
-            const double area = 0.5 * sqrt((nx * nx + ny * ny) + nz * nz);
-            if (flip) fn(A, C, B, area);
-            else fn(A, B, C, area);
-        };
-        if (nneg == 1 || nneg == 3) {
-            int odd = 0, j[3], m = 0;
-            for (int q = 0; q < 4; ++q)
-                if (neg[q] == (nneg == 1)) odd = q;
-            for (int q = 0; q < 4; ++q)
-                if (q != odd) j[m++] = q;
-            tri(odd, j[0], odd, j[1], odd, j[2]);
-        } else {
-            int ng[2], ps[2], mn = 0, mp = 0;
-            for (int q = 0; q < 4; ++q) {
-                if (neg[q]) ng[mn++] = q;
-                else ps[mp++] = q;
-            }
-            tri(ng[0], ps[0], ng[0], ps[1], ng[1], ps[1]);
-            tri(ng[0], ps[0], ng[1], ps[1], ng[1], ps[0]);
+            const double pi = (double(base[comp] + ((ki >> comp) & 1)) + 0.5) * s;
+            const double pj = (double(base[comp] + ((kj >> comp) & 1)) + 0.5) * s;
+            P[k][comp] = pi + tt * (pj - pi);
         }
     }
+    const double ab[3] = {P[1][0] - P[0][0], P[1][1] - P[0][1], P[1][2] - P[0][2]};
+    const double ac[3] = {P[2][0] - P[0][0], P[2][1] - P[0][1], P[2][2] - P[0][2]};
+    const double nx = ab[1] * ac[2] - ab[2] * ac[1];
+    const double ny = ab[2] * ac[0] - ab[0] * ac[2];
+    const double nz = ab[0] * ac[1] - ab[1] * ac[0];
+    const bool flip = (nx * double(r[0]) + ny * double(r[1])) + nz * double(r[2]) < 0.0;
+    fn(P[0], flip ? P[2] : P[1], flip ? P[1] : P[2], 0.5 * sqrt((nx * nx + ny * ny) + nz * nz));
 }
 
-__global__ __launch_bounds__(512) void k_mesh_count(int64_t nb, const int32_t *__restrict__ nbr,
-                                                    const uint8_t *__restrict__ emask, const float *__restrict__ u,
-                                                    int64_t *__restrict__ counts)
+__global__ __launch_bounds__(256) void k_mesh_count(const int32_t *__restrict__ nbr, const uint32_t *__restrict__ em4,
+                                                    const float *__restrict__ u, int64_t *__restrict__ counts)
 {
-    __shared__ int wsum[8];
+    __shared__ Tile sh;
+    __shared__ uint8_t count[256];
+    __shared__ int wave_sum[8];
     const int64_t b = blockIdx.x;
     const int t = threadIdx.x;
-    Cube c;
-    int n = cube_load(nbr + b * kNbr, u, emask, t & 7, (t >> 3) & 7, t >> 6, c) ? cube_count(c) : 0;
-    for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
-    if ((t & 63) == 0) wsum[t >> 6] = n;
-    __syncthreads();
-    if (t == 0) {
-        int sum = 0;
-        for (int i = 0; i < 8; ++i) sum += wsum[i];
-        counts[b] = sum;
-    }
+    count[t] = kMesh.count[t];
+    load_tile(sh, b, nbr, em4, u, t);
+    int p0, p1;
+    const int n = prefix_counts(count[cube_signs(sh, t)], count[cube_signs(sh, t + 256)], p0, p1, wave_sum);
+    if (t == 0) counts[b] = n;
 }
 
-__global__ __launch_bounds__(512) void k_mesh_write(int64_t nb, const int32_t *__restrict__ coords,
-                                                    const int32_t *__restrict__ nbr,
-                                                    const uint8_t *__restrict__ emask, const float *__restrict__ u,
+__global__ __launch_bounds__(256) void k_mesh_write(const int32_t *__restrict__ coords, const int32_t *__restrict__ nbr,
+                                                    const uint32_t *__restrict__ em4, const float *__restrict__ u,
                                                     const int64_t *__restrict__ offsets, double s,
                                                     float *__restrict__ out)
 {
-    __shared__ int scan[512];
-    const int64_t b = blockIdx.x;
-    const int t = threadIdx.x, lx = t & 7, ly = (t >> 3) & 7, lz = t >> 6;
-    Cube c;
-    const bool ok = cube_load(nbr + b * kNbr, u, emask, lx, ly, lz, c);
-    const int n = ok ? cube_count(c) : 0;
-    scan[t] = n;
-    __syncthreads();
-    for (int d = 1; d < 512; d <<= 1) {
-        const int v = t >= d ? scan[t - d] : 0;
-        __syncthreads();
-        scan[t] += v;
-        __syncthreads();
-    }
-    if (!ok || n == 0) return;
-    int64_t pos = offsets[b] + scan[t] - n;
-    cube_triangles(c, coords + 4 * b, lx, ly, lz, s, [&](const double *A, const double *B, const double *C, double) {
-        float *o = out + 9 * pos;
-        for (int i = 0; i < 3; ++i) {
-            o[i] = float(A[i]);
-            o[3 + i] = float(B[i]);
-            o[6 + i] = float(C[i]);
-        }
-        ++pos;
-    });
+    __shared__ MeshShared sh;
+    const int64_t b = blockIdx.x, first = offsets[b];
+    if (offsets[b + 1] == first) return;
+    const int n = list_triangles(sh, b, nbr, em4, u, threadIdx.x);
+    const int4 c4 = reinterpret_cast<const int4 *>(coords)[b];
+    for (int e = threadIdx.x; e < n; e += 256)
+        triangle(sh, e, c4, s, [&](const double *A, const double *B, const double *C, double) {
+            float *o = out + 9 * (first + e);
+            for (int i = 0; i < 3; ++i) {
+                o[i] = float(A[i]);
+                o[3 + i] = float(B[i]);
+                o[6 + i] = float(C[i]);
+            }
+        });
 }
 
-// Per-block (area, triangle count) pairs, float64, fixed order: lanes by
-// xor butterflies, then the 8 wave sums in wave order.
-__global__ __launch_bounds__(512) void k_mesh_area(int64_t nb, const int32_t *__restrict__ coords,
-                                                   const int32_t *__restrict__ nbr,
-                                                   const uint8_t *__restrict__ emask, const float *__restrict__ u,
+// Per-block (area, triangle count) pairs, float64, fixed order: each thread
+// its triangles in list order, lanes by xor butterflies, waves in order.
+__global__ __launch_bounds__(256) void k_mesh_area(const int32_t *__restrict__ coords, const int32_t *__restrict__ nbr,
+                                                   const uint32_t *__restrict__ em4, const float *__restrict__ u,
                                                    double s, double *__restrict__ partials)
 {
-    __shared__ double wa[8], wn[8];
+    __shared__ MeshShared sh;
+    __shared__ double wa[4];
     const int64_t b = blockIdx.x;
-    const int t = threadIdx.x, lx = t & 7, ly = (t >> 3) & 7, lz = t >> 6;
-    Cube c;
-    double a = 0.0, n = 0.0;
-    if (cube_load(nbr + b * kNbr, u, emask, lx, ly, lz, c))
-        cube_triangles(c, coords + 4 * b, lx, ly, lz, s, [&](const double *, const double *, const double *,
-                                                             double ar) {
-            a += ar;
-            n += 1.0;
-        });
-    for (int o = 32; o > 0; o >>= 1) {
-        a += __shfl_xor(a, o, 64);
-        n += __shfl_xor(n, o, 64);
-    }
-    if ((t & 63) == 0) { wa[t >> 6] = a; wn[t >> 6] = n; }
+    const int t = threadIdx.x;
+    const int n = list_triangles(sh, b, nbr, em4, u, t);
+    const int4 c4 = reinterpret_cast<const int4 *>(coords)[b];
+    double a = 0.0;
+    for (int e = t; e < n; e += 256)
+        triangle(sh, e, c4, s, [&](const double *, const double *, const double *, double ar) { a += ar; });
+    for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
+    if ((t & 63) == 0) wa[t >> 6] = a;
     __syncthreads();
     if (t == 0) {
-        double sa = 0.0, sn = 0.0;
-        for (int i = 0; i < 8; ++i) { sa += wa[i]; sn += wn[i]; }
-        partials[2 * b] = sa;
-        partials[2 * b + 1] = sn;
+        partials[2 * b] = ((wa[0] + wa[1]) + wa[2]) + wa[3];
+        partials[2 * b + 1] = double(n);
     }
 }
 
 __global__ void k_fill_zero_i64(int64_t *a) { *a = 0; }
+
+// Offsets of nb counts and their total (ofs[nb], also reported), by one
+// workgroup: quicker than a device-wide scan's launches up to kScanBlocks.
+constexpr int64_t kScanBlocks = 32768;
+__global__ __launch_bounds__(1024) void k_scan_counts(const int64_t *__restrict__ cnt, int nb, int64_t *__restrict__ ofs,
+                                                      int64_t *__restrict__ total)
+{
+    __shared__ int64_t wave_sum[16];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    int64_t carry = 0;
+    int64_t ahead[4];
+    auto fetch = [&](int i0) {
+        for (int k = 0; k < 4; ++k) {
+            const int i = i0 + 4 * t + k;
+            ahead[k] = i < nb ? cnt[i] : 0;
+        }
+    };
+    fetch(0);
+    for (int i0 = 0; i0 < nb; i0 += 4096) {
+        int64_t c[4];
+        for (int k = 0; k < 4; ++k) c[k] = ahead[k];
+        fetch(i0 + 4096);
+        const int64_t mine = (c[0] + c[1]) + (c[2] + c[3]);
+        int64_t inc = mine;
+        for (int d = 1; d < 64; d <<= 1) {
+            const int64_t other = __shfl_up(inc, d, 64);
+            if (lane >= d) inc += other;
+        }
+        if (lane == 63) wave_sum[wave] = inc;
+        __syncthreads();
+        int64_t at = carry + inc - mine;
+        for (int k = 0; k < 16; ++k) {
+            if (k < wave) at += wave_sum[k];
+            carry += wave_sum[k];
+        }
+        for (int k = 0; k < 4; ++k) {
+            const int i = i0 + 4 * t + k;
+            if (i < nb) ofs[i] = at;
+            at += c[k];
+        }
+        __syncthreads();
+    }
+    if (t == 0) {
+        ofs[nb] = carry;
+        *total = carry;
+    }
+}
 
 __global__ void k_copy_coords(const int32_t *__restrict__ c4, int64_t nb, int32_t *__restrict__ out)
 {
@@ -338,8 +478,15 @@ static int count_and_scan(dn_volume *v, CountK count_kernel, ScanScratch &x, int
     x = carve_scan(bump, nb);
     if (!bump.fits()) { set_error("scratch too small for the extraction"); return DN_E_CAPACITY; }
     if (nb > 0) {
-        hipLaunchKernelGGL(count_kernel, dim3(unsigned(nb)), dim3(512), 0, st, nb, v->nbr, v->emask, v->u, x.cnt);
+        hipLaunchKernelGGL(count_kernel, dim3(unsigned(nb)), dim3(256), 0, st, v->nbr, v->em4, v->u, x.cnt);
         DN_HIP(hipGetLastError());
+    }
+    if (nb > 0 && nb <= kScanBlocks) {
+        hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, st, x.cnt, int(nb), x.ofs, report(v));
+        DN_HIP(hipGetLastError());
+        const int rc = fetch_report(v, 1);
+        *total = v->host_stage[0];
+        return rc;
     }
     hipLaunchKernelGGL(k_fill_zero_i64, dim3(1), dim3(1), 0, st, x.cnt + nb);
     DN_HIP(hipGetLastError());
@@ -384,8 +531,8 @@ extern "C" int dn_extract(dn_volume *v, int32_t what, void *out, size_t out_byte
         *n_out = items;
         if (items == 0) return DN_OK;
         if (!out || out_bytes < need) { set_error("output too small: need %zu bytes", need); return DN_E_CAPACITY; }
-        hipLaunchKernelGGL(k_surface_write, dim3(unsigned(nb)), dim3(512), 0, st, nb, v->coords, v->nbr, v->emask,
-                           v->u, x.ofs, v->prm.voxel_size, static_cast<float *>(out));
+        hipLaunchKernelGGL(k_surface_write, dim3(unsigned(nb)), dim3(256), 0, st, v->coords, v->nbr, v->em4, v->u,
+                           x.ofs, v->prm.voxel_size, static_cast<float *>(out));
         DN_HIP(hipGetLastError());
         DN_HIP(hipStreamSynchronize(st));
         return DN_OK;
@@ -398,8 +545,8 @@ extern "C" int dn_extract(dn_volume *v, int32_t what, void *out, size_t out_byte
         *n_out = items;
         if (items == 0) return DN_OK;
         if (!out || out_bytes < need) { set_error("output too small: need %zu bytes", need); return DN_E_CAPACITY; }
-        hipLaunchKernelGGL(k_mesh_write, dim3(unsigned(nb)), dim3(512), 0, st, nb, v->coords, v->nbr, v->emask,
-                           v->u, x.ofs, v->prm.voxel_size, static_cast<float *>(out));
+        hipLaunchKernelGGL(k_mesh_write, dim3(unsigned(nb)), dim3(256), 0, st, v->coords, v->nbr, v->em4, v->u,
+                           x.ofs, v->prm.voxel_size, static_cast<float *>(out));
         DN_HIP(hipGetLastError());
         DN_HIP(hipStreamSynchronize(st));
         return DN_OK;
@@ -449,8 +596,8 @@ extern "C" int dn_mesh_area(dn_volume *v, double *area, int64_t *n_tris)
     if ((rc = build_masks(v))) return rc;
     double ed[2] = {0.0, 0.0};
     if (v->nb > 0) {
-        hipLaunchKernelGGL(k_mesh_area, dim3(unsigned(v->nb)), dim3(512), 0, v->stream, v->nb, v->coords, v->nbr,
-                           v->emask, v->u, v->prm.voxel_size, v->partials);
+        hipLaunchKernelGGL(k_mesh_area, dim3(unsigned(v->nb)), dim3(256), 0, v->stream, v->coords, v->nbr, v->em4,
+                           v->u, v->prm.voxel_size, v->partials);
         DN_HIP(hipGetLastError());
         if ((rc = reduce_pairs(v, v->nb))) return rc;
         if ((rc = read_energy(v, ed))) return rc;

@@ -273,6 +273,34 @@ __global__ __launch_bounds__(256) void k_energy_reduce(int64_t n, const double *
     if (t == 0) { out[2 * blockIdx.x] = se[0]; out[2 * blockIdx.x + 1] = sd[0]; }
 }
 
+// The last step: n <= kFinalPairs pairs by one workgroup, in a fixed order
+// (each thread every 1024th pair, then a tree), to the call's report.
+constexpr int64_t kFinalPairs = 16384;
+__global__ __launch_bounds__(1024) void k_energy_final(int n, const double *__restrict__ in, double *__restrict__ out)
+{
+    __shared__ double se[16], sd[16];
+    const int t = threadIdx.x;
+    double e = 0.0, d = 0.0;
+    const double2 *pairs = reinterpret_cast<const double2 *>(in);
+    int k = t;
+    for (; k + 3 * 1024 < n; k += 4 * 1024) {
+        const double2 a = pairs[k], b = pairs[k + 1024], c = pairs[k + 2048], f = pairs[k + 3072];
+        e += (a.x + b.x) + (c.x + f.x);
+        d += (a.y + b.y) + (c.y + f.y);
+    }
+    for (; k < n; k += 1024) { e += pairs[k].x; d += pairs[k].y; }
+    e = wave_sum(e);
+    d = wave_sum(d);
+    if ((t & 63) == 0) { se[t >> 6] = e; sd[t >> 6] = d; }
+    __syncthreads();
+    if (t == 0) {
+        e = d = 0.0;
+        for (int w = 0; w < 16; ++w) { e += se[w]; d += sd[w]; }
+        out[0] = e;
+        out[1] = d;
+    }
+}
+
 // ------------------------------------------------------- helpers
 template <class T> __global__ void k_fill(T *__restrict__ a, int64_t n, T v)
 {
@@ -353,7 +381,8 @@ static int energy_launch(dn_volume *v, double lambda, int l1, const typename S::
     hipStream_t st = v->stream;
     const int64_t ps = v->cap_blocks * kBlockVox;
     if (v->nb == 0) {
-        hipLaunchKernelGGL(k_fill<double>, dim3(1), dim3(256), 0, st, v->energy2, int64_t(2), 0.0);
+        hipLaunchKernelGGL(k_fill<double>, dim3(1), dim3(256), 0, st, reinterpret_cast<double *>(report(v)), int64_t(2),
+                           0.0);
         DN_HIP(hipGetLastError());
         return DN_OK;
     }
@@ -363,29 +392,28 @@ static int energy_launch(dn_volume *v, double lambda, int l1, const typename S::
     return reduce_pairs(v, v->nb);
 }
 
-// Fixed-order sum of the n per-block pairs in v->partials into
-// v->energy2: level by level (ping-pong inside the scratch that follows the
-// per-block partials) until one pair is left.
+// Fixed-order sum of the n per-block pairs in v->partials, into the call's
+// report: sums of 1024 pairs until one workgroup takes the rest.
 int reduce_pairs(dn_volume *v, int64_t n)
 {
     hipStream_t st = v->stream;
     double *src = v->partials;
     double *bufs[2] = {v->partials + 2 * v->cap_blocks, v->partials + 2 * v->cap_blocks + 2 * ((v->cap_blocks + 1023) / 1024 + 1)};
     int which = 0;
-    while (n > 1) {
+    while (n > kFinalPairs) {
         const int64_t g = (n + 1023) / 1024;
-        double *dst = (g == 1) ? v->energy2 : bufs[which];
-        hipLaunchKernelGGL(k_energy_reduce, dim3(unsigned(g)), dim3(256), 0, st, n, src, dst);
+        hipLaunchKernelGGL(k_energy_reduce, dim3(unsigned(g)), dim3(256), 0, st, n, src, bufs[which]);
         DN_HIP(hipGetLastError());
-        src = dst;
+        src = bufs[which];
         which ^= 1;
         n = g;
     }
-    if (src != v->energy2) DN_HIP(hipMemcpyAsync(v->energy2, src, 16, hipMemcpyDeviceToDevice, st));
+    hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(1024), 0, st, int(n), src, reinterpret_cast<double *>(report(v)));
+    DN_HIP(hipGetLastError());
     return DN_OK;
 }
 
-// Energies of the current state into v->energy2 (device).
+// Energies of the current state into the call's report (read_energy).
 int energy_current(dn_volume *v, double lambda, bool use_f32, int data_term)
 {
     const int l1 = data_term == DN_DATA_L1;
@@ -403,7 +431,7 @@ int energy_current(dn_volume *v, double lambda, bool use_f32, int data_term)
 
 int read_energy(dn_volume *v, double out[2])
 {
-    int rc = read_back(v, v->energy2, 16);
+    int rc = fetch_report(v, 2);
     if (rc) return rc;
     memcpy(out, v->host_stage, 16);
     return DN_OK;

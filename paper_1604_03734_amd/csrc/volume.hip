@@ -1402,7 +1402,6 @@ static size_t volume_layout(const dn_volume_params &p, void *base, dn_volume *v)
     uint32_t *em4 = b.take<uint32_t>(mb * 64);
     int32_t *order = b.take<int32_t>(mb);
     double *partials = b.take<double>(mb * 2 + 2 * ((mb + 1023) / 1024 + 1) * 2 + 8);
-    double *energy2 = b.take<double>(8);
     int64_t *misc = b.take<int64_t>(32);
     uint64_t *cand = b.take<uint64_t>(size_t(p.max_candidates));
     void *u16 = nullptr, *ub16a = nullptr, *ub16b = nullptr, *p16a = nullptr, *p16b = nullptr;
@@ -1433,7 +1432,7 @@ static size_t volume_layout(const dn_volume_params &p, void *base, dn_volume *v)
     if (v) {
         v->coords = coords; v->keys = keys; v->hash[0] = h0; v->hash[1] = h1; v->nbr = nbr;
         v->f = f; v->w = w; v->u = u; v->ubar[0] = ub0; v->ubar[1] = ub1; v->p[0] = p0; v->p[1] = p1;
-        v->emask = emask; v->em4 = em4; v->order = order; v->partials = partials; v->energy2 = energy2; v->misc = misc;
+        v->emask = emask; v->em4 = em4; v->order = order; v->partials = partials; v->misc = misc;
         v->cand = cand;
         v->hord_home[0] = oh0; v->hord_home[1] = oh1; v->hord_ids[0] = oi0; v->hord_ids[1] = oi1;
         v->new_set = nset; v->new_key = nkey; v->sort_key = skey; v->new_home = nhome; v->new_slot = nslot;
