@@ -48,6 +48,7 @@ struct BatchArgs {
     int32_t *err;             // set when a barrier wait exceeds its bound
     long long spin_limit;
     int32_t l1;               // L1 data term
+    int32_t still;            // p is zero outside Omega in every volume
 };
 
 // Barrier state: one 256-byte slot per word that is written concurrently,
@@ -234,7 +235,7 @@ __global__ __launch_bounds__(64 * kBatchWaves) __attribute__((amdgpu_waves_per_e
             const int2 bi = load_item(items, lo + rel);
             CPArgs<SF32> A;
             item_args(a, vols, bi, it, sigma, tau, theta, A);
-            cp_block<SF32, false, kStream, kBatchWaves>(A, bi.y, sh, wave_index(), opaque_lane());
+            cp_block<SF32, false, kStream, false, kBatchWaves>(A, bi.y, sh, wave_index(), opaque_lane());
             if (threadIdx.x == 0) s_next = nraw - base;
             __syncthreads();
             rel = s_next;
@@ -254,7 +255,7 @@ __global__ __launch_bounds__(64 * kBatchWaves) __attribute__((amdgpu_waves_per_e
 // iteration.
 constexpr int kStepKernel = 1;   // variant code of this kernel in the tuner
 constexpr int kPersistent = 257; // ... and of the persistent one
-template <bool kStream>
+template <bool kStream, bool kStill>
 __global__ __launch_bounds__(64 * kBatchWaves) void k_cp_batch_step(BatchArgs a, const VolDesc *__restrict__ vols,
                                                        const int2 *__restrict__ items, int it, float sigma,
                                                        float tau, float theta)
@@ -265,7 +266,7 @@ __global__ __launch_bounds__(64 * kBatchWaves) void k_cp_batch_step(BatchArgs a,
     const int2 bi = load_item(items, slot);
     CPArgs<SF32> A;
     item_args(a, vols, bi, it, sigma, tau, theta, A);
-    cp_block<SF32, false, kStream, kBatchWaves>(A, bi.y, sh, wave_index(), threadIdx.x & 63u);
+    cp_block<SF32, false, kStream, kStill, kBatchWaves>(A, bi.y, sh, wave_index(), threadIdx.x & 63u);
 }
 
 __global__ void k_make_items(const int32_t *__restrict__ order, int64_t nb, int32_t vol, int2 *__restrict__ items)
@@ -282,7 +283,7 @@ struct BatchCtx {
     // key of the captured graph
     const void *k_items = nullptr;
     int64_t k_n = -1;
-    int k_iters = -1, k_grid = -1, k_xcd = -1, k_nt = -1, k_l1 = -1;
+    int k_iters = -1, k_grid = -1, k_xcd = -1, k_nt = -1, k_l1 = -1, k_still = -1;
     float k_prm[4] = {0, 0, 0, 0};
     double k_acc[3] = {0, 0, 0};
     const void *vols_ptr = nullptr;
@@ -341,8 +342,10 @@ static void launch_kernel(hipStream_t st, const BatchArgs &a, int grid, int nt)
                 acc_tau = th * acc_tau;
                 acc_sigma = acc_sigma / th;
             }
-            hipLaunchKernelGGL(stream ? k_cp_batch_step<true> : k_cp_batch_step<false>, dim3(g), dim3(64 * kBatchWaves),
-                               0, st, a, a.vols, a.items, it, sigma, tau, theta);
+            // (off Omega both buffers are alike after two iterations, as in the single-map solver)
+            auto k = !stream ? k_cp_batch_step<false, false>
+                             : (a.still && it >= 2 ? k_cp_batch_step<true, true> : k_cp_batch_step<true, false>);
+            hipLaunchKernelGGL(k, dim3(g), dim3(64 * kBatchWaves), 0, st, a, a.vols, a.items, it, sigma, tau, theta);
         }
     } else {
         hipLaunchKernelGGL(stream ? k_cp_persistent<true> : k_cp_persistent<false>, dim3(grid), dim3(64 * kBatchWaves), 0, st, a, a.vols, a.items);
@@ -367,7 +370,7 @@ static int launch_graph(BatchCtx &c, hipStream_t st, const BatchArgs &a, int gri
         DN_HIP(hipEventCreateWithFlags(&c.ev_out, hipEventDisableTiming));
     }
     bool same = c.exec && c.k_items == a.items && c.k_n == a.n_items && c.k_iters == a.iters && c.k_grid == grid &&
-                c.k_nt == nt && c.k_l1 == a.l1 &&
+                c.k_nt == nt && c.k_l1 == a.l1 && c.k_still == a.still &&
                 c.k_xcd == a.xcd_chunks && c.k_prm[0] == a.sigma && c.k_prm[1] == a.tau &&
                 c.k_prm[2] == a.lambda && c.k_prm[3] == a.theta && c.vols_ptr == a.vols && c.bar_ptr == a.bar &&
                 c.k_acc[0] == a.gamma && c.k_acc[1] == a.tau0 && c.k_acc[2] == a.sigma0;
@@ -386,6 +389,7 @@ static int launch_graph(BatchCtx &c, hipStream_t st, const BatchArgs &a, int gri
         c.k_items = a.items; c.k_n = a.n_items; c.k_iters = a.iters; c.k_grid = grid; c.k_xcd = a.xcd_chunks;
         c.k_nt = nt;
         c.k_l1 = a.l1;
+        c.k_still = a.still;
         c.k_prm[0] = a.sigma; c.k_prm[1] = a.tau; c.k_prm[2] = a.lambda; c.k_prm[3] = a.theta;
         c.k_acc[0] = a.gamma; c.k_acc[1] = a.tau0; c.k_acc[2] = a.sigma0;
         c.vols_ptr = a.vols; c.bar_ptr = a.bar;
@@ -514,6 +518,9 @@ extern "C" int dn_regularize_batch(dn_volume *const *vols, int32_t n, const dn_r
     a.spin_limit = 1LL << 22;
     a.xcd_chunks = 1;
     a.l1 = prm->data_term == DN_DATA_L1;
+    a.still = 1;
+    for (int i = 0; i < n; ++i)
+        if (!vols[i]->p_off_zero) a.still = 0;
 
     // occupancy bound: every workgroup of the grid must be resident at once
     int dev_cu = 0, per_cu = 0;

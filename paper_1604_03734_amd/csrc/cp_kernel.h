@@ -213,7 +213,15 @@ template <int W> __device__ __forceinline__ void block_sync()
 // voxel.  Per iteration, that layout and this one: 202195 blocks FP32 0.946
 // and 0.939 ms; 60001 blocks BF16 236 and 169 us; 5777 blocks FP32 34.0 and
 // 24.3 us (with the cache hints dropped there); 503 blocks 5.4 and 4.7 us.
-template <class S, bool kRefine, bool kStream, int W>
+//
+// kStill: the voxels outside Omega hold the same u, ubar and p in both sets
+// of buffers (see still_state), so a memory line without an observed voxel is
+// neither read nor written.  Whole lines only: leaving out single voxels
+// makes every line a partial write (1.11 ms at 202195 blocks, where whole
+// lines take it from 0.936 to 0.869; 12 % of that map's lines are empty).
+// It pays where memory bounds the kernel: the loads have to wait for the
+// masks (5777 blocks: no gain; 503: 4.5 -> 4.7 us).
+template <class S, bool kRefine, bool kStream, bool kStill, int W>
 __device__ __forceinline__ void cp_block(const CPArgs<S> &A, int32_t b, CPShared<W> &sh, int wave, unsigned lane)
 {
     using T = typename S::T;
@@ -228,14 +236,30 @@ __device__ __forceinline__ void cp_block(const CPArgs<S> &A, int32_t b, CPShared
     // the wave's own planes
     float ub[ZP], p0[ZP], p1[ZP], p2[ZP], uo[ZP], fv[ZP], wv[ZP];
     const uint32_t mw0 = (A.em4 + int64_t(b) * 64)[lane];
+    // kStill: bit k of `lines`: this lane's 128-byte line of plane z0 + k
+    // holds an observed voxel
+    uint32_t lines = 0;
+    if constexpr (kStill) {
+        static_assert(!S::kLow && !kRefine, "half a wave's plane is a line of FP32");
 #pragma unroll
-    for (int k = 0; k < ZP; ++k) ub[k] = S::ld((A.ubar_in + o0)[64 * k + lane]);
+        for (int k = 0; k < ZP; ++k) {
+            const uint64_t m = __ballot((mw0 >> (4 * (z0 + k))) & 1u);
+            lines |= ((lane < 32u ? uint32_t(m) : uint32_t(m >> 32)) != 0u ? 1u : 0u) << k;
+        }
+    }
+    auto on = [&](int k) { return !kStill || ((lines >> k) & 1u) != 0u; };
 #pragma unroll
     for (int k = 0; k < ZP; ++k) {
-        p0[k] = S::ld((A.p_in + o0)[64 * k + lane]);
-        p1[k] = S::ld((A.p_in + o0 + ps)[64 * k + lane]);
-        p2[k] = S::ld((A.p_in + o0 + 2 * ps)[64 * k + lane]);
+        if constexpr (kStill) ub[k] = p0[k] = p1[k] = p2[k] = uo[k] = fv[k] = wv[k] = 0.0f;
+        if (on(k)) ub[k] = S::ld((A.ubar_in + o0)[64 * k + lane]);
     }
+#pragma unroll
+    for (int k = 0; k < ZP; ++k)
+        if (on(k)) {
+            p0[k] = S::ld((A.p_in + o0)[64 * k + lane]);
+            p1[k] = S::ld((A.p_in + o0 + ps)[64 * k + lane]);
+            p2[k] = S::ld((A.p_in + o0 + 2 * ps)[64 * k + lane]);
+        }
     const unsigned ax = 110u + 10u * l8 + 100u * h8, ay = 101u + l8 + 100u * h8, az = 11u + l8 + 10u * h8;
     // ubar on the faces and edges and the old dual and masks on the -1 faces,
     // shared out over the waves; every load is issued before the first value
@@ -305,11 +329,12 @@ __device__ __forceinline__ void cp_block(const CPArgs<S> &A, int32_t b, CPShared
             if (w == kWy) load_face(fy, 3, l8 + 56u);
         }
 #pragma unroll
-    for (int k = 0; k < ZP; ++k) {
-        uo[k] = S::ld(ld_own<kStream>((const T *)(A.u + o0) + 64 * k + lane));
-        fv[k] = ld_own<kStream>(A.f + o0 + 64 * k + lane);
-        wv[k] = ld_own<kStream>(A.w + o0 + 64 * k + lane);
-    }
+    for (int k = 0; k < ZP; ++k)
+        if (on(k)) {
+            uo[k] = S::ld(ld_own<kStream>((const T *)(A.u + o0) + 64 * k + lane));
+            fv[k] = ld_own<kStream>(A.f + o0 + 64 * k + lane);
+            wv[k] = ld_own<kStream>(A.w + o0 + 64 * k + lane);
+        }
 #pragma unroll
     for (int w = 0; w < W; ++w)
         if (wave == w) {
@@ -340,7 +365,8 @@ __device__ __forceinline__ void cp_block(const CPArgs<S> &A, int32_t b, CPShared
         sh.py[qy + 72 * k] = d1[k];
         const unsigned i = 64 * k + lane;
         T *po = A.p_out + o0;
-        if constexpr (S::kLow) {
+        if (!on(k)) {
+        } else if constexpr (S::kLow) {
             // stochastic rounding; where it would leave the unit ball, toward zero
             const int64_t gi = o0 + i;
             const uint32_t r0 = voxel_bits(gi, 0, A.seed), r1 = voxel_bits(gi, 1, A.seed);
@@ -405,7 +431,8 @@ __device__ __forceinline__ void cp_block(const CPArgs<S> &A, int32_t b, CPShared
         un = keep_if(mw, 4 * k) ? un : uo[k];
         const float ubn = un + A.theta * (un - uo[k]);
         const unsigned i = 64 * k + lane;
-        if constexpr (S::kLow) {
+        if (!on(k)) {
+        } else if constexpr (S::kLow) {
             const uint32_t r2 = voxel_bits(o0 + i, 2, A.seed);
             st_own<kStream>(A.u + o0 + i, S::sr(un, r2));
             st_own<kStream>(A.ubar_out + o0 + i, S::sr(ubn, r2 >> 16));

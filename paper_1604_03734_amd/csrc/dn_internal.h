@@ -121,6 +121,11 @@ struct dn_volume {
     float *u = nullptr;
     float *ubar[2] = {nullptr, nullptr};
     float *p[2] = {nullptr, nullptr};   // each [3][max][512]
+    // outside Omega: whether p is zero there (not after a given p0, or when
+    // loaded weights may have taken voxels out of Omega), and how many
+    // iterations of this call have written all voxels (regularize.hip)
+    bool p_off_zero = true;
+    int64_t full_iters = 0;
     int cur = 0;                        // index of the current ubar/p buffers
     // 16-bit solver state (in the arena when the volume has state16)
     void *u16 = nullptr;

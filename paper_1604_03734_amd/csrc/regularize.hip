@@ -28,14 +28,14 @@
 namespace dn {
 
 // W waves of 64 lanes per block, 8 / W planes each.
-template <class S, bool kRefine, bool kStream, int W>
+template <class S, bool kRefine, bool kStream, bool kStill, int W>
 __global__ __launch_bounds__(64 * W) void k_cp_fused(CPArgs<S> A)
 {
     __shared__ CPShared<W> sh;
     const int64_t slot = block_slot(blockIdx.x, A.nb, A.xcd);
     if (slot >= A.nb) return;
     const int32_t b = A.order ? as_scalar(A.order)[slot] : int32_t(slot);
-    cp_block<S, kRefine, kStream, W>(A, b, sh, wave_index(), threadIdx.x & 63u);
+    cp_block<S, kRefine, kStream, kStill, W>(A, b, sh, wave_index(), threadIdx.x & 63u);
 }
 
 // ----------------------------------------------------- two-pass variant
@@ -458,24 +458,43 @@ static CPArgs<S> make_args(dn_volume *v, const dn_reg_params *prm, typename S::T
     return A;
 }
 
+// Off Omega an iteration leaves u and p as they are and sets ubar to u, as
+// long as p is zero there (it is projected with the rest).  Two iterations
+// that write everything put the same values into both sets of buffers; after
+// those (true here), iterations may leave empty lines alone.  Counts the
+// iteration about to run.
+static bool still_state(dn_volume *v) { return v->p_off_zero && v->full_iters++ >= 2; }
+
 static unsigned fused_grid(int64_t nb) { return unsigned(((nb + 7) / 8) * 8); }
 
-template <class S, bool kRefine, bool kStream>
+template <class S, bool kRefine, bool kStream, bool kStill>
 static void launch_fused_w(hipStream_t st, const CPArgs<S> &A, int kernel)
 {
     const dim3 grid(fused_grid(A.nb));
     switch (kernel) {
-    case DN_K_FUSED64: hipLaunchKernelGGL((k_cp_fused<S, kRefine, kStream, 1>), grid, dim3(64), 0, st, A); break;
-    case DN_K_FUSED128: hipLaunchKernelGGL((k_cp_fused<S, kRefine, kStream, 2>), grid, dim3(128), 0, st, A); break;
-    case DN_K_FUSED256: hipLaunchKernelGGL((k_cp_fused<S, kRefine, kStream, 4>), grid, dim3(256), 0, st, A); break;
-    default: hipLaunchKernelGGL((k_cp_fused<S, kRefine, kStream, 8>), grid, dim3(512), 0, st, A);
+    case DN_K_FUSED64: hipLaunchKernelGGL((k_cp_fused<S, kRefine, kStream, kStill, 1>), grid, dim3(64), 0, st, A); break;
+    case DN_K_FUSED128: hipLaunchKernelGGL((k_cp_fused<S, kRefine, kStream, kStill, 2>), grid, dim3(128), 0, st, A); break;
+    case DN_K_FUSED256: hipLaunchKernelGGL((k_cp_fused<S, kRefine, kStream, kStill, 4>), grid, dim3(256), 0, st, A); break;
+    default: hipLaunchKernelGGL((k_cp_fused<S, kRefine, kStream, kStill, 8>), grid, dim3(512), 0, st, A);
     }
 }
 
-template <class S, bool kRefine> static void launch_fused(hipStream_t st, const CPArgs<S> &A, int kernel)
+// `still`: see still_state.  Not with 8 waves per block (a wait for the masks
+// for a single plane each: no faster) and not in 16 bits, where a line is a
+// whole plane and the waits cost more than the few empty planes give (60001
+// blocks BF16: 179 and 232 us).
+template <class S, bool kRefine> static void launch_fused(hipStream_t st, const CPArgs<S> &A, int kernel, bool still)
 {
-    if (kRefine || streams_state(A.nb, sizeof(typename S::T))) launch_fused_w<S, kRefine, true>(st, A, kernel);
-    else launch_fused_w<S, kRefine, false>(st, A, kernel);
+    if (!kRefine && !streams_state(A.nb, sizeof(typename S::T))) {
+        launch_fused_w<S, kRefine, kRefine, false>(st, A, kernel);   // (kRefine: not reached)
+        return;
+    }
+    if constexpr (!kRefine && !S::kLow)
+        if (still && kernel != DN_K_FUSED) {
+            launch_fused_w<S, kRefine, true, true>(st, A, kernel);
+            return;
+        }
+    launch_fused_w<S, kRefine, true, false>(st, A, kernel);
 }
 
 // One FP32 iteration with the chosen kernel.
@@ -495,7 +514,7 @@ static int step_f32(dn_volume *v, const dn_reg_params *prm, int kernel)
     }
     const int c = v->cur, n = 1 - c;
     auto A = make_args<SF32>(v, prm, v->u, v->ubar[c], v->ubar[n], v->p[c], v->p[n]);
-    launch_fused<SF32, false>(st, A, kernel);
+    launch_fused<SF32, false>(st, A, kernel, still_state(v));
     DN_HIP(hipGetLastError());
     v->cur = n;
     return DN_OK;
@@ -511,9 +530,9 @@ static int step_lowp(dn_volume *v, const dn_reg_params *prm, bool refine, int ke
     A.seed = uint32_t(v->lowp_iter++);
     if (refine) {
         A.u32 = v->u; A.ubar32 = v->ubar[n]; A.p32 = v->p[n];
-        launch_fused<S, true>(v->stream, A, kernel);
+        launch_fused<S, true>(v->stream, A, kernel, false);
     } else {
-        launch_fused<S, false>(v->stream, A, kernel);
+        launch_fused<S, false>(v->stream, A, kernel, false);
     }
     DN_HIP(hipGetLastError());
     v->cur = n;
@@ -578,6 +597,8 @@ template <class S> static int promote_state(dn_volume *v)
 
 int zero_state(dn_volume *v)
 {
+    v->p_off_zero = true;
+    v->full_iters = 0;
     hipStream_t st = v->stream;
     const int64_t n = v->nb * kBlockVox, ps = v->cap_blocks * kBlockVox;
     int rc;
@@ -650,7 +671,8 @@ static int autotune_single(dn_volume *v, const dn_reg_params *prm, int *choice)
             v->layout = layout;
             int rc = zero_state(v);
             if (rc) return rc;
-            if ((rc = step_f32(v, prm, k))) return rc;  // warm up
+            for (int i = 0; i < 2; ++i)
+                if ((rc = step_f32(v, prm, k))) return rc;  // warm up
             DN_HIP(hipEventRecord(e0, v->stream));
             for (int i = 0; i < trial; ++i)
                 if ((rc = step_f32(v, prm, k))) return rc;
@@ -760,6 +782,7 @@ int dn_regularize(dn_volume *v, const dn_reg_params *prm, const float *u0, const
             }
         }
         v->state_storage = DN_F32;
+        v->p_off_zero = p0 == nullptr;
     } else if (prm->init == DN_INIT_CONTINUE) {
         // a 16-bit run ended with an FP32 sweep: continue from its output
         v->state_storage = DN_F32;
@@ -774,6 +797,7 @@ int dn_regularize(dn_volume *v, const dn_reg_params *prm, const float *u0, const
                 if ((rc = fill<float>(st, v->p[v->cur] + a * ps + first * kBlockVox, cnt, 0.f))) return rc;
         }
     }
+    v->full_iters = 0;     // Omega may have changed since the last call
     if (prm->init != DN_INIT_KEEP || v->acc_tau <= 0.0) {
         v->acc_tau = prm->tau;
         v->acc_sigma = prm->sigma;

@@ -1632,6 +1632,7 @@ int dn_volume_clear(dn_volume *v)
                        reinterpret_cast<int4 *>(v->hash[v->cur_hash]), v->hash_slots);
     DN_HIP(hipGetLastError());
     v->nb = 0;
+    v->p_off_zero = true;
     v->nb_state = 0;
     v->emask_nb = -1;
     v->cand_n = 0;
@@ -1734,6 +1735,7 @@ int dn_load_fused(dn_volume *v, const float *f, const float *w)
     size_t bytes = size_t(v->nb) * kBlockVox * 4;
     DN_HIP(hipMemcpyAsync(v->f, f, bytes, hipMemcpyDeviceToDevice, v->stream));
     DN_HIP(hipMemcpyAsync(v->w, w, bytes, hipMemcpyDeviceToDevice, v->stream));
+    v->p_off_zero = false;      // (until a solve starts from p = 0)
     v->emask_nb = -1;
     return DN_OK;
 }

@@ -1,0 +1,85 @@
+"""Maps whose state does not fit the caches (12,700 blocks and more in FP32)
+leave memory lines without an observed voxel alone from the third iteration
+on.  The kernel with 8 waves per block never does; both give the same state
+bit for bit, off the observed voxels too, from every initial state: zero,
+given with and without a dual, kept and continued, and after loaded weights
+have moved the observed set under an existing state."""
+import numpy as np
+import pytest
+
+import scenes
+from gpu_common import LAM, dn, state_of, to_dev
+
+pytestmark = pytest.mark.gpu
+
+NB = 13001
+
+
+def _fields(seed):
+    coords, f, w = scenes.random_block_field(NB, 5, extent=26, omega_frac=0.7)
+    rng = np.random.default_rng(seed)
+    w = np.asarray(w, np.float32).reshape(NB, 512).copy()
+    w[rng.random(NB) < 0.2] = 0                       # empty blocks
+    w.reshape(-1, 32)[rng.random(NB * 16) < 0.3] = 0  # empty lines
+    w.reshape(-1, 64)[rng.random(NB * 8) < 0.1] = 1
+    return coords.astype(np.int32), np.asarray(f, np.float32).reshape(NB, 512), w
+
+
+def _run(D, kernel):
+    coords, f, w = _fields(1)
+    w2 = _fields(2)[2]
+    rng = np.random.default_rng(3)
+    u0 = to_dev(rng.normal(size=(NB, 512)).astype(np.float32))
+    p0 = to_dev(rng.normal(size=(3, NB, 512)).astype(np.float32))
+    gv = D.Volume(0.1, 0.3, 10.0, NB, 16, 256, max_points=0, max_candidates=NB)
+    gv.insert_blocks(to_dev(coords), keep_order=True)
+    gv.load_fused(to_dev(f), to_dev(w))
+    out = []
+
+    def solve(init, *given, iters=7, **kw):
+        gv.regularize(D.reg_params(LAM, iters=iters, kernel=kernel, init=init, **kw), *given)
+        out.extend(state_of(D, gv))
+
+    solve(D.DN_INIT_ZERO)
+    solve(D.DN_INIT_KEEP, iters=1)
+    solve(D.DN_INIT_KEEP, iters=4)
+    solve(D.DN_INIT_GIVEN, u0, p0)
+    solve(D.DN_INIT_CONTINUE)
+    solve(D.DN_INIT_GIVEN, u0, gamma=0.5)
+    gv.load_fused(to_dev(f), to_dev(w2))
+    solve(D.DN_INIT_CONTINUE)
+    solve(D.DN_INIT_ZERO, data_term=D.DN_DATA_L1)
+    gv.close()
+    return out
+
+
+def test_resting_lines_change_nothing():
+    D = dn()
+    want = _run(D, D.DN_K_FUSED)
+    for kernel in (D.DN_K_FUSED256, D.DN_K_AUTO):
+        for a, b in zip(want, _run(D, kernel)):
+            np.testing.assert_array_equal(a, b)
+
+
+def test_batched_solve_rests_the_same_lines():
+    """The batched solver at a streaming total, against single-map solves."""
+    D = dn()
+    vols = []
+    for _ in range(2):
+        pair = []
+        for seed in (1, 2):
+            coords, f, w = _fields(seed)
+            gv = D.Volume(0.1, 0.3, 10.0, NB, 16, 256, max_points=0, max_candidates=NB)
+            gv.insert_blocks(to_dev(coords), keep_order=True)
+            gv.load_fused(to_dev(f), to_dev(w))
+            pair.append(gv)
+        vols.append(pair)
+    prm = D.reg_params(LAM, iters=9, kernel=D.DN_K_FUSED)
+    for gv in vols[0]:
+        gv.regularize(prm)
+    D.regularize_batch(vols[1], D.reg_params(LAM, iters=9, kernel=D.DN_K_FUSED256))
+    for a, b in zip(*vols):
+        for x, y in zip(state_of(D, a), state_of(D, b)):
+            np.testing.assert_array_equal(x, y)
+        a.close()
+        b.close()
