@@ -49,6 +49,7 @@ struct BatchArgs {
     long long spin_limit;
     int32_t l1;               // L1 data term
     int32_t still;            // p is zero outside Omega in every volume
+    int32_t first;            // iterations already done (the first one from zero)
 };
 
 // Barrier state: one 256-byte slot per word that is written concurrently,
@@ -201,6 +202,7 @@ __global__ __launch_bounds__(64 * kBatchWaves) __attribute__((amdgpu_waves_per_e
             acc_tau = th * acc_tau;
             acc_sigma = acc_sigma / th;
         }
+        if (it < a.first) continue;
         int64_t lo = 0, hi = a.n_items, stride = G, cx = 0;
         if (a.xcd_chunks && G >= 8) {
             // workgroup g runs on XCD g % 8; XCD x owns items [x*chunk, (x+1)*chunk)
@@ -222,7 +224,7 @@ __global__ __launch_bounds__(64 * kBatchWaves) __attribute__((amdgpu_waves_per_e
         // 2^32, which keeps differences exact).
         unsigned *ctr = a.bar + kBarCtr + cx * kBarSlot;
         const unsigned len = unsigned(hi > lo ? hi - lo : 0);
-        const unsigned base = unsigned(it) * (len + unsigned(stride));
+        const unsigned base = unsigned(it - a.first) * (len + unsigned(stride));
         if (threadIdx.x == 0)
             s_next = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - base;
         __syncthreads();
@@ -240,7 +242,7 @@ __global__ __launch_bounds__(64 * kBatchWaves) __attribute__((amdgpu_waves_per_e
             __syncthreads();
             rel = s_next;
         }
-        grid_barrier(a, nwg, unsigned(it + 1));
+        grid_barrier(a, nwg, unsigned(it - a.first + 1));
         if (threadIdx.x == 0)
             s_stop = __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
@@ -283,7 +285,7 @@ struct BatchCtx {
     // key of the captured graph
     const void *k_items = nullptr;
     int64_t k_n = -1;
-    int k_iters = -1, k_grid = -1, k_xcd = -1, k_nt = -1, k_l1 = -1, k_still = -1;
+    int k_iters = -1, k_grid = -1, k_xcd = -1, k_nt = -1, k_l1 = -1, k_still = -1, k_first = -1;
     float k_prm[4] = {0, 0, 0, 0};
     double k_acc[3] = {0, 0, 0};
     const void *vols_ptr = nullptr;
@@ -342,6 +344,7 @@ static void launch_kernel(hipStream_t st, const BatchArgs &a, int grid, int nt)
                 acc_tau = th * acc_tau;
                 acc_sigma = acc_sigma / th;
             }
+            if (it < a.first) continue;
             // (off Omega both buffers are alike after two iterations, as in the single-map solver)
             auto k = !stream ? k_cp_batch_step<false, false>
                              : (a.still && it >= 2 ? k_cp_batch_step<true, true> : k_cp_batch_step<true, false>);
@@ -370,7 +373,7 @@ static int launch_graph(BatchCtx &c, hipStream_t st, const BatchArgs &a, int gri
         DN_HIP(hipEventCreateWithFlags(&c.ev_out, hipEventDisableTiming));
     }
     bool same = c.exec && c.k_items == a.items && c.k_n == a.n_items && c.k_iters == a.iters && c.k_grid == grid &&
-                c.k_nt == nt && c.k_l1 == a.l1 && c.k_still == a.still &&
+                c.k_nt == nt && c.k_l1 == a.l1 && c.k_still == a.still && c.k_first == a.first &&
                 c.k_xcd == a.xcd_chunks && c.k_prm[0] == a.sigma && c.k_prm[1] == a.tau &&
                 c.k_prm[2] == a.lambda && c.k_prm[3] == a.theta && c.vols_ptr == a.vols && c.bar_ptr == a.bar &&
                 c.k_acc[0] == a.gamma && c.k_acc[1] == a.tau0 && c.k_acc[2] == a.sigma0;
@@ -390,6 +393,7 @@ static int launch_graph(BatchCtx &c, hipStream_t st, const BatchArgs &a, int gri
         c.k_nt = nt;
         c.k_l1 = a.l1;
         c.k_still = a.still;
+        c.k_first = a.first;
         c.k_prm[0] = a.sigma; c.k_prm[1] = a.tau; c.k_prm[2] = a.lambda; c.k_prm[3] = a.theta;
         c.k_acc[0] = a.gamma; c.k_acc[1] = a.tau0; c.k_acc[2] = a.sigma0;
         c.vols_ptr = a.vols; c.bar_ptr = a.bar;
@@ -463,6 +467,18 @@ extern "C" int dn_regularize_batch(dn_volume *const *vols, int32_t n, const dn_r
     BatchCtx &c = g_batch[v0->device];
     Bump bump(workspace, workspace_bytes);
     const BatchWS ws = carve_batch(bump, n, total);
+    // from zero, the first iteration need not find the zeros in memory
+    const bool first = prm->init == DN_INIT_ZERO && prm->iters > 0;
+    auto zero_all = [&]() {
+        for (int i = 0; i < n; ++i) {
+            hipStream_t keep = vols[i]->stream;
+            vols[i]->stream = st;
+            const int zrc = zero_state(vols[i]);
+            vols[i]->stream = keep;
+            if (zrc) return zrc;
+        }
+        return int(DN_OK);
+    };
     total = 0;
     for (int i = 0; i < n; ++i) {
         dn_volume *v = vols[i];
@@ -471,7 +487,8 @@ extern "C" int dn_regularize_batch(dn_volume *const *vols, int32_t n, const dn_r
         hipStream_t keep = v->stream;
         v->stream = st;
         rc = build_masks(v);
-        if (!rc && prm->init == DN_INIT_ZERO) rc = zero_state(v);
+        if (first) from_zero(v);
+        else if (!rc && prm->init == DN_INIT_ZERO) rc = zero_state(v);
         if (!rc && v->state_storage != DN_F32) v->state_storage = DN_F32;
         v->stream = keep;
         if (rc) return rc;
@@ -519,6 +536,7 @@ extern "C" int dn_regularize_batch(dn_volume *const *vols, int32_t n, const dn_r
     a.xcd_chunks = 1;
     a.l1 = prm->data_term == DN_DATA_L1;
     a.still = 1;
+    a.first = 0;
     for (int i = 0; i < n; ++i)
         if (!vols[i]->p_off_zero) a.still = 0;
 
@@ -548,6 +566,7 @@ extern "C" int dn_regularize_batch(dn_volume *const *vols, int32_t n, const dn_r
         // all with the items in XCD chunks (without, the persistent kernel's
         // one counter for all workgroups took 3.1 against 1.4 ms for six
         // iterations of 16 sub-maps, and the launches were within 1 %)
+        if ((rc = zero_all())) return rc;
         hipEvent_t e0, e1;
         DN_HIP(hipEventCreate(&e0));
         DN_HIP(hipEventCreate(&e1));
@@ -580,13 +599,6 @@ extern "C" int dn_regularize_batch(dn_volume *const *vols, int32_t n, const dn_r
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
         g_tuned[key] = ch;
-        for (int i = 0; i < n; ++i) {
-            hipStream_t keep = vols[i]->stream;
-            vols[i]->stream = st;
-            rc = zero_state(vols[i]);
-            vols[i]->stream = keep;
-            if (rc) return rc;
-        }
     }
     if ((rc = build_items(ch.pool))) return rc;
     a.iters = prm->iters;
@@ -598,6 +610,21 @@ extern "C" int dn_regularize_batch(dn_volume *const *vols, int32_t n, const dn_r
     DN_HIP(hipEventCreate(&e1));
     DN_HIP(hipEventRecord(e0, st));
     if (total > 0 && prm->iters > 0) {
+        if (first) {
+            double th = prm->theta, tau = prm->tau;
+            if (prm->gamma > 0.0) {
+                th = 1.0 / std::sqrt(1.0 + 2.0 * a.gamma * a.tau0);
+                tau = a.tau0;
+            }
+            for (int i = 0; i < n; ++i) {
+                hipStream_t keep = vols[i]->stream;
+                vols[i]->stream = st;
+                rc = first_iteration(vols[i], float(tau), a.lambda, float(th), a.l1);
+                vols[i]->stream = keep;
+                if (rc) return rc;
+            }
+            a.first = 1;
+        }
         if ((rc = launch_graph(c, st, a, grid, ch.nt))) return rc;
     }
     DN_HIP(hipEventRecord(e1, st));
@@ -613,14 +640,22 @@ extern "C" int dn_regularize_batch(dn_volume *const *vols, int32_t n, const dn_r
             v0->acc_tau = th * v0->acc_tau;
             v0->acc_sigma = v0->acc_sigma / th;
         }
+    // the energies of all sub-maps, then one wait for them
     for (int i = 0; i < n; ++i) {
         dn_volume *v = vols[i];
         v->cur = (v->cur + prm->iters) & 1;
         hipStream_t keep = v->stream;
         v->stream = st;
-        double ed[2] = {0, 0};
         rc = energy_current(v, prm->lambda, true, prm->data_term);
-        if (!rc) rc = read_energy(v, ed);
+        v->stream = keep;
+        if (rc) return rc;
+    }
+    for (int i = 0; i < n; ++i) {
+        dn_volume *v = vols[i];
+        hipStream_t keep = v->stream;
+        v->stream = st;
+        double ed[2] = {0, 0};
+        rc = read_energy(v, ed);
         v->stream = keep;
         if (rc) return rc;
         if (out) {

@@ -168,6 +168,19 @@ __device__ __forceinline__ float prox_div(float num, float den)
     return num / den;
 }
 
+// The data term's proximal step of u~, tl = tau lambda.
+__device__ __forceinline__ float data_prox(float ut, float fv, float wv, float tl, int l1)
+{
+    const float tlw = tl * wv;
+    if (l1) {
+        // soft threshold of u~ - f by tau lambda w, then the [-1, 1] box
+        float r = ut - fv;
+        r = r > tlw ? r - tlw : (r < -tlw ? r + tlw : 0.0f);
+        return fminf(fmaxf(fv + r, -1.0f), 1.0f);
+    }
+    return prox_div(ut + tlw * fv, 1.0f + tlw);
+}
+
 // One wave of 64 lanes holds whole (x, y) planes of a block: lane = x + 8 y,
 // plane z in registers.  Bit 4z + i of a mask word: bit i (0 Omega, 1 + a
 // m_a) of the edge mask of voxel (lane, z).
@@ -417,17 +430,7 @@ __device__ __forceinline__ void cp_block(const CPArgs<S> &A, int32_t b, CPShared
         float dv = d0[k] - sh.px[qx + 72 * k - 1];
         dv += d1[k] - sh.py[qy + 72 * k - 8];
         dv += d2[k] - (k > 0 ? d2[k > 0 ? k - 1 : 0] : zlow);
-        const float ut = uo[k] + A.tau * dv;
-        const float tlw = tl * wv[k];
-        float un;
-        if (A.l1) {
-            // soft threshold of u~ - f by tau lambda w, then the [-1, 1] box
-            float r = ut - fv[k];
-            r = r > tlw ? r - tlw : (r < -tlw ? r + tlw : 0.0f);
-            un = fminf(fmaxf(fv[k] + r, -1.0f), 1.0f);
-        } else {
-            un = prox_div(ut + tlw * fv[k], 1.0f + tlw);
-        }
+        float un = data_prox(uo[k] + A.tau * dv, fv[k], wv[k], tl, A.l1);
         un = keep_if(mw, 4 * k) ? un : uo[k];
         const float ubn = un + A.theta * (un - uo[k]);
         const unsigned i = 64 * k + lane;

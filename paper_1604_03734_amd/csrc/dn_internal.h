@@ -165,6 +165,10 @@ size_t masks_scratch(int64_t n_blocks);
 int build_candidates(dn_volume *v, uint64_t **uniq, int64_t *n_uniq);
 size_t candidates_scratch(int64_t n_cand);
 int zero_state(dn_volume *v);
+// the state is zero, but not in memory: first_iteration comes next
+void from_zero(dn_volume *v);
+// the first FP32 iteration from there, into u and the other set of buffers
+int first_iteration(dn_volume *v, float tau, float lambda, float theta, int l1);
 int energy_current(dn_volume *v, double lambda, bool use_f32, int data_term);
 int read_energy(dn_volume *v, double out[2]);
 int reduce_pairs(dn_volume *v, int64_t n);

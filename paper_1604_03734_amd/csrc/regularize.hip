@@ -38,6 +38,42 @@ __global__ __launch_bounds__(64 * W) void k_cp_fused(CPArgs<S> A)
     cp_block<S, kRefine, kStream, kStill, W>(A, b, sh, wave_index(), threadIdx.x & 63u);
 }
 
+// The first iteration from the zero state, four voxels per thread: ubar and p
+// are zero, so the dual stays zero, and each voxel takes the data term's step
+// from u = 0.  Reads f, w and the masks, writes u, ubar and p: 29 bytes per
+// FP32 voxel, where clearing the state (20) and a general iteration (48) were
+// before; the result has the same bits.  A whole solve before and now: 202195
+// blocks, 30 iterations FP32 28.1 and 27.0 ms; 60001 blocks, 50 iterations
+// BF16 (whose zeros were also converted) 9.50 and 8.84 ms.
+template <class S>
+__global__ __launch_bounds__(256) void k_cp_first(int64_t n4, int64_t ps, const uint32_t *__restrict__ em,
+                                                  const float4 *__restrict__ f, const float4 *__restrict__ w,
+                                                  typename S::T *__restrict__ u, typename S::T *__restrict__ ubar,
+                                                  typename S::T *__restrict__ p, float tl, float theta, int l1,
+                                                  uint32_t seed)
+{
+    typedef typename S::T T4 __attribute__((ext_vector_type(4)));
+    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (i >= n4) return;
+    const uint32_t m = em[i];
+    const float4 fv = f[i], wv = w[i];
+    const float fs[4] = {fv.x, fv.y, fv.z, fv.w}, ws[4] = {wv.x, wv.y, wv.z, wv.w};
+    T4 a, b;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        float un = data_prox(0.0f, fs[k], ws[k], tl, l1);
+        un = (m >> (8 * k)) & 1u ? un : 0.0f;
+        const float ubn = un + theta * un;
+        const uint32_t r = S::kLow ? voxel_bits(4 * i + k, 2, seed) : 0u;
+        a[k] = S::sr(un, r);
+        b[k] = S::sr(ubn, r >> 16);
+    }
+    const T4 zero = T4(0);
+    reinterpret_cast<T4 *>(u)[i] = a;
+    reinterpret_cast<T4 *>(ubar)[i] = b;
+    for (int c = 0; c < 3; ++c) reinterpret_cast<T4 *>(p + c * ps)[i] = zero;
+}
+
 // ----------------------------------------------------- two-pass variant
 __global__ __launch_bounds__(512) void k_dual(int64_t nb, int64_t ps, const int32_t *__restrict__ nbr,
                                               const uint8_t *__restrict__ emask, const float *__restrict__ ubar,
@@ -159,17 +195,33 @@ __global__ void k_morton(const int32_t *__restrict__ coords, int64_t nb, uint64_
 }
 
 // ---------------------------------------------------------- energies
-__device__ __forceinline__ double wave_sum(double v)
+template <int kCtrl> __device__ __forceinline__ double dpp_add(double v)
 {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), kCtrl, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), kCtrl, 0xF, 0xF, true);
+    return v + __hiloint2double(hi, lo);
+}
+// A wave's sums of two values: of e in lane 0, of d in lane 32.  The halves
+// of the wave take one value each, then four steps inside rows of 16 lanes
+// (quads, mirrors) without LDS, and one across.
+__device__ __forceinline__ double wave_sum2(double e, double d)
+{
+    const bool low = (threadIdx.x & 32u) == 0;
+    double v = (low ? e : d) + __shfl_xor(low ? d : e, 32, 64);
+    v = dpp_add<0xB1>(v);      // lane ^ 1
+    v = dpp_add<0x4E>(v);      // lane ^ 2
+    v = dpp_add<0x141>(v);     // the other quad of 8
+    v = dpp_add<0x140>(v);     // the other 8 of 16
+    return v + __shfl_xor(v, 16, 64);
 }
 
 // Per-block partial sums of E(u) and D(p) (Eq. 2 with the weight of the
 // proximal step, Eq. 6), float64.  256 threads, two voxels each; u with its
-// +1 faces, p and the edge masks with their -1 faces are staged in LDS.
-// Fixed reduction order: lanes by xor-shuffle butterflies, then the 4 wave
-// sums in wave order.
+// +1 faces, p and the edge masks with their -1 faces are staged in LDS.  Bound
+// by latency and the float64 units: every load is issued before the barrier,
+// nothing branches on the masks, and the sums stay in registers down to 16
+// lanes: 5777 blocks 23.9 -> 19.8 us, 60001 269 -> 192.
+// Fixed reduction order: wave_sum2, then the 4 wave sums in wave order.
 template <class S>
 __global__ __launch_bounds__(256) void k_energy_partial(int64_t nb, int64_t ps, const int32_t *__restrict__ nbr,
                                                         const uint8_t *__restrict__ emask,
@@ -187,64 +239,74 @@ __global__ __launch_bounds__(256) void k_energy_partial(int64_t nb, int64_t ps, 
     const int t = threadIdx.x;
     const int32_t *nb27 = nbr + b * kNbr;
     auto iu = [](int x, int y, int z) { return (z * 9 + y) * 9 + x; };
+    float u2[2], f2[2], w2[2], q0[2], q1[2], q2[2];
+    uint8_t m2[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int64_t gi = b * kBlockVox + t + 256 * k;
+        u2[k] = S::ld(u[gi]);
+        m2[k] = emask[gi];
+        q0[k] = S::ld(p[gi]); q1[k] = S::ld(p[gi + ps]); q2[k] = S::ld(p[gi + 2 * ps]);
+        f2[k] = f[gi];
+        w2[k] = w[gi];
+    }
+    // wave a < 3: the +1 face of u along axis a, and on the -1 face the
+    // component of p along it and the edge mask (of the block itself, and then
+    // 0, where the neighbour is not allocated)
+    const int a = __builtin_amdgcn_readfirstlane(t >> 6), c0 = t & 7, c1 = (t >> 3) & 7;
+    if (a < 3) {
+        const int32_t up = nb27[a == 0 ? 14 : (a == 1 ? 16 : 22)], low = nb27[a == 0 ? 12 : (a == 1 ? 10 : 4)];
+        const int at = a == 0 ? 8 * c0 + 64 * c1 : (a == 1 ? c0 + 64 * c1 : c0 + 8 * c1);
+        const int64_t ju = (up >= 0 ? up : b) * kBlockVox + at;
+        const int64_t jl = (low >= 0 ? low : b) * kBlockVox + at + (a == 0 ? 7 : (a == 1 ? 56 : 448));
+        const float uf = S::ld(u[ju]), pf = S::ld(p[jl + a * ps]);
+        const uint8_t mf = emask[jl];
+        su[a == 0 ? iu(8, c0, c1) : (a == 1 ? iu(c0, 8, c1) : iu(c0, c1, 8))] = up >= 0 ? uf : 0.0f;
+        const int q = a == 0 ? i9(-1, c0, c1) : (a == 1 ? i9(c0, -1, c1) : i9(c0, c1, -1));
+        sm[q] = low >= 0 ? mf : uint8_t(0);
+        sp[a][q] = low >= 0 ? pf : 0.0f;
+    }
+#pragma unroll
     for (int k = 0; k < 2; ++k) {
         const int v = t + 256 * k, lx = v & 7, ly = (v >> 3) & 7, lz = v >> 6;
-        const int64_t gi = b * kBlockVox + v;
-        su[iu(lx, ly, lz)] = S::ld(u[gi]);
         const int q = i9(lx, ly, lz);
-        sm[q] = emask[gi];
-        sp[0][q] = S::ld(p[gi]); sp[1][q] = S::ld(p[gi + ps]); sp[2][q] = S::ld(p[gi + 2 * ps]);
-    }
-    if (t < 192) {
-        // +1 faces of u: face a = t / 64
-        const int a = t >> 6, i = t & 63, c0 = i & 7, c1 = i >> 3;
-        int x, y, z;
-        if (a == 0) { x = 8; y = c0; z = c1; }
-        else if (a == 1) { x = c0; y = 8; z = c1; }
-        else { x = c0; y = c1; z = 8; }
-        int64_t j = halo_index(nb27, x, y, z);
-        su[iu(x, y, z)] = j >= 0 ? S::ld(u[j]) : 0.0f;
-        // -1 faces: the normal component of p and the edge mask
-        int hx, hy, hz;
-        face_pos(t, hx, hy, hz);
-        int64_t jm = halo_index(nb27, hx, hy, hz);
-        const int q = i9(hx, hy, hz);
-        sm[q] = jm >= 0 ? emask[jm] : uint8_t(0);
-        sp[a][q] = jm >= 0 ? S::ld(p[jm + a * ps]) : 0.0f;
+        su[iu(lx, ly, lz)] = u2[k];
+        sm[q] = m2[k];
+        sp[0][q] = q0[k]; sp[1][q] = q1[k]; sp[2][q] = q2[k];
     }
     __syncthreads();
     double e = 0.0, d = 0.0;
+#pragma unroll
     for (int k = 0; k < 2; ++k) {
         const int v = t + 256 * k, lx = v & 7, ly = (v >> 3) & 7, lz = v >> 6;
         const int q = i9(lx, ly, lz);
-        const uint8_t m = sm[q];
-        if (!(m & 1)) continue;
-        const int64_t gi = b * kBlockVox + v;
-        const double u0 = su[iu(lx, ly, lz)];
-        const double g0 = (m & 2) ? double(su[iu(lx + 1, ly, lz)]) - u0 : 0.0;
-        const double g1 = (m & 4) ? double(su[iu(lx, ly + 1, lz)]) - u0 : 0.0;
-        const double g2 = (m & 8) ? double(su[iu(lx, ly, lz + 1)]) - u0 : 0.0;
-        const double fv = f[gi], wv = w[gi];
-        const double r = u0 - fv;
-        e += sqrt((g0 * g0 + g1 * g1) + g2 * g2) + (l1 ? lambda * wv * fabs(r) : 0.5 * lambda * wv * r * r);
+        // (no branch on the masks: each would hold up the LDS reads after it)
+        const uint32_t m = m2[k];
         const int qx = i9(lx - 1, ly, lz), qy = i9(lx, ly - 1, lz), qz = i9(lx, ly, lz - 1);
-        double dv = 0.0;
-        dv += ((m & 2) ? double(sp[0][q]) : 0.0) - ((sm[qx] & 2) ? double(sp[0][qx]) : 0.0);
-        dv += ((m & 4) ? double(sp[1][q]) : 0.0) - ((sm[qy] & 4) ? double(sp[1][qy]) : 0.0);
-        dv += ((m & 8) ? double(sp[2][q]) : 0.0) - ((sm[qz] & 8) ? double(sp[2][qz]) : 0.0);
+        const float ux = su[iu(lx + 1, ly, lz)], uy = su[iu(lx, ly + 1, lz)], uz = su[iu(lx, ly, lz + 1)];
+        const float px = sp[0][qx], py = sp[1][qy], pz = sp[2][qz];
+        const uint32_t mx = sm[qx], my = sm[qy], mz = sm[qz];
+        const double u0 = u2[k], fv = f2[k], wv = w2[k], r = u0 - fv;
+        const double g0 = double(m & 2 ? ux : u2[k]) - u0, g1 = double(m & 4 ? uy : u2[k]) - u0,
+                     g2 = double(m & 8 ? uz : u2[k]) - u0;
+        const double ev = sqrt((g0 * g0 + g1 * g1) + g2 * g2) + (l1 ? lambda * wv * fabs(r) : 0.5 * lambda * wv * r * r);
+        double dv = 0.0, db;
+        dv += double(m & 2 ? q0[k] : 0.0f) - double(mx & 2 ? px : 0.0f);
+        dv += double(m & 4 ? q1[k] : 0.0f) - double(my & 4 ? py : 0.0f);
+        dv += double(m & 8 ? q2[k] : 0.0f) - double(mz & 8 ? pz : 0.0f);
         if (l1) {
             // minimum over u in [-1, 1] of -u d + lambda w |u - f|: at -1, f or 1
             const double lw = lambda * wv;
             const double c0 = -fv * dv, c1 = -dv + lw * fabs(1.0 - fv), c2 = dv + lw * fabs(1.0 + fv);
-            d += fmin(fmin(c0, c1), c2);
+            db = fmin(fmin(c0, c1), c2);
         } else {
-            d += -fv * dv - dv * dv / (2.0 * lambda * wv);
+            db = -fv * dv - dv * dv / (2.0 * lambda * wv);
         }
+        e += m & 1 ? ev : 0.0;
+        d += m & 1 ? db : 0.0;
     }
-    e = wave_sum(e);
-    d = wave_sum(d);
-    const int wave = t >> 6;
-    if ((t & 63) == 0) { se[wave] = e; sd[wave] = d; }
+    const double v = wave_sum2(e, d);
+    if ((t & 31) == 0) (t & 32 ? sd : se)[t >> 6] = v;
     __syncthreads();
     if (t == 0) {
         partials[2 * b] = ((se[0] + se[1]) + se[2]) + se[3];
@@ -289,9 +351,8 @@ __global__ __launch_bounds__(1024) void k_energy_final(int n, const double *__re
         d += (a.y + b.y) + (c.y + f.y);
     }
     for (; k < n; k += 1024) { e += pairs[k].x; d += pairs[k].y; }
-    e = wave_sum(e);
-    d = wave_sum(d);
-    if ((t & 63) == 0) { se[t >> 6] = e; sd[t >> 6] = d; }
+    const double v = wave_sum2(e, d);
+    if ((t & 31) == 0) (t & 32 ? sd : se)[t >> 6] = v;
     __syncthreads();
     if (t == 0) {
         e = d = 0.0;
@@ -306,6 +367,17 @@ template <class T> __global__ void k_fill(T *__restrict__ a, int64_t n, T v)
 {
     int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < n) a[i] = v;
+}
+
+__global__ __launch_bounds__(256) void k_zero_state(int64_t n4, int64_t ps, float *__restrict__ u,
+                                                    float *__restrict__ ubar, float *__restrict__ p)
+{
+    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (i >= n4) return;
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    reinterpret_cast<float4 *>(u)[i] = zero;
+    reinterpret_cast<float4 *>(ubar)[i] = zero;
+    for (int c = 0; c < 3; ++c) reinterpret_cast<float4 *>(p + c * ps)[i] = zero;
 }
 
 template <class S> __global__ void k_demote(const float *__restrict__ a, typename S::T *__restrict__ b, int64_t n, int rz)
@@ -597,16 +669,46 @@ template <class S> static int promote_state(dn_volume *v)
 
 int zero_state(dn_volume *v)
 {
+    const int64_t n4 = v->nb * kBlockVox / 4, ps = v->cap_blocks * kBlockVox;
+    from_zero(v);
+    if (n4 == 0) return DN_OK;
+    hipLaunchKernelGGL(k_zero_state, dim3(grid1(n4)), dim3(256), 0, v->stream, n4, ps, v->u, v->ubar[v->cur],
+                       v->p[v->cur]);
+    DN_HIP(hipGetLastError());
+    return DN_OK;
+}
+
+void from_zero(dn_volume *v)
+{
     v->p_off_zero = true;
     v->full_iters = 0;
-    hipStream_t st = v->stream;
-    const int64_t n = v->nb * kBlockVox, ps = v->cap_blocks * kBlockVox;
-    int rc;
-    if ((rc = fill<float>(st, v->u, n, 0.f))) return rc;
-    if ((rc = fill<float>(st, v->ubar[v->cur], n, 0.f))) return rc;
-    for (int a = 0; a < 3; ++a)
-        if ((rc = fill<float>(st, v->p[v->cur] + a * ps, n, 0.f))) return rc;
     v->state_storage = DN_F32;
+}
+
+int first_iteration(dn_volume *v, float tau, float lambda, float theta, int l1)
+{
+    const int64_t n4 = v->nb * kBlockVox / 4, ps = v->cap_blocks * kBlockVox;
+    const int n = 1 - v->cur;
+    if (n4 == 0) return DN_OK;
+    hipLaunchKernelGGL(k_cp_first<SF32>, dim3(grid1(n4)), dim3(256), 0, v->stream, n4, ps,
+                       reinterpret_cast<const uint32_t *>(v->emask), reinterpret_cast<const float4 *>(v->f),
+                       reinterpret_cast<const float4 *>(v->w), v->u, v->ubar[n], v->p[n], tau * lambda, theta, l1, 0u);
+    DN_HIP(hipGetLastError());
+    return DN_OK;
+}
+
+template <class S> static int first_lowp(dn_volume *v, const dn_reg_params *prm)
+{
+    using T = typename S::T;
+    const int64_t n4 = v->nb * kBlockVox / 4, ps = v->cap_blocks * kBlockVox;
+    const int n = 1 - v->cur;
+    hipLaunchKernelGGL(k_cp_first<S>, dim3(grid1(n4)), dim3(256), 0, v->stream, n4, ps,
+                       reinterpret_cast<const uint32_t *>(v->emask), reinterpret_cast<const float4 *>(v->f),
+                       reinterpret_cast<const float4 *>(v->w), (T *)v->u16, (T *)v->ubar16[n], (T *)v->p16[n],
+                       float(prm->tau) * float(prm->lambda), float(prm->theta),
+                       int(prm->data_term == DN_DATA_L1), uint32_t(v->lowp_iter++));
+    DN_HIP(hipGetLastError());
+    v->cur = n;
     return DN_OK;
 }
 
@@ -634,6 +736,9 @@ static int size_bucket(int64_t nb)
 }
 
 static int64_t tune_key(const dn_volume *v, int64_t sub) { return (int64_t(v->device) << 32) | sub; }
+
+// Long enough for the events' own time not to decide between small maps.
+static int trial_iterations(int64_t nb) { return int(std::min<int64_t>(48, std::max<int64_t>(6, 24576 / nb))); }
 
 static bool find_choice(std::map<int64_t, AutoChoice> &m, int64_t key, AutoChoice *out)
 {
@@ -665,7 +770,7 @@ static int autotune_single(dn_volume *v, const dn_reg_params *prm, int *choice)
     DN_HIP(hipEventCreate(&e1));
     float best_ms = 1e30f;
     AutoChoice best{DN_K_FUSED, 0};
-    const int trial = 6;
+    const int trial = trial_iterations(v->nb);
     for (int k : kTuned)
         for (int layout = 0; layout < 2; ++layout) {
             v->layout = layout;
@@ -693,12 +798,13 @@ static int autotune_single(dn_volume *v, const dn_reg_params *prm, int *choice)
 }
 
 // The same choice for 16-bit state storage, timed on the 16-bit kernels.
-// It runs only on a state just demoted from FP32 (the trials overwrite the
-// 16-bit buffers, which are then demoted again).
+// It runs only on a state just demoted from FP32, or zero (the trials
+// overwrite the 16-bit buffers, which are then demoted again).
 static std::map<int64_t, AutoChoice> g_auto_lowp;
 
-template <class S> static int autotune_lowp(dn_volume *v, const dn_reg_params *prm, int storage, int *choice)
+template <class S> static int autotune_lowp(dn_volume *v, const dn_reg_params *prm, bool zero, int *choice)
 {
+    const int storage = prm->storage;
     const int64_t key = tune_key(v, storage * 64 + size_bucket(v->nb));
     AutoChoice found;
     if (find_choice(g_auto_lowp, key, &found)) {
@@ -713,8 +819,12 @@ template <class S> static int autotune_lowp(dn_volume *v, const dn_reg_params *p
     const uint64_t seed_iter = v->lowp_iter;   // the trials are discarded, so are their seeds
     float best_ms = 1e30f;
     AutoChoice best{DN_K_FUSED, 0};
-    const int trial = 6;
+    const int trial = trial_iterations(v->nb);
     int rc = DN_OK;
+    if (zero) {                 // (the solve's own first iteration does without)
+        if ((rc = zero_state(v)) || (rc = demote_state<S>(v))) return rc;
+        v->state_storage = storage;
+    }
     for (int k : kTuned)
         for (int layout = 0; layout < 2 && !rc; ++layout) {
             v->layout = layout;
@@ -767,7 +877,13 @@ int dn_regularize(dn_volume *v, const dn_reg_params *prm, const float *u0, const
     const int64_t n = v->nb * kBlockVox, ps = v->cap_blocks * kBlockVox;
     const int storage = prm->storage;
     // initial state
-    if (prm->init == DN_INIT_ZERO) {
+    // from zero, the first iteration need not find the zeros in memory, unless
+    // it is the two-pass kernels' or a refinement sweep
+    const bool first = prm->init == DN_INIT_ZERO && prm->iters > 0 && v->nb > 0 &&
+                       (storage == DN_F32 ? prm->kernel != DN_K_TWOPASS : prm->iters > 1 && prm->refine_every != 1);
+    if (first) {
+        from_zero(v);
+    } else if (prm->init == DN_INIT_ZERO) {
         if ((rc = zero_state(v))) return rc;
     } else if (prm->init == DN_INIT_GIVEN) {
         if (n > 0) {
@@ -816,15 +932,17 @@ int dn_regularize(dn_volume *v, const dn_reg_params *prm, const float *u0, const
                           v->state_storage == DN_F16 ? "FP16" : "BF16");
                 return DN_E_INVALID;
             }
-            rc = storage == DN_F16 ? demote_state<SF16>(v) : demote_state<SBF16>(v);
-            if (rc) return rc;
+            if (!first) {
+                rc = storage == DN_F16 ? demote_state<SF16>(v) : demote_state<SBF16>(v);
+                if (rc) return rc;
+            }
             v->state_storage = storage;
             fresh16 = true;
         }
         if (prm->kernel == DN_K_AUTO && v->nb > 0) {
             if (fresh16) {
-                rc = storage == DN_F16 ? autotune_lowp<SF16>(v, prm, storage, &kernel)
-                                       : autotune_lowp<SBF16>(v, prm, storage, &kernel);
+                rc = storage == DN_F16 ? autotune_lowp<SF16>(v, prm, first, &kernel)
+                                       : autotune_lowp<SBF16>(v, prm, first, &kernel);
                 if (rc) return rc;
             } else {
                 AutoChoice found;
@@ -870,7 +988,16 @@ int dn_regularize(dn_volume *v, const dn_reg_params *prm, const float *u0, const
             v->acc_tau = th * v->acc_tau;
             v->acc_sigma = v->acc_sigma / th;
         }
-        if (storage == DN_F32) {
+        if (first && it == 0) {
+            if (storage == DN_F32) {
+                (void)still_state(v);
+                rc = first_iteration(v, float(step_prm.tau), float(step_prm.lambda), float(step_prm.theta),
+                                     prm->data_term == DN_DATA_L1);
+                v->cur = 1 - v->cur;
+            } else {
+                rc = storage == DN_F16 ? first_lowp<SF16>(v, &step_prm) : first_lowp<SBF16>(v, &step_prm);
+            }
+        } else if (storage == DN_F32) {
             rc = step_f32(v, &step_prm, kernel);
         } else {
             bool refine = (prm->refine_every > 0 && (it + 1) % prm->refine_every == 0) || it + 1 == prm->iters;
@@ -883,7 +1010,15 @@ int dn_regularize(dn_volume *v, const dn_reg_params *prm, const float *u0, const
             if ((rc = energy_current(v, prm->lambda, false, prm->data_term))) return rc;
             if ((rc = read_energy(v, ed))) return rc;
             double gap = ed[0] - ed[1];
-            if (!std::isfinite(gap)) { set_error("non-finite gap at iteration %d", it + 1); return DN_E_NUMERIC; }
+            if (!std::isfinite(gap)) {
+                set_error("non-finite gap at iteration %d", it + 1);
+                // (no sweep has written the FP32 state yet: it starts at zero)
+                if (first && storage != DN_F32 && !(prm->refine_every > 0 && it + 1 >= prm->refine_every)) {
+                    if ((rc = zero_state(v))) return rc;
+                    v->state_storage = storage;
+                }
+                return DN_E_NUMERIC;
+            }
             if (prm->gap_tol > 0 && gap <= prm->gap_tol * ed[0]) { ++it; stats.converged = 1; break; }
         }
     }
@@ -896,7 +1031,10 @@ int dn_regularize(dn_volume *v, const dn_reg_params *prm, const float *u0, const
         if (rc) return rc;
     }
     DN_HIP(hipEventRecord(ev1, st));
-    DN_HIP(hipEventSynchronize(ev1));
+    // after a 16-bit run the FP32 buffers hold the result: the output of
+    // the last sweep, or the promoted 16-bit state after an early stop
+    if ((rc = energy_current(v, prm->lambda, true, prm->data_term))) return rc;
+    if ((rc = read_energy(v, ed))) return rc;
     {
         float ms = 0.f;
         DN_HIP(hipEventElapsedTime(&ms, ev0, ev1));
@@ -904,10 +1042,6 @@ int dn_regularize(dn_volume *v, const dn_reg_params *prm, const float *u0, const
         (void)hipEventDestroy(ev0);
         (void)hipEventDestroy(ev1);
     }
-    // after a 16-bit run the FP32 buffers hold the result: the output of
-    // the last sweep, or the promoted 16-bit state after an early stop
-    if ((rc = energy_current(v, prm->lambda, true, prm->data_term))) return rc;
-    if ((rc = read_energy(v, ed))) return rc;
     stats.energy = ed[0];
     stats.dual = ed[1];
     stats.gap = ed[0] - ed[1];
