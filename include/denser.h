@@ -399,8 +399,9 @@ int dn_net_forward_static(const float *tiles_dev, int64_t n, const float *params
  * prediction is f + r (kind 0, a primal residual) or r (kind 1, a dual
  * component); targets_dev, mask_dev float [n][512] in the tile's centre
  * order (mask 0/1); grad_dev float [8241] (overwritten).  *loss_host
- * receives the loss (synchronises).  workspace_dev: dn_net_bytes(n, 1)
- * bytes. */
+ * receives the loss (synchronises; a page-locked word that the device can
+ * address is written by the last kernel, any other by a copy).
+ * workspace_dev: dn_net_bytes(n, 1) bytes. */
 int dn_net_loss_grad(const float *tiles_dev, int64_t n, const float *params_dev,
                      const float *targets_dev, const float *mask_dev, int32_t kind, float *grad_dev,
                      void *workspace_dev, size_t workspace_bytes, double *loss_host, void *hip_stream);

@@ -100,7 +100,7 @@ __global__ void k_gather(const int32_t *__restrict__ nbr, const float *__restric
 // fixed order (thread-strided, then a tree) into part[g]; then one
 // workgroup sums the parts in order.
 // The gradient of all 8241 parameters from the per-workgroup partials of
-// the three layers (parts[layer][p][27 * 256 + 16]), written to the
+// the three layers, written to the
 // canonical parameter layout and scaled by 1 / N (the partials are of the
 // loss before its division by N: every entry is linear in d3).  The sum over p has a fixed order: a
 // workgroup takes 32 consecutive partial entries (contiguous reads across
@@ -108,10 +108,13 @@ __global__ void k_gather(const int32_t *__restrict__ nbr, const float *__restric
 // partials (each in order, eight loads in flight), then the eight group
 // sums are added in group order.
 constexpr int kFinalEntries = 32, kFinalGroups = 8;
+// a workgroup's partial of each layer: weights [tap][co][ci], then biases
+constexpr int kPart1 = kTaps * kC * 2 + kC, kPart2 = kWPack + kC, kPart3 = kTaps * kC + 1;
 __global__ __launch_bounds__(256) void k_grad_final(const float *__restrict__ parts, int nparts,
                                                     const double *__restrict__ tile_loss,
                                                     const double *__restrict__ tile_count, int64_t ntiles,
-                                                    double *__restrict__ loss, float *__restrict__ grad)
+                                                    double *__restrict__ loss, double *__restrict__ host_loss,
+                                                    float *__restrict__ grad)
 {
     __shared__ float sg[kFinalGroups][kFinalEntries];
     __shared__ double sl[256], sc[256];
@@ -139,11 +142,14 @@ __global__ __launch_bounds__(256) void k_grad_final(const float *__restrict__ pa
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         loss[0] = sl[0] / N;
         loss[1] = inv_n;
+        if (host_loss) *host_loss = sl[0] / N;
     }
     const int el = threadIdx.x % kFinalEntries, grp = threadIdx.x / kFinalEntries;
     const int k = blockIdx.x * kFinalEntries + el;
-    const bool live = k < 3 * (kWPack + kC);
-    const int layer = live ? k / (kWPack + kC) : 0, idx = k - layer * (kWPack + kC);
+    const bool live = k < kPart1 + kPart2 + kPart3;
+    const int layer = k < kPart1 ? 0 : (k < kPart1 + kPart2 ? 1 : 2);
+    const int idx = layer == 0 ? k : (layer == 1 ? k - kPart1 : k - kPart1 - kPart2);
+    const int size = layer == 0 ? kPart1 : (layer == 1 ? kPart2 : kPart3);
     const int per = (nparts + kFinalGroups - 1) / kFinalGroups;
     const int p0 = grp * per, p1 = min(nparts, p0 + per);
     float a = 0.f;
@@ -153,11 +159,11 @@ __global__ __launch_bounds__(256) void k_grad_final(const float *__restrict__ pa
         for (; p + 8 <= p1; p += 8) {
             float q[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) q[e] = src[int64_t(p + e) * (kWPack + kC)];
+            for (int e = 0; e < 8; ++e) q[e] = src[int64_t(p + e) * size];
 #pragma unroll
             for (int e = 0; e < 8; ++e) a += q[e];
         }
-        for (; p < p1; ++p) a += src[int64_t(p) * (kWPack + kC)];
+        for (; p < p1; ++p) a += src[int64_t(p) * size];
     }
     sg[grp][el] = a;
     __syncthreads();
@@ -168,12 +174,12 @@ __global__ __launch_bounds__(256) void k_grad_final(const float *__restrict__ pa
     const int cout = layer == 2 ? 1 : 16, cin = layer == 0 ? 2 : 16;
     const int wbase = layer == 0 ? kW1 : (layer == 1 ? kW2 : kW3);
     const int bbase = layer == 0 ? kB1 : (layer == 1 ? kB2 : kB3);
-    if (idx < kWPack) {
-        const int t = idx / (kC * kC), co = (idx / kC) % kC, ci = idx % kC;
-        if (co < cout && ci < cin) grad[wbase + (co * cin + ci) * kTaps + t] = sum;
+    const int weights = kTaps * cin * cout;
+    if (idx < weights) {
+        const int t = idx / (cin * cout), co = (idx / cin) % cout, ci = idx % cin;
+        grad[wbase + (co * cin + ci) * kTaps + t] = sum;
     } else {
-        const int co = idx - kWPack;
-        if (co < cout) grad[bbase + co] = sum;
+        grad[bbase + idx - weights] = sum;
     }
 }
 
@@ -504,7 +510,8 @@ __global__ void k_voxel_pairs(const float *__restrict__ f, const float *__restri
 // and some 4800 vector instructions, with two waves per SIMD to overlap them.
 // Row tiles in linear order (a tap mask per voxel, an LDS read per MFMA, one
 // chain of MFMAs at a time) and a launch per axis: warm start of 5777 blocks
-// 588 us, now 448; a training step's forward at 256 tiles 27.2 us, now 20.6.
+// 588 us, now 448; a training step's forward at 256 tiles 27.2 us, now 20.6 (21.4
+// with the loss, which was a launch of 3.9).
 //
 // kTraining: the forward pass of a training step on n given tiles (f holds the
 // float tiles [n][2][1000]); the layer inputs are also written to global
@@ -553,6 +560,15 @@ __device__ __forceinline__ void gate_bits(const uint16_t *h, uint16_t *__restric
 }
 
 enum NetUse { kPrimal, kDual, kTraining };
+// what a training step reads and writes beside the tiles
+struct TrainIO {
+    uint16_t *x1cf, *h1cf, *h2cf, *gates;    // for the backward pass
+    const float *targets, *mask;             // [n][512]
+    int kind;
+    float *d3;                               // the loss's gradient, see loss_of_tile
+    uint16_t *d3cf;
+    double *tile_loss, *tile_count;
+};
 // Layer-1 input words: the planes -1 .. 10 of a grid with rows of 16 (10 and
 // zeros) and 11 rows a plane (10 and one of zeros), kInLead zeros before; the
 // (y, z) tap pairs of the four lane groups are then 16 banks apart.
@@ -560,12 +576,70 @@ constexpr int kInRow = 16, kInPlane = 176, kInLead = 20, kInWords = 2148;
 static_assert(kInLead > kInRow && kInWords % 4 == 0 &&
                   kInWords > kInLead + 10 + 10 * kInRow + 10 * kInPlane + kInRow + kInPlane + 2, "layer-1 input grid");
 __device__ __forceinline__ int in_word(int x, int y, int z) { return kInLead + x + kInRow * y + kInPlane * (z + 1); }
+// Compact-row index of tile voxel (x, y, z), and its decoding (false for
+// padding entries).
+__device__ __forceinline__ int row_index(int x, int y, int z) { return (x + 1) + 12 * (10 * z + y); }
+__device__ __forceinline__ bool row_voxel(int c, int &x, int &y, int &z)
+{
+    if (c >= 1200) return false;
+    const int xr = c % 12, r = c / 12;
+    x = xr - 1; y = r % 10; z = r / 10;
+    return xr >= 1 && xr <= 10;
+}
+
+// Masked squared loss of a tile, r of this thread's centre voxel given (512
+// threads), before the division by N = max(1, sum of the mask), which
+// k_grad_final forms and applies: d3 = N dL/dr on the centre (float [n][512])
+// and the same in the compact-row layout for the weight gradient of layer 3
+// (d3cf [n][1216], bfloat16, zero off the centre), the tile's sum of squared
+// errors and of the mask.  (A launch of its own took 3.9 us for 256 tiles.)
+__device__ __forceinline__ void loss_of_tile(const float *__restrict__ tiles, const TrainIO &io, int64_t tile, int v,
+                                             float r, uint8_t *lds /* 16-byte aligned, 2176 bytes */)
+{
+    double *sl = reinterpret_cast<double *>(lds), *sc = sl + 8;         // [8] each
+    uint16_t *sg = reinterpret_cast<uint16_t *>(lds + 128);             // [1024]
+    const int tv = ((v & 7) + 1) + 10 * (((v >> 3) & 7) + 1) + 100 * ((v >> 6) + 1);
+    const double m = io.mask[tile * 512 + v];
+    const double e = (io.kind == 0 ? double(tiles[tile * 2 * kT + tv]) : 0.0) + double(r) -
+                     double(io.targets[tile * 512 + v]);
+    double l = m != 0.0 ? e * e : 0.0, c = m;
+    const float gv = m != 0.0 ? float(2.0 * e) : 0.f;
+    io.d3[tile * 512 + v] = gv;
+    for (int k = v; k < kT; k += 512) sg[k] = 0;
+    __syncthreads();
+    sg[tv] = f2bf(gv);
+    for (int o = 32; o > 0; o >>= 1) {
+        l += __shfl_xor(l, o, 64);
+        c += __shfl_xor(c, o, 64);
+    }
+    if ((v & 63) == 0) {
+        sl[v >> 6] = l;
+        sc[v >> 6] = c;
+    }
+    __syncthreads();
+    uint16_t *dst = io.d3cf + tile * kRowVox;
+    for (int k = v; k < kRowVox; k += 512) {
+        uint16_t val = 0;
+        int x, y, z;
+        if (row_voxel(k, x, y, z)) val = sg[x + 10 * y + 100 * z];
+        dst[k] = val;
+    }
+    if (v == 0) {
+        double s = 0.0, t = 0.0;
+        for (int k = 0; k < 8; ++k) {
+            s += sl[k];
+            t += sc[k];
+        }
+        io.tile_loss[tile] = s;
+        io.tile_count[tile] = t;
+    }
+}
+
 template <NetUse kUse, int W>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_net_fwd(
     const int32_t *__restrict__ nbr, const uint32_t *__restrict__ pair, const float *__restrict__ f,
     const uint8_t *__restrict__ emask, int64_t nb, const uint16_t *__restrict__ lw, const float *__restrict__ params, int64_t ps,
-    float *__restrict__ out, uint16_t *__restrict__ x1cf, uint16_t *__restrict__ h1cf, uint16_t *__restrict__ h2cf,
-    uint16_t *__restrict__ gates)
+    float *__restrict__ out, TrainIO io)
 {
     constexpr bool kTrain = kUse == kTraining;
     constexpr int kAxes = kUse == kDual ? 3 : 1;
@@ -678,7 +752,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
                 const int ch = e / kPadVox, p = e - ch * kPadVox;
                 const int x = p % 12 - 1, y = (p / 12) % 12 - 1, z = p / 144 - 1;
                 const bool in = x >= 0 && x < 10 && y >= 0 && y < 10 && z >= 0 && z < 10;
-                x1cf[b * (2 * kPadVox) + e] = in ? uint16_t(x0[in_word(x, y, z)] >> (16 * ch)) : uint16_t(0);
+                io.x1cf[b * (2 * kPadVox) + e] = in ? uint16_t(x0[in_word(x, y, z)] >> (16 * ch)) : uint16_t(0);
             }
 
         // layer 1: 2 -> 16, ReLU.  Lane group g of MFMA m takes the (y, z)
@@ -720,8 +794,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         if constexpr (kTrain) {
             // layer inputs for the backward pass (read-only use of h1 until
             // the barrier after layer 2), and which ReLUs are open
-            copy_act_cl<kThreads>(h1, h1cf + b * (16 * kPadVox), tid);
-            gate_bits<kThreads>(h1, gates + b * (2 * kT), tid);
+            copy_act_cl<kThreads>(h1, io.h1cf + b * (16 * kPadVox), tid);
+            gate_bits<kThreads>(h1, io.gates + b * (2 * kT), tid);
         }
 
         if (next < items) fetch_words(next);
@@ -733,8 +807,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         });
         __syncthreads();
         if constexpr (kTrain) {
-            copy_act_cl<kThreads>(h2, h2cf + b * (16 * kPadVox), tid);
-            gate_bits<kThreads>(h2, gates + b * (2 * kT) + kT, tid);
+            copy_act_cl<kThreads>(h2, io.h2cf + b * (16 * kPadVox), tid);
+            gate_bits<kThreads>(h2, io.gates + b * (2 * kT) + kT, tid);
         }
 
         // the centre voxels this thread will write, and whether it does
@@ -801,7 +875,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             }
             const float rv = acc + bias3;
             if constexpr (kTrain) {
-                out[b * kBlockVox + c] = rv;
+                static_assert(!kTrain || kOwn == 1, "one centre voxel per thread");
+                loss_of_tile(f, io, b, tid, rv, reinterpret_cast<uint8_t *>(h1) + 4 * 9 * kPRow);
             } else {
                 float y1 = rv;
                 if constexpr (kUse == kPrimal) {
@@ -841,71 +916,6 @@ __global__ void k_pack_train(const float *__restrict__ params, uint16_t *__restr
 }
 
 __device__ __forceinline__ bool bf_pos(uint16_t h) { return !(h & 0x8000u) && (h & 0x7FFFu) != 0; }
-
-// Compact-row index of tile voxel (x, y, z), and its decoding (false for
-// padding entries).
-__device__ __forceinline__ int row_index(int x, int y, int z) { return (x + 1) + 12 * (10 * z + y); }
-__device__ __forceinline__ bool row_voxel(int c, int &x, int &y, int &z)
-{
-    if (c >= 1200) return false;
-    const int xr = c % 12, r = c / 12;
-    x = xr - 1; y = r % 10; z = r / 10;
-    return xr >= 1 && xr <= 10;
-}
-
-// Masked squared loss of one tile per workgroup (512 threads, one per
-// centre voxel), before the division by N = max(1, sum of the mask), which
-// k_grad_final forms and applies: d3 = N dL/dr on the centre
-// (float [n][512]) and the same in the compact-row layout for the weight
-// gradient of layer 3 (d3cf [n][1216], bfloat16, zero off the centre), the
-// tile's sum of squared errors and of the mask.
-__global__ __launch_bounds__(512) void k_loss_train(const float *__restrict__ tiles, const float *__restrict__ R,
-                                                    const float *__restrict__ targets, const float *__restrict__ mask,
-                                                    int64_t n, int kind, float *__restrict__ d3,
-                                                    uint16_t *__restrict__ d3cf, double *__restrict__ tile_loss,
-                                                    double *__restrict__ tile_count)
-{
-    __shared__ double sl[8], sc[8];
-    __shared__ uint16_t sg[kT];
-    const int64_t tile = blockIdx.x;
-    const int v = threadIdx.x;
-    const int cx = v & 7, cy = (v >> 3) & 7, cz = v >> 6;
-    const int tv = (cx + 1) + 10 * (cy + 1) + 100 * (cz + 1);
-    const double m = mask[tile * 512 + v];
-    const double e = (kind == 0 ? double(tiles[tile * 2 * kT + tv]) : 0.0) + double(R[tile * 512 + v]) -
-                     double(targets[tile * 512 + v]);
-    double l = m != 0.0 ? e * e : 0.0, c = m;
-    const float gv = m != 0.0 ? float(2.0 * e) : 0.f;
-    d3[tile * 512 + v] = gv;
-    for (int k = v; k < kT; k += 512) sg[k] = 0;
-    __syncthreads();
-    sg[tv] = f2bf(gv);
-    for (int o = 32; o > 0; o >>= 1) {
-        l += __shfl_xor(l, o, 64);
-        c += __shfl_xor(c, o, 64);
-    }
-    if ((v & 63) == 0) {
-        sl[v >> 6] = l;
-        sc[v >> 6] = c;
-    }
-    __syncthreads();
-    uint16_t *dst = d3cf + tile * kRowVox;
-    for (int k = v; k < kRowVox; k += 512) {
-        uint16_t val = 0;
-        int x, y, z;
-        if (row_voxel(k, x, y, z)) val = sg[x + 10 * y + 100 * z];
-        dst[k] = val;
-    }
-    if (v == 0) {
-        double s = 0.0, t = 0.0;
-        for (int k = 0; k < 8; ++k) {
-            s += sl[k];
-            t += sc[k];
-        }
-        tile_loss[tile] = s;
-        tile_count[tile] = t;
-    }
-}
 
 // Backward through layers 3 and 2 of one tile per iteration of a
 // workgroup, on MFMA: d2 = (W3 applied backwards to d3) gated by [h2 > 0],
@@ -1079,36 +1089,37 @@ __device__ __forceinline__ v4u lds8_a8(const uint16_t *p)
 // 32 voxels instead of 27 with one used row.  Partials in the
 // [tap][co][ci] layout (co = 0), bias db3 = sum of d3.
 constexpr int kD3Row = 2080;   // LDS entries of d3: 168 zero margin + 1728 + margin
-constexpr int kWgrad3Lds = 2 * 16 * kXRow + 2 * kD3Row + 4 * 256 + 4 * 4 * 32 * 16;
+constexpr int kWgrad3Lds = 2 * 16 * kXRow + 2 * kD3Row + 4 * 512;
+static_assert(4 * 8 * 32 * 16 <= 2 * 16 * kXRow, "the waves' sums lie where the tiles did");
 __device__ __forceinline__ void wgrad3_body(const uint16_t *__restrict__ X, const uint16_t *__restrict__ d3cf,
                                             int64_t n, float *__restrict__ partials, int wg, int ngroups,
                                             uint8_t *lds)
 {
     uint16_t *sx = reinterpret_cast<uint16_t *>(lds);                  // [16][kXRow]
     uint16_t *sd = sx + 16 * kXRow;                                     // [kD3Row]
-    float *sb = reinterpret_cast<float *>(sd + kD3Row);                 // [256]
-    float(*red)[32][16] = reinterpret_cast<float(*)[32][16]>(sb + 256);  // [4][32][16]
+    float *sb = reinterpret_cast<float *>(sd + kD3Row);                 // [512]
+    float(*red)[32][16] = reinterpret_cast<float(*)[32][16]>(sx);       // [8][32][16], after the last tile
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int i = lane & 15, g = lane >> 4;
-    for (int k = tid; k < 16 * kXRow / 8; k += 256) reinterpret_cast<uint4 *>(sx)[k] = make_uint4(0, 0, 0, 0);
-    for (int k = tid; k < kD3Row / 8; k += 256) reinterpret_cast<uint4 *>(sd)[k] = make_uint4(0, 0, 0, 0);
+    for (int k = tid; k < 16 * kXRow / 8; k += 512) reinterpret_cast<uint4 *>(sx)[k] = make_uint4(0, 0, 0, 0);
+    for (int k = tid; k < kD3Row / 8; k += 512) reinterpret_cast<uint4 *>(sd)[k] = make_uint4(0, 0, 0, 0);
     v4f acc[2] = {v4f{0.f, 0.f, 0.f, 0.f}, v4f{0.f, 0.f, 0.f, 0.f}};
     float bsum = 0.f;
     __syncthreads();
     constexpr int kXc = kPadVox / 8;
-    constexpr int kPer = (16 * kXc + 255) / 256;
-    constexpr int kDPer = (kRowVox + 255) / 256;
+    constexpr int kPer = (16 * kXc + 511) / 512;
+    constexpr int kDPer = (kRowVox + 511) / 512;
     uint4 nxt[kPer];
     uint16_t nd[kDPer];
     auto fetch = [&](int64_t tl) {
 #pragma unroll
         for (int e = 0; e < kPer; ++e) {
-            const int k = tid + 256 * e;
+            const int k = tid + 512 * e;
             if (k < 16 * kXc) nxt[e] = reinterpret_cast<const uint4 *>(X + tl * 16 * kPadVox)[k];
         }
 #pragma unroll
         for (int e = 0; e < kDPer; ++e) {
-            const int c = tid + 256 * e;
+            const int c = tid + 512 * e;
             nd[e] = c < kRowVox ? d3cf[tl * kRowVox + c] : uint16_t(0);
         }
     };
@@ -1116,13 +1127,13 @@ __device__ __forceinline__ void wgrad3_body(const uint16_t *__restrict__ X, cons
     for (int64_t tile = wg; tile < n; tile += ngroups) {
 #pragma unroll
         for (int e = 0; e < kPer; ++e) {
-            const int k = tid + 256 * e;
+            const int k = tid + 512 * e;
             if (k < 16 * kXc) scatter8(sx + (k & 1) * 8 * kXRow + 8, kXRow, k >> 1, nxt[e]);
         }
         // d3 from its compact rows onto the padded grid (zero elsewhere)
 #pragma unroll
         for (int e = 0; e < kDPer; ++e) {
-            const int c = tid + 256 * e;
+            const int c = tid + 512 * e;
             int x, y, z;
             if (c < kRowVox && row_voxel(c, x, y, z)) {
                 sd[168 + pad_index(x, y, z)] = nd[e];
@@ -1131,8 +1142,8 @@ __device__ __forceinline__ void wgrad3_body(const uint16_t *__restrict__ X, cons
         }
         __syncthreads();
         if (tile + ngroups < n) fetch(tile + ngroups);
-        // wave w takes the 32-voxel chunks w, w + 4, ...
-        for (int c0 = 32 * wave; c0 < kRowVox; c0 += 128) {
+        // wave w takes the 32-voxel chunks w, w + 8, ...
+        for (int c0 = 32 * wave; c0 < kRowVox; c0 += 256) {
             const int c = c0 + 8 * g;
             const int plane = c / 120, within = c - 120 * plane;
             const int pc = within + 12 + 144 * (plane + 1);          // padded index of entry c
@@ -1147,26 +1158,27 @@ __device__ __forceinline__ void wgrad3_body(const uint16_t *__restrict__ X, cons
             }
         }
         __syncthreads();
-        for (int c = tid; c < kRowVox; c += 256) {      // clear d3's entries for the next tile
+        for (int c = tid; c < kRowVox; c += 512) {      // clear d3's entries for the next tile
             int x, y, z;
             if (row_voxel(c, x, y, z)) sd[168 + pad_index(x, y, z)] = 0;
         }
     }
-    // the four waves' sums of each (tap, ci), then one partial per workgroup
+    // the eight waves' sums of each (tap, ci), then one partial per workgroup
     for (int h = 0; h < 2; ++h)
         for (int r = 0; r < 4; ++r) red[wave][16 * h + 4 * g + r][i] = acc[h][r];
     sb[tid] = bsum;
     __syncthreads();
-    float *out = partials + int64_t(wg) * (kWPack + kC);
-    for (int e = tid; e < kWPack + kC; e += 256) {
+    float *out = partials + int64_t(wg) * kPart3;
+    for (int e = tid; e < kTaps * kC; e += 512) {
         float v = 0.f;
-        if (e < kWPack) {
-            const int t = e / (kC * kC), co = (e / kC) % kC, ci = e % kC;
-            if (co == 0) v = ((red[0][t][ci] + red[1][t][ci]) + red[2][t][ci]) + red[3][t][ci];
-        } else if (e == kWPack) {
-            for (int k = 0; k < 256; ++k) v += sb[k];
-        }
+        for (int w = 0; w < 8; ++w) v += red[w][e / kC][e % kC];
         out[e] = v;
+    }
+    if (wave == 7) {
+        float v = 0.f;
+        for (int w = 0; w < 8; ++w) v += sb[64 * w + lane];
+        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+        if (lane == 0) out[kTaps * kC] = v;
     }
 }
 
@@ -1175,19 +1187,20 @@ __device__ __forceinline__ void wgrad3_body(const uint16_t *__restrict__ X, cons
 // as (output channels) x (54 (ci, t) columns in four MFMAs) x (32 voxels):
 // each column reads the input channel shifted by its own tap (the y and z
 // shifts keep the reads 8-byte aligned, x shifts per lane from x_shift).
-constexpr int kWgrad1Lds = 2 * 2 * kXRow + 2 * 16 * kDRow + 4 * 256 + 4 * 4 * 16 * 64;
+constexpr int kWgrad1Lds = 2 * 2 * kXRow + 2 * 16 * kDRow + 4 * 512;
+static_assert(4 * 8 * 16 * 64 <= 2 * 16 * kDRow, "the waves' sums lie where the tiles did");
 __device__ __forceinline__ void wgrad1_body(const uint16_t *__restrict__ X, const uint16_t *__restrict__ dY,
                                             int64_t n, float *__restrict__ partials, int wg, int ngroups,
                                             uint8_t *lds)
 {
     uint16_t *sx = reinterpret_cast<uint16_t *>(lds);                  // [2][kXRow]
     uint16_t *sd = sx + 2 * kXRow;                                      // [16][kDRow]
-    float *sb = reinterpret_cast<float *>(sd + 16 * kDRow);             // [256]
-    float(*red)[16][64] = reinterpret_cast<float(*)[16][64]>(sb + 256);  // [4][16][64]
+    float *sb = reinterpret_cast<float *>(sd + 16 * kDRow);             // [512]
+    float(*red)[16][64] = reinterpret_cast<float(*)[16][64]>(sd);       // [8][16][64], after the last tile
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int i = lane & 15, g = lane >> 4;
-    for (int k = tid; k < 2 * kXRow / 8; k += 256) reinterpret_cast<uint4 *>(sx)[k] = make_uint4(0, 0, 0, 0);
-    for (int k = tid; k < 16 * kDRow / 8; k += 256) reinterpret_cast<uint4 *>(sd)[k] = make_uint4(0, 0, 0, 0);
+    for (int k = tid; k < 2 * kXRow / 8; k += 512) reinterpret_cast<uint4 *>(sx)[k] = make_uint4(0, 0, 0, 0);
+    for (int k = tid; k < 16 * kDRow / 8; k += 512) reinterpret_cast<uint4 *>(sd)[k] = make_uint4(0, 0, 0, 0);
     v4f acc[4];
     for (int q = 0; q < 4; ++q) acc[q] = v4f{0.f, 0.f, 0.f, 0.f};
     float bsum = 0.f;
@@ -1202,12 +1215,12 @@ __device__ __forceinline__ void wgrad1_body(const uint16_t *__restrict__ X, cons
     __syncthreads();
     constexpr int kXc = kPadVox / 8, kDc = kRowVox / 8;
     constexpr int kChunks = 2 * kXc + 16 * kDc;
-    constexpr int kPer = (kChunks + 255) / 256;
+    constexpr int kPer = (kChunks + 511) / 512;
     uint4 nxt[kPer];
     auto fetch = [&](int64_t tl) {
 #pragma unroll
         for (int e = 0; e < kPer; ++e) {
-            const int k = tid + 256 * e;
+            const int k = tid + 512 * e;
             if (k < 2 * kXc) nxt[e] = reinterpret_cast<const uint4 *>(X + tl * 2 * kPadVox)[k];
             else if (k < kChunks) nxt[e] = reinterpret_cast<const uint4 *>(dY + tl * 16 * kRowVox)[k - 2 * kXc];
         }
@@ -1216,7 +1229,7 @@ __device__ __forceinline__ void wgrad1_body(const uint16_t *__restrict__ X, cons
     for (int64_t tile = wg; tile < n; tile += ngroups) {
 #pragma unroll
         for (int e = 0; e < kPer; ++e) {
-            const int k = tid + 256 * e;
+            const int k = tid + 512 * e;
             if (k < 2 * kXc) {
                 const int ch = k / kXc, r = k - ch * kXc;
                 reinterpret_cast<uint4 *>(sx + ch * kXRow + 8)[r] = nxt[e];
@@ -1227,8 +1240,8 @@ __device__ __forceinline__ void wgrad1_body(const uint16_t *__restrict__ X, cons
         }
         __syncthreads();
         if (tile + ngroups < n) fetch(tile + ngroups);
-        for (int c = tid >> 4; c < kRowVox; c += 16) bsum += bf2f(sd[(tid & 15) * kDRow + c]);
-        for (int c0 = 32 * wave; c0 < kRowVox; c0 += 128) {
+        for (int c = tid >> 4; c < kRowVox; c += 32) bsum += bf2f(sd[(tid & 15) * kDRow + c]);
+        for (int c0 = 32 * wave; c0 < kRowVox; c0 += 256) {
             const int c = c0 + 8 * g;
             const v8bf a = as_v8bf(*reinterpret_cast<const v4u *>(sd + i * kDRow + c));
             const int plane = c / 120, within = c - 120 * plane;
@@ -1243,34 +1256,34 @@ __device__ __forceinline__ void wgrad1_body(const uint16_t *__restrict__ X, cons
         __syncthreads();
     }
     // D[co][col]: lane holds column 16 q + i, rows co = 4g .. 4g + 3; the
-    // four waves' sums, then one partial per workgroup in [tap][co][ci]
+    // D[co][col]: lane holds column 16 q + i, rows co = 4g .. 4g + 3; the
+    // eight waves' sums, then one partial per workgroup in [tap][co][ci]
     for (int q = 0; q < 4; ++q)
         for (int r = 0; r < 4; ++r) red[wave][4 * g + r][16 * q + i] = acc[q][r];
     sb[tid] = bsum;
     __syncthreads();
-    float *out = partials + int64_t(wg) * (kWPack + kC);
-    for (int e = tid; e < kWPack + kC; e += 256) {
+    float *out = partials + int64_t(wg) * kPart1;
+    for (int e = tid; e < kTaps * kC * 2; e += 512) {
+        const int col = (e & 1) * kTaps + e / (2 * kC), co = (e >> 1) % kC;
         float v = 0.f;
-        if (e < kWPack) {
-            const int t = e / (kC * kC), co = (e / kC) % kC, ci = e % kC;
-            if (ci < 2) {
-                const int col = ci * kTaps + t;
-                v = ((red[0][co][col] + red[1][co][col]) + red[2][co][col]) + red[3][co][col];
-            }
-        } else {
-            const int co = e - kWPack;
-            for (int k = 0; k < 16; ++k) v += sb[k * 16 + co];
-        }
+        for (int w = 0; w < 8; ++w) v += red[w][co][col];
         out[e] = v;
+    }
+    if (tid < kC) {
+        float v = 0.f;
+        for (int k = 0; k < 32; ++k) v += sb[k * 16 + tid];
+        out[kTaps * kC * 2 + tid] = v;
     }
 }
 
 // The layer-1 and layer-3 weight gradients in one launch: workgroups
 // [0, g1) take layer 1, the rest layer 3.  Each is latency-bound with one
 // workgroup per compute unit; sharing one LDS allocation (the larger of the
-// two) lets a unit hold one of each, so the two run side by side.
+// two) lets a unit hold one of each, so the two run side by side.  8 waves
+// each: with 4, and partials in layer 2's shape, 17.8 us for 256 tiles, now
+// 11.9.
 constexpr int kWgrad13Lds = kWgrad1Lds > kWgrad3Lds ? kWgrad1Lds : kWgrad3Lds;
-__global__ __launch_bounds__(256) void k_wgrad13(const uint16_t *__restrict__ X1, const uint16_t *__restrict__ d1,
+__global__ __launch_bounds__(512) void k_wgrad13(const uint16_t *__restrict__ X1, const uint16_t *__restrict__ d1,
                                                  const uint16_t *__restrict__ X3, const uint16_t *__restrict__ d3,
                                                  int64_t n, float *__restrict__ parts1, float *__restrict__ parts3,
                                                  int g1)
@@ -1302,22 +1315,24 @@ constexpr int kRowVox2 = 1280;
 // leaves its z plane, where the two layouts are contiguous alike; the y and
 // z shifts keep X 8-byte aligned, the x shifts come from x_shifts).  One
 // workgroup per compute unit loops over tiles and keeps every tap's 16 x 16
-// block in registers; one partial [27][16][16] + [16] per workgroup.
+// block in registers, 8 waves for the first half of the K steps and 8 for the
+// second (8 waves for all: 17.5 us for 256 tiles, now 15.9); one partial
+// [27][16][16] + [16] per workgroup.
 template <int CI, int CO>
-__global__ __launch_bounds__(512) void k_wgrad_mfma(const uint16_t *__restrict__ X, const uint16_t *__restrict__ dY,
+__global__ __launch_bounds__(1024) void k_wgrad_mfma(const uint16_t *__restrict__ X, const uint16_t *__restrict__ dY,
                                                     int64_t n, float *__restrict__ partials)
 {
     __shared__ __align__(16) uint16_t sx[16 * kXRow2];
     __shared__ __align__(16) uint16_t sd[16 * kDRow2];
-    __shared__ float sb[512];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    __shared__ float sb[1024];
+    const int tid = threadIdx.x, wave = (tid >> 6) & 7, part = tid >> 9, lane = tid & 63;
     const int i = lane & 15, g = lane >> 4;
     // wave w: the taps t = 3w .. 3w + 2 of the (y, z) offset pair w (x
     // offsets -1, 0, +1, one read for the three); waves 0..2 also tap
     // 24 + w of pair 8 (y and z offsets +1)
     const int ky = wave % 3 - 1, kz = wave / 3 - 1;
-    for (int k = tid; k < 16 * kXRow2 / 8; k += 512) reinterpret_cast<uint4 *>(sx)[k] = make_uint4(0, 0, 0, 0);
-    for (int k = tid; k < 16 * kDRow2 / 8; k += 512) reinterpret_cast<uint4 *>(sd)[k] = make_uint4(0, 0, 0, 0);
+    for (int k = tid; k < 16 * kXRow2 / 8; k += 1024) reinterpret_cast<uint4 *>(sx)[k] = make_uint4(0, 0, 0, 0);
+    for (int k = tid; k < 16 * kDRow2 / 8; k += 1024) reinterpret_cast<uint4 *>(sd)[k] = make_uint4(0, 0, 0, 0);
     v4f acc[4];
     for (int j = 0; j < 4; ++j) acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
     float bsum = 0.f;
@@ -1326,12 +1341,12 @@ __global__ __launch_bounds__(512) void k_wgrad_mfma(const uint16_t *__restrict__
     // next tile's held in registers while the current one is computed
     constexpr int kXc = kPadVox / 8, kDc = kRowVox / 8;
     constexpr int kChunks = CI * kXc + CO * kDc;
-    constexpr int kPer = (kChunks + 511) / 512;
+    constexpr int kPer = (kChunks + 1023) / 1024;
     uint4 nxt[kPer];
     auto fetch = [&](int64_t tl) {
 #pragma unroll
         for (int e = 0; e < kPer; ++e) {
-            const int k = tid + 512 * e;
+            const int k = tid + 1024 * e;
             if (k < CI * kXc) nxt[e] = reinterpret_cast<const uint4 *>(X + tl * CI * kPadVox)[k];
             else if (k < kChunks) nxt[e] = reinterpret_cast<const uint4 *>(dY + tl * CO * kRowVox)[k - CI * kXc];
         }
@@ -1340,7 +1355,7 @@ __global__ __launch_bounds__(512) void k_wgrad_mfma(const uint16_t *__restrict__
     for (int64_t tile = blockIdx.x; tile < n; tile += gridDim.x) {
 #pragma unroll
         for (int e = 0; e < kPer; ++e) {
-            const int k = tid + 512 * e;
+            const int k = tid + 1024 * e;
             if (k < CI * kXc) {
                 scatter8(sx + (k & 1) * 8 * kXRow2 + 8, kXRow2, k >> 1, nxt[e]);
             } else if (k < kChunks) {
@@ -1350,11 +1365,11 @@ __global__ __launch_bounds__(512) void k_wgrad_mfma(const uint16_t *__restrict__
         }
         __syncthreads();
         if (tile + gridDim.x < n) fetch(tile + gridDim.x);
-        for (int c = tid >> 4; c < kRowVox; c += 32) bsum += bf2f(sd[(tid & 15) * kDRow2 + c]);
+        for (int c = tid >> 4; c < kRowVox; c += 64) bsum += bf2f(sd[(tid & 15) * kDRow2 + c]);
         const uint16_t *xrow = sx + i * kXRow2;
         // K steps: runs of 8 entries 64 apart for the four lane groups
         // (c = cb + j + 64 g over 1280 entries, the last 64 zero in dY)
-        for (int step = 0; step < kRowVox2 / 32; ++step) {
+        for (int step = part * (kRowVox2 / 64); step < (part + 1) * (kRowVox2 / 64); ++step) {
             const int c = 256 * (step >> 3) + 8 * (step & 7) + 64 * g;
             const v8bf a = as_v8bf(*reinterpret_cast<const v4u *>(sd + i * kDRow2 + c));
             const int plane = c / 120, within = c - 120 * plane;
@@ -1372,18 +1387,23 @@ __global__ __launch_bounds__(512) void k_wgrad_mfma(const uint16_t *__restrict__
         }
         __syncthreads();
     }
+    // the second half's sums to the first, through LDS
+    float *other = reinterpret_cast<float *>(sx);
+    if (part == 1)
+        for (int j = 0; j < 4; ++j) *reinterpret_cast<v4f *>(other + ((tid & 511) * 4 + j) * 4) = acc[j];
+    sb[tid] = bsum;
+    __syncthreads();
     float *out = partials + int64_t(blockIdx.x) * (kWPack + kC);
+    if (part == 0) for (int j = 0; j < 4; ++j) acc[j] += *reinterpret_cast<const v4f *>(other + (tid * 4 + j) * 4);
     // lane: column ci = i, rows co = 4g .. 4g + 3
     for (int j = 0; j < 4; ++j) {
         const int t = j < 3 ? 3 * wave + j : 24 + wave;
-        if (j < 3 || wave < 3)
+        if (part == 0 && (j < 3 || wave < 3))
             for (int r = 0; r < 4; ++r) out[(t * kC + 4 * g + r) * kC + i] = acc[j][r];
     }
-    sb[tid] = bsum;
-    __syncthreads();
     if (tid < kC) {
         float sum = 0.f;
-        for (int k = 0; k < 32; ++k) sum += sb[k * 16 + tid];
+        for (int k = 0; k < 64; ++k) sum += sb[k * 16 + tid];
         out[kWPack + tid] = sum;
     }
 }
@@ -1616,17 +1636,23 @@ int dn_net_loss_grad(const float *tiles, int64_t n, const float *params, const f
     // units' waves idle at 256 tiles: 20.6 and 15.4 us for the two kernels
     // against 27.2 and 23.5)
     const unsigned grid1w = unsigned(std::min<int64_t>(n, std::max(cus, 1)));
-    // weights, forward with the layer inputs kept
+    // weights; forward with the layer inputs kept, loss and its gradient on the centre
+    // a loss word that the device can write (pinned) spares the copy: with that
+    // and the loss in the forward pass a step of 256 tiles 141.6 -> 114.0 us
+    double *host_loss = nullptr;
+    if (loss_host) {
+        hipPointerAttribute_t at{};
+        if (hipPointerGetAttributes(&at, loss_host) == hipSuccess && at.type == hipMemoryTypeHost)
+            host_loss = static_cast<double *>(at.devicePointer);
+        else (void)hipGetLastError();
+    }
+    double *lsum = ws.misc;   // [0] loss, [1] 1 / N (written by k_grad_final)
+    const TrainIO io{ws.x1cf, ws.h1cf, ws.h2cf, ws.gates, targets, mask, int(kind), ws.d3, ws.d3cf, ws.tl, ws.tc};
     hipLaunchKernelGGL(k_pack_train, dim3(grid1(kLaneW + kL2M * 64 * 8)), dim3(256), 0, st, params, ws.lanew,
                        ws.lanef);
     hipLaunchKernelGGL((k_net_fwd<kTraining, 8>), dim3(grid1w), dim3(512), 0, st, (const int32_t *)nullptr,
                        (const uint32_t *)nullptr, tiles, (const uint8_t *)nullptr, n, ws.lanew, params, int64_t(0),
-                       ws.rc, ws.x1cf, ws.h1cf, ws.h2cf, ws.gates);
-    DN_HIP(hipGetLastError());
-    // loss and its gradient on the centre
-    double *lsum = ws.misc;   // [0] loss, [1] 1 / N (written by k_grad_final)
-    hipLaunchKernelGGL(k_loss_train, dim3(unsigned(n)), dim3(512), 0, st, tiles, ws.rc, targets, mask, n, int(kind),
-                       ws.d3, ws.d3cf, ws.tl, ws.tc);
+                       (float *)nullptr, io);
     DN_HIP(hipGetLastError());
     // input gradients of layers 3 and 2
     hipLaunchKernelGGL(k_net_bwd<8>, dim3(grid1w), dim3(512), 0, st, ws.d3, ws.gates, n, ws.lanef, params, ws.d2cf,
@@ -1635,13 +1661,15 @@ int dn_net_loss_grad(const float *tiles, int64_t n, const float *params, const f
     // weight gradients, one partial per workgroup and layer, summed in a fixed order
     const unsigned gw = unsigned(ws.nparts);
     const size_t lp = size_t(ws.nparts) * (kWPack + kC);
-    hipLaunchKernelGGL(k_wgrad13, dim3(2 * gw), dim3(256), 0, st, ws.x1cf, ws.d1cf, ws.h2cf, ws.d3cf, n, ws.parts,
+    hipLaunchKernelGGL(k_wgrad13, dim3(2 * gw), dim3(512), 0, st, ws.x1cf, ws.d1cf, ws.h2cf, ws.d3cf, n, ws.parts,
                        ws.parts + 2 * lp, int(gw));
-    hipLaunchKernelGGL((k_wgrad_mfma<16, 16>), dim3(gw), dim3(512), 0, st, ws.h1cf, ws.d2cf, n, ws.parts + lp);
-    hipLaunchKernelGGL(k_grad_final, dim3((3 * (kWPack + kC) + kFinalEntries - 1) / kFinalEntries), dim3(256), 0, st,
-                       ws.parts, ws.nparts, ws.tl, ws.tc, n, lsum, grad);
+    hipLaunchKernelGGL((k_wgrad_mfma<16, 16>), dim3(gw), dim3(1024), 0, st, ws.h1cf, ws.d2cf, n, ws.parts + lp);
+    hipLaunchKernelGGL(k_grad_final, dim3((kPart1 + kPart2 + kPart3 + kFinalEntries - 1) / kFinalEntries), dim3(256), 0, st,
+                       ws.parts, ws.nparts, ws.tl, ws.tc, n, lsum, host_loss, grad);
     DN_HIP(hipGetLastError());
-    if (loss_host) {
+    if (host_loss) {
+        DN_HIP(hipStreamSynchronize(st));
+    } else if (loss_host) {
         double h = 0.0;
         DN_HIP(hipMemcpyAsync(&h, lsum, 8, hipMemcpyDeviceToHost, st));
         DN_HIP(hipStreamSynchronize(st));
@@ -1699,8 +1727,7 @@ int dn_net_warm_start(dn_volume *v, const float *params, int32_t mode, double de
     hipLaunchKernelGGL(k_voxel_pairs, dim3(grid1(ps)), dim3(256), 0, st, v->f, v->w, ps, vp);
     auto fwd = mode == DN_WARM_DUAL ? k_net_fwd<kDual, 4> : k_net_fwd<kPrimal, 4>;
     hipLaunchKernelGGL(fwd, dim3(grid), dim3(256), 0, st, v->nbr, vp, v->f, v->emask, v->nb, lanew, params, ps,
-                       mode == DN_WARM_DUAL ? p0 : u0, (uint16_t *)nullptr, (uint16_t *)nullptr, (uint16_t *)nullptr,
-                       (uint16_t *)nullptr);
+                       mode == DN_WARM_DUAL ? p0 : u0, TrainIO{});
     DN_HIP(hipGetLastError());
     if (mode == DN_WARM_DUAL) {
         hipLaunchKernelGGL(k_warm_finish, dim3(grid1(ps)), dim3(256), 0, st, ps, ps, v->emask, v->f, p0, u0);

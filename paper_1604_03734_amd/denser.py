@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import threading
 from dataclasses import dataclass
 
 import numpy as np
@@ -372,14 +373,25 @@ def net_forward_static(tiles, params, out, stream=None):
                                       _stream_handle(stream)))
 
 
+_local = threading.local()
+
+
+def _loss_word():
+    """This thread's pinned double, which the device writes a step's loss to."""
+    import torch
+    if not hasattr(_local, "loss"):
+        _local.loss = torch.empty(1, dtype=torch.float64, pin_memory=True)
+    return _local.loss
+
+
 def net_loss_grad(tiles, params, targets, mask, grad, kind=0, stream=None, sync=True):
     """Loss (returned when sync, which waits for it) and gradient into grad."""
-    loss = ctypes.c_double(0)
     ws, nbytes = workspace("net_train", lib().dn_net_bytes(tiles.shape[0], 1))
+    loss = _loss_word() if sync else None
     check(lib().dn_net_loss_grad(_ptr(tiles), tiles.shape[0], _ptr(params), _ptr(targets), _ptr(mask),
-                                 int(kind), _ptr(grad), ws, nbytes, ctypes.byref(loss) if sync else None,
-                                 _stream_handle(stream)))
-    return loss.value if sync else None
+                                 int(kind), _ptr(grad), ws, nbytes,
+                                 ctypes.c_void_p(loss.data_ptr()) if sync else None, _stream_handle(stream)))
+    return loss.item() if sync else None
 
 
 def net_adam(params, grad, m, v, lr, step, beta1=0.9, beta2=0.999, eps=1e-8, stream=None):
