@@ -15,8 +15,8 @@ One step (timed, inputs already resident in HBM):
 value = allocated voxels x iterations / step time (voxel-iterations/s).
 
 The JSON line also carries the roofline of the dominant kernel (the fused
-iteration kernel, 48 algorithmic bytes per voxel-iteration, timed with HIP
-events on the volume's stream), the FP64 CPU oracle timed on one street as
+iteration kernel, 48 algorithmic bytes per voxel-iteration of the lines that
+it moves, timed with HIP events on the volume's stream), the FP64 CPU oracle timed on one street as
 the CPU baseline, and the time to a relative gap of 1e-3 of the plain and
 the warm-started solver.
 """
@@ -35,6 +35,18 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 ALG_BYTES_PER_VOXEL_ITER = 48  # u, ubar, p(3), f, w read; p(3), u, ubar written (FP32)
+
+
+def moved_share(D, volumes, kernel_id):
+    """Share of the FP32 state's 128-byte lines that an iteration moves: on
+    maps beyond the caches (272 MiB of state) every kernel but the one with 8
+    waves per block leaves lines without an observed voxel alone, and the
+    batched solver's launches likewise; else 1."""
+    n = sum(v.num_blocks for v in volumes)
+    if n * 512 * 44 <= 272 << 20 or kernel_id in (D.DN_K_TWOPASS, D.DN_K_FUSED, 257):
+        return 1.0
+    lines = sum(int((v.extract(D.DN_X_W) > 0).view(-1, 32).any(1).sum().item()) for v in volumes)
+    return lines / (n * 16)
 ALG_BYTES_PER_VOXEL_ITER_16 = 28  # the same with u, ubar, p stored in 16 bits (f, w FP32)
 HBM_PEAK_GBS = 8000.0
 
@@ -489,8 +501,9 @@ def batched_run(wl, submaps=64, iters=300, steps=2):
         ms.append(st.ms_loop / iters)
     nvox = bw.voxels()
     per = float(np.mean(ms))
-    ach = ALG_BYTES_PER_VOXEL_ITER * nvox / (per / 1000.0) / 1e9
     kid = st.kernel_used // 100
+    share = moved_share(D, bw.subs, 257 if kid == 257 else -1)
+    ach = ALG_BYTES_PER_VOXEL_ITER * share * nvox / (per / 1000.0) / 1e9
     out = {"submaps": submaps, "blocks": nvox // 512, "voxels": nvox, "iters": iters,
            "ms_per_iter": per, "voxel_iters_per_s": nvox / (per / 1000.0),
            "kernel": BATCH_KERNELS.get(kid, "k_cp_persistent"),
@@ -498,7 +511,8 @@ def batched_run(wl, submaps=64, iters=300, steps=2):
            "roofline": {"bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                         "frac": ach / HBM_PEAK_GBS,
                         "traffic": load_traffic(nvox, "batched", "f32", kid, st.layout_used),
-                        "alg_bytes_per_launch": ALG_BYTES_PER_VOXEL_ITER * nvox}}
+                        "moved_share": share,
+                        "alg_bytes_per_launch": ALG_BYTES_PER_VOXEL_ITER * share * nvox}}
     for v in bw.subs:
         v.close()
     return out
@@ -659,8 +673,14 @@ def main():
     value = nvox * args.iters / (ms_step / 1000.0)
     kern_ms = float(np.mean(loops))
     alg_bytes = ALG_BYTES_PER_VOXEL_ITER if args.storage == "f32" else ALG_BYTES_PER_VOXEL_ITER_16
-    achieved = alg_bytes * nvox / (kern_ms / 1000.0) / 1e9
     kernel_id = st.kernel_used // 100 if args.workload == "batched" else st.kernel_used
+    share = 1.0
+    if args.storage == "f32":
+        batched = args.workload == "batched"
+        share = moved_share(wl.D, wl.subs if batched else [wl.big],
+                            (257 if kernel_id == 257 else -1) if batched else kernel_id)
+    alg_bytes *= share
+    achieved = alg_bytes * nvox / (kern_ms / 1000.0) / 1e9
     traffic = load_traffic(nvox, args.workload, args.storage, kernel_id,
                            st.layout_used if args.workload == "batched" else None)
     if args.workload == "batched":
@@ -695,6 +715,7 @@ def main():
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
                      "traffic": traffic,
+                     "moved_share": share,
                      "alg_bytes_per_launch": alg_bytes * nvox,
                      "avg_launch_ms": kern_ms},
         "cp_voxel_iters_per_s": nvox / (kern_ms / 1000.0),

@@ -369,6 +369,24 @@ template <class T> __global__ void k_fill(T *__restrict__ a, int64_t n, T v)
     if (i < n) a[i] = v;
 }
 
+// A given dual into the state; *off = 1 if it is not zero outside Omega.
+__global__ __launch_bounds__(256) void k_copy_dual(int64_t n4, int64_t ps4, const uint32_t *__restrict__ em,
+                                                   const float4 *__restrict__ p0, float4 *__restrict__ p,
+                                                   int64_t *__restrict__ off)
+{
+    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (i >= n4) return;
+    const uint32_t m = em[i];
+    bool bad = false;
+    for (int c = 0; c < 3; ++c) {
+        const float4 q = p0[c * n4 + i];
+        p[c * ps4 + i] = q;
+        bad = bad || (!(m & 1u) && q.x != 0.0f) || (!(m & 0x100u) && q.y != 0.0f) || (!(m & 0x10000u) && q.z != 0.0f) ||
+              (!(m & 0x1000000u) && q.w != 0.0f);
+    }
+    if (bad) *off = 1;
+}
+
 __global__ __launch_bounds__(256) void k_zero_state(int64_t n4, int64_t ps, float *__restrict__ u,
                                                     float *__restrict__ ubar, float *__restrict__ p)
 {
@@ -877,6 +895,8 @@ int dn_regularize(dn_volume *v, const dn_reg_params *prm, const float *u0, const
     const int64_t n = v->nb * kBlockVox, ps = v->cap_blocks * kBlockVox;
     const int storage = prm->storage;
     // initial state
+    constexpr int kOffWord = 7;     // of the report (energies take the first two)
+    bool look = false;
     // from zero, the first iteration need not find the zeros in memory, unless
     // it is the two-pass kernels' or a refinement sweep
     const bool first = prm->init == DN_INIT_ZERO && prm->iters > 0 && v->nb > 0 &&
@@ -886,10 +906,23 @@ int dn_regularize(dn_volume *v, const dn_reg_params *prm, const float *u0, const
     } else if (prm->init == DN_INIT_ZERO) {
         if ((rc = zero_state(v))) return rc;
     } else if (prm->init == DN_INIT_GIVEN) {
+        // a given dual of a map whose lines may rest (still_state) is looked
+        // at as it is copied: a warm start's is zero outside Omega (202195
+        // blocks: 0.95 ms per iteration without, 0.87 with)
+        look = p0 && storage == DN_F32 && prm->kernel != DN_K_TWOPASS && prm->iters > 2 &&
+               streams_state(v->nb, sizeof(float)) && (reinterpret_cast<uintptr_t>(p0) & 15) == 0;
+        if (look) {
+            if ((rc = fill<int64_t>(st, report(v) + kOffWord, 1, 0))) return rc;
+            hipLaunchKernelGGL(k_copy_dual, dim3(grid1(n / 4)), dim3(256), 0, st, n / 4, ps / 4,
+                               reinterpret_cast<const uint32_t *>(v->emask), reinterpret_cast<const float4 *>(p0),
+                               reinterpret_cast<float4 *>(v->p[v->cur]), report(v) + kOffWord);
+            DN_HIP(hipGetLastError());
+        }
         if (n > 0) {
             DN_HIP(hipMemcpyAsync(v->u, u0, n * 4, hipMemcpyDeviceToDevice, st));
             DN_HIP(hipMemcpyAsync(v->ubar[v->cur], u0, n * 4, hipMemcpyDeviceToDevice, st));
             for (int a = 0; a < 3; ++a) {
+                if (look) continue;
                 if (p0) {
                     DN_HIP(hipMemcpyAsync(v->p[v->cur] + a * ps, p0 + a * n, n * 4, hipMemcpyDeviceToDevice, st));
                 } else if ((rc = fill<float>(st, v->p[v->cur] + a * ps, n, 0.f))) {
@@ -987,6 +1020,11 @@ int dn_regularize(dn_volume *v, const dn_reg_params *prm, const float *u0, const
             step_prm.theta = th;
             v->acc_tau = th * v->acc_tau;
             v->acc_sigma = v->acc_sigma / th;
+        }
+        if (look && it == 2) {       // (two full iterations are under way)
+            if ((rc = fetch_report(v, kOffWord + 1))) return rc;
+            v->p_off_zero = v->host_stage[kOffWord] == 0;
+            v->full_iters = 2;
         }
         if (first && it == 0) {
             if (storage == DN_F32) {

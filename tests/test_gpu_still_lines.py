@@ -46,6 +46,13 @@ def _run(D, kernel):
     solve(D.DN_INIT_GIVEN, u0, p0)
     solve(D.DN_INIT_CONTINUE)
     solve(D.DN_INIT_GIVEN, u0, gamma=0.5)
+    p0[:, to_dev(w == 0)] = 0      # zero off the observed voxels: seen as it is copied
+    solve(D.DN_INIT_GIVEN, u0, p0, gap_every=2)
+    solve(D.DN_INIT_KEEP)
+    p0[2, NB - 1, 511] = 0.25 if w[NB - 1, 511] == 0 else p0[2, NB - 1, 511]
+    p0[0, 0] = to_dev(np.where(w[0] == 0, np.float32(0.5), 0))
+    solve(D.DN_INIT_GIVEN, u0, p0)
+    solve(D.DN_INIT_KEEP)
     gv.load_fused(to_dev(f), to_dev(w2))
     solve(D.DN_INIT_CONTINUE)
     solve(D.DN_INIT_ZERO, data_term=D.DN_DATA_L1)
