@@ -15,8 +15,9 @@ One step (timed, inputs already resident in HBM):
 value = allocated voxels x iterations / step time (voxel-iterations/s).
 
 The JSON line also carries the roofline of the dominant kernel (the fused
-iteration kernel, 48 algorithmic bytes per voxel-iteration of the lines that
-it moves, timed with HIP events on the volume's stream), the FP64 CPU oracle timed on one street as
+iteration kernel, 48 algorithmic bytes per voxel-iteration, timed with HIP
+events on the volume's stream; moved_share is the share of the state's lines
+that an iteration moves, moved_gbs the rate of those alone), the FP64 CPU oracle timed on one street as
 the CPU baseline, and the time to a relative gap of 1e-3 of the plain and
 the warm-started solver.
 """
@@ -503,7 +504,7 @@ def batched_run(wl, submaps=64, iters=300, steps=2):
     per = float(np.mean(ms))
     kid = st.kernel_used // 100
     share = moved_share(D, bw.subs, 257 if kid == 257 else -1)
-    ach = ALG_BYTES_PER_VOXEL_ITER * share * nvox / (per / 1000.0) / 1e9
+    ach = ALG_BYTES_PER_VOXEL_ITER * nvox / (per / 1000.0) / 1e9
     out = {"submaps": submaps, "blocks": nvox // 512, "voxels": nvox, "iters": iters,
            "ms_per_iter": per, "voxel_iters_per_s": nvox / (per / 1000.0),
            "kernel": BATCH_KERNELS.get(kid, "k_cp_persistent"),
@@ -511,8 +512,8 @@ def batched_run(wl, submaps=64, iters=300, steps=2):
            "roofline": {"bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                         "frac": ach / HBM_PEAK_GBS,
                         "traffic": load_traffic(nvox, "batched", "f32", kid, st.layout_used),
-                        "moved_share": share,
-                        "alg_bytes_per_launch": ALG_BYTES_PER_VOXEL_ITER * share * nvox}}
+                        "moved_share": share, "moved_gbs": ach * share,
+                        "alg_bytes_per_launch": ALG_BYTES_PER_VOXEL_ITER * nvox}}
     for v in bw.subs:
         v.close()
     return out
@@ -679,7 +680,6 @@ def main():
         batched = args.workload == "batched"
         share = moved_share(wl.D, wl.subs if batched else [wl.big],
                             (257 if kernel_id == 257 else -1) if batched else kernel_id)
-    alg_bytes *= share
     achieved = alg_bytes * nvox / (kern_ms / 1000.0) / 1e9
     traffic = load_traffic(nvox, args.workload, args.storage, kernel_id,
                            st.layout_used if args.workload == "batched" else None)
@@ -715,7 +715,7 @@ def main():
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
                      "traffic": traffic,
-                     "moved_share": share,
+                     "moved_share": share, "moved_gbs": achieved * share,
                      "alg_bytes_per_launch": alg_bytes * nvox,
                      "avg_launch_ms": kern_ms},
         "cp_voxel_iters_per_s": nvox / (kern_ms / 1000.0),
