@@ -1219,13 +1219,17 @@ __global__ __launch_bounds__(256) void k_laser_accumulate(LGeo g, const float *_
                         if (e == kNone || id >= 0) break;
                     }
                 } else if (tag != ~0u) {
+                    // (waves replace each other's entries at any time: an
+                    // entry's two halves are read and written as one)
                     unsigned long long *at = seen + place(tag);
-                    const unsigned long long e = *at;
+                    const unsigned long long e =
+                        __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                     if (uint32_t(e >> 32) == tag) {
                         id = int32_t(uint32_t(e));
                     } else {
                         id = hash_lookup(slots, nslots, cap, bx, by, bz);
-                        *at = (unsigned long long)tag << 32 | uint32_t(id);
+                        __hip_atomic_store(at, (unsigned long long)tag << 32 | uint32_t(id), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
                     }
                 } else {
                     id = hash_lookup(slots, nslots, cap, bx, by, bz);
