@@ -1199,8 +1199,10 @@ __global__ __launch_bounds__(256) void k_laser_accumulate(LGeo g, const float *_
     }
     // Up to the parameter `safe` a cell's centre, at most 0.87 s from the
     // ray, is more than mu in front of the surface: psi = 1 without its
-    // distance.
-    const double safe = (r - g.mu - 2.0 * g.s) / (r + g.mu);
+    // distance.  At the parameter t the ray is t (r + mu) |D|^2 along D, and
+    // |D| is 1 for a rigid pose only.
+    const double dd = (D[0] * D[0] + D[1] * D[1]) + D[2] * D[2];
+    const double safe = (r - g.mu - 2.0 * g.s * fmax(1.0, sqrt(dd))) / ((r + g.mu) * dd);
     double now = 2.0;                    // the parameter at which the ray entered the cell (2: unknown)
     int32_t id = -1, moved = ~7;         // ~7: not in this block yet
     unsigned mine = 0;
@@ -1779,7 +1781,9 @@ int dn_fuse_laser(dn_volume *v, const float *pts, int64_t n, const double T[16])
         const double scale = std::ldexp(1.0, bits), inv = std::ldexp(1.0, -bits);
         int64_t *total = v->misc + kMiscObs;
         hipLaunchKernelGGL(k_laser_clear, dim3(grid1(nvox / 4)), dim3(256), 0, st, cnt, sum, nvox, total);
-        // (the whole map in the table: every block that a ray can reach has a tag)
+        // (the whole map in the table: every block that a ray can observe has a tag.  A
+        // voxel that observes is within r + mu of the sensor, whatever the pose: with
+        // k = |D|, the ray ends at k (r + mu), and eta >= -mu only up to (r + mu) / k)
         const bool all = v->nb <= kSeenAll && (g.maxd + g.mu) / (8.0 * g.s) <= kSeenRange;
         hipLaunchKernelGGL(all ? k_laser_accumulate<true> : k_laser_accumulate<false>, dim3(grid1(n), 2), dim3(256), 0,
                            st, g, pts, n, slots, v->hash_slots, v->hash_cap, reinterpret_cast<const int4 *>(v->coords),
