@@ -273,7 +273,7 @@ int dn_fuse_depth(dn_volume *vol, const float *depth_dev, const dn_intrinsics *K
  * voxel centre, o the sensor, D the world direction), observes
  * psi = min(1, eta / mu); one call applies all of its observations
  * together: f <- (w f + sum psi) / (w + k), w <- w + k (the sum in
- * float64).  Both synchronise.  DN_E_CAPACITY (volume unchanged) if n
+ * float64, or in fixed point with its digits).  Both synchronise.  DN_E_CAPACITY (volume unchanged) if n
  * exceeds max_points, the band cells max_candidates or the observations
  * max_observations. */
 int dn_alloc_laser(dn_volume *vol, const float *pts_dev, int64_t n, const double T_gs[16], int32_t *n_new_out);

@@ -999,8 +999,9 @@ static int make_geo(const dn_volume *v, const dn_intrinsics *K, const double *T,
 //   Fusion: the voxels met by rho in [0, r + mu] in allocated blocks with
 //   eta = r - (c - o) . D >= -mu give psi = min(1, eta / mu); one scan's
 //   observations are applied together, f <- (w f + sum psi) / (w + k),
-//   w <- w + k, the sum in float64 (a segmented reduction over the
-//   observations sorted by voxel).
+//   w <- w + k, the sum in fixed point on maps of up to kAccumBlocks blocks
+//   (LaserSums), else in float64 (a segmented reduction over the observations
+//   sorted by voxel).
 struct LGeo {
     double T[16];
     double s, mu, maxd;
@@ -1112,12 +1113,10 @@ __global__ void k_laser_obs_emit(LGeo g, const float *__restrict__ pts, int64_t 
 }
 
 // Fusion of a scan into a map of up to kAccumBlocks blocks: every voxel has
-// an accumulator in the scratch, a count of its observations and the sum of
-// 1 - psi over those in the band (in free space psi = 1).  The sum is a
-// 64-bit fixed-point number, scaled so that all n returns in one voxel still
-// fit: the result does not depend on the order of the additions, and its
-// rounding (2^-45 per observation for 65536 returns) is far below the
-// float32 result's.  Bound by latency along each ray: one lane walks a ray
+// an accumulator in the scratch: a count of its observations and the sum of
+// 1 - psi over those in the band (in free space psi = 1), in fixed point, so
+// that the result does not depend on the order of the additions (LaserSums).
+// Bound by latency along each ray: one lane walks a ray
 // and looks a block up when it enters it, in LDS, where a map of up to
 // kSeenAll blocks lies whole (a larger one's table keeps the blocks that its
 // workgroup met: neighbouring rays pass the same ones, but each costs one
@@ -1126,27 +1125,81 @@ __global__ void k_laser_obs_emit(LGeo g, const float *__restrict__ pts, int64_t 
 // observations, 65536 returns into 1400 blocks: 0.90 ms a scan before
 // (allocation included), 0.21 ms now.
 constexpr int64_t kAccumBlocks = 16384;
+
+// The two words of a voxel's accumulator.  `fine` is the sum with F bits after
+// the point, modulo 2^64; `coarse` the count in its upper b bits (n < 2^b
+// returns) and below it the sum of the same terms cut to q bits after the
+// point.  Each term, in [0, 2], loses less than one unit there, so the whole
+// sum is the coarse one plus less than n units, and `fine` tells how much: it
+// is exact.  With 60 bits (56 for the largest scans) a term keeps the digits
+// of psi in float64 up to the rounding of the distances; one word of 63 - b
+// bits lost them (f near the surface had 3 of float32's 7 digits after a scan
+// of 10^6 returns), and was 4 us of 130 quicker for 65536 returns.  Coarse
+// parts are added up over a run of lanes first: an atomic per observation for
+// them cost 4 us more.
+struct LaserSums {
+    int b, q, F;
+    static constexpr int kMaxB = 23;
+    explicit LaserSums(int64_t n)
+    {
+        b = 1;
+        while ((n >> b) > 0) ++b;
+        F = std::min(60, 125 - 3 * b);      // n units of the coarse sum are less than 2^63 fine ones
+        q = std::min(25, 63 - 2 * b);       // n terms of the coarse sum fit its 64 - b bits, and 64 of them 32
+    }
+    // (not negative: psi < 1)
+    __device__ __forceinline__ unsigned long long term(double psi) const
+    {
+        return (1ull << F) - (unsigned long long)(int64_t)(psi * double(1ull << F));
+    }
+    __device__ __forceinline__ uint32_t cut(unsigned long long term) const { return uint32_t(term >> (F - q)); }
+    // of up to 64 observations, given the sum of their cut terms
+    __device__ __forceinline__ unsigned long long coarse(unsigned count, uint32_t cuts) const
+    {
+        return (unsigned long long)count << (64 - b) | cuts;
+    }
+    __device__ __forceinline__ uint32_t count(unsigned long long c) const { return uint32_t(c >> (64 - b)); }
+    // the sum of psi over all observations
+    __device__ __forceinline__ double psi(unsigned long long c, unsigned long long fine) const
+    {
+        const unsigned long long cut = c & ((1ull << (64 - b)) - 1ull);
+        const int64_t a = (int64_t(count(c)) << q) - int64_t(cut);          // at least the sum, in 2^-q
+        const int64_t less = int64_t(fine - (cut << (F - q)));              // by that, in 2^-F
+        const int64_t top = int64_t(1) << (62 - (F - q));
+        const double unit = 1.0 / double(1ull << F);
+        if (a < top && a > -top) return double((a << (F - q)) - less) * unit;
+        return double(a) / double(1ull << q) - double(less) * unit;
+    }
+};
 constexpr int kSeen = 8192, kSeenAll = kSeen / 2;   // entries of the table
 constexpr double kSeenRange = 500.0;                // blocks from the sensor that its tags tell apart
 
-__global__ void k_laser_clear(uint32_t *__restrict__ cnt, unsigned long long *__restrict__ sum, int64_t nvox,
-                              int64_t *__restrict__ total)
+// Inclusive prefix sums over the lanes of a wave, without LDS.
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);      // from the lane 1, 2, 4 and 8 before, in rows of 16
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);      // the row before, to rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);      // the half before, to rows 2 and 3
+    return v;
+}
+
+// (sums: coarse and fine word of each voxel)
+__global__ void k_laser_clear(ulonglong2 *__restrict__ sums, int64_t nvox, int64_t *__restrict__ total)
 {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;   // 4 voxels
     if (i == 0) *total = 0;
     if (4 * i >= nvox) return;
-    reinterpret_cast<uint4 *>(cnt)[i] = make_uint4(0, 0, 0, 0);
-    reinterpret_cast<ulonglong2 *>(sum)[2 * i] = make_ulonglong2(0, 0);
-    reinterpret_cast<ulonglong2 *>(sum)[2 * i + 1] = make_ulonglong2(0, 0);
+    for (int k = 0; k < 4; ++k) sums[k * (nvox / 4) + i] = make_ulonglong2(0, 0);
 }
 
 template <bool kAll>
 __global__ __launch_bounds__(256) void k_laser_accumulate(LGeo g, const float *__restrict__ pts, int64_t n,
                                                           const int4 *__restrict__ slots, int64_t nslots, uint32_t cap,
-                                                          const int4 *__restrict__ coords, int nb, double scale,
-                                                          uint32_t *__restrict__ cnt,
-                                                          unsigned long long *__restrict__ sum,
-                                                          int64_t *__restrict__ total)
+                                                          const int4 *__restrict__ coords, int nb, LaserSums ls,
+                                                          ulonglong2 *__restrict__ sums, int64_t *__restrict__ total)
 {
     __shared__ unsigned long long seen[kSeen];      // block relative to the sensor's (high half) and its id
     __shared__ unsigned long long s_total;
@@ -1207,7 +1260,7 @@ __global__ __launch_bounds__(256) void k_laser_accumulate(LGeo g, const float *_
     int32_t id = -1, moved = ~7;         // ~7: not in this block yet
     unsigned mine = 0;
     while (__any(alive)) {
-        uint32_t vox = 0;
+        uint32_t vox = 0, cut = 0;
         bool hit = false;
         if (alive) {
             if ((moved & ~7) != 0) {
@@ -1239,14 +1292,19 @@ __global__ __launch_bounds__(256) void k_laser_accumulate(LGeo g, const float *_
             }
             if (id >= 0) {
                 vox = uint32_t(id) * uint32_t(kBlockVox) + uint32_t((w.k[0] & 7) + 8 * (w.k[1] & 7) + 64 * (w.k[2] & 7));
-                hit = true;
-                if (!(now < safe)) {
+                hit = now < safe;
+                if (!hit) {
                     double rho = 0.0;
 #pragma unroll
                     for (int q = 0; q < 3; ++q) rho += ((double(w.k[q]) + 0.5) * g.s - g.T[4 * q + 3]) * D[q];
                     const double eta = r - rho;
-                    hit = eta >= -g.mu;
-                    if (hit && eta < g.mu) atomicAdd(sum + vox, (unsigned long long)rint((1.0 - eta / g.mu) * scale));
+                    hit = eta >= g.mu;
+                    if (!hit && eta >= -g.mu) {
+                        const unsigned long long term = ls.term(eta / g.mu);
+                        atomicAdd(&sums[vox].y, term);
+                        cut = ls.cut(term);
+                        hit = true;
+                    }
                 }
                 if (hit) ++mine;
             }
@@ -1255,10 +1313,16 @@ __global__ __launch_bounds__(256) void k_laser_accumulate(LGeo g, const float *_
         // one addition per run of neighbouring lanes in the same voxel
         const uint64_t hits = __ballot(hit);
         if (hits == 0) continue;
-        const uint32_t before = __shfl_up(vox, 1, 64);
+        const uint32_t before = uint32_t(__builtin_amdgcn_update_dpp(0, int(vox), 0x138, 0xF, 0xF, false));   // lane - 1
         const bool head = hit && (lane == 0 || !((hits >> (lane - 1)) & 1ull) || before != vox);
         const uint64_t ends = (__ballot(head) | ~hits) >> lane >> 1;      // where a run after this lane ends
-        if (head) atomicAdd(cnt + vox, ends ? uint32_t(__ffsll((unsigned long long)ends)) : uint32_t(64 - lane));
+        const int len = ends ? __ffsll((unsigned long long)ends) : 64 - lane;
+        uint32_t run = 0;
+        if (__any(cut != 0)) {
+            const uint32_t to = wave_prefix(cut);
+            run = __shfl(to, lane + len - 1, 64) - (to - cut);
+        }
+        if (head) atomicAdd(&sums[vox].x, ls.coarse(unsigned(len), run));
     }
     if (mine) atomicAdd(&s_total, (unsigned long long)mine);
     __syncthreads();
@@ -1267,19 +1331,19 @@ __global__ __launch_bounds__(256) void k_laser_accumulate(LGeo g, const float *_
 
 // Apply the accumulators (unless the scan has more observations than the
 // volume takes) and hand their number to the host.
-__global__ void k_laser_apply_sums(const uint32_t *__restrict__ cnt, const unsigned long long *__restrict__ sum,
-                                   int64_t nvox, double inv_scale, const int64_t *__restrict__ total, int64_t most,
-                                   int64_t *host, float *__restrict__ f, float *__restrict__ w)
+__global__ void k_laser_apply_sums(const ulonglong2 *__restrict__ sums, int64_t nvox, LaserSums ls,
+                                   const int64_t *__restrict__ total, int64_t most, int64_t *host,
+                                   float *__restrict__ f, float *__restrict__ w)
 {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     const int64_t m = *total;
     if (i == 0) *host = m;
     if (m > most || i >= nvox) return;
-    const uint32_t c = cnt[i];
+    const ulonglong2 q = sums[i];
+    const uint32_t c = ls.count(q.x);
     if (c == 0) return;
     const double w0 = w[i], wn = w0 + double(c);
-    const double psi = double(c) - double(sum[i]) * inv_scale;
-    f[i] = float((w0 * double(f[i]) + psi) / wn);
+    f[i] = float((w0 * double(f[i]) + ls.psi(q.x, q.y)) / wn);
     w[i] = float(wn);
 }
 
@@ -1433,6 +1497,10 @@ static size_t volume_layout(const dn_volume_params &p, void *base, dn_volume *v)
         Bump m(nullptr, 0);
         carve_laser(m, p.max_points, p.max_observations);
         upd(m.off);
+        // the accumulators (16 bytes a voxel) of every map that three quarters of
+        // them fit beside the other needs
+        const size_t blocks = std::min({mb, size_t(kAccumBlocks), need / (12 * kBlockVox)});
+        upd(blocks * kBlockVox * 16);
     }
     char *scratch = b.take<char>(need);
     if (v) {
@@ -1772,23 +1840,19 @@ int dn_fuse_laser(dn_volume *v, const float *pts, int64_t n, const double T[16])
     const int4 *slots = reinterpret_cast<const int4 *>(v->hash[v->cur_hash]);
     Bump bump(v->scratch, v->scratch_bytes);
     const int64_t nvox = v->nb * int64_t(kBlockVox);
-    uint32_t *cnt = bump.take<uint32_t>(size_t(nvox));
-    unsigned long long *sum = bump.take<unsigned long long>(size_t(nvox));
-    if (v->nb <= kAccumBlocks && bump.fits()) {
-        // sums of at most n terms in [0, 2], each 2^bits per unit
-        int bits = 61;
-        while (bits > 0 && (n >> (61 - bits)) > 0) --bits;
-        const double scale = std::ldexp(1.0, bits), inv = std::ldexp(1.0, -bits);
+    ulonglong2 *sums = bump.take<ulonglong2>(size_t(nvox));
+    const LaserSums ls(n);
+    if (v->nb <= kAccumBlocks && ls.b <= LaserSums::kMaxB && bump.fits()) {
         int64_t *total = v->misc + kMiscObs;
-        hipLaunchKernelGGL(k_laser_clear, dim3(grid1(nvox / 4)), dim3(256), 0, st, cnt, sum, nvox, total);
+        hipLaunchKernelGGL(k_laser_clear, dim3(grid1(nvox / 4)), dim3(256), 0, st, sums, nvox, total);
         // (the whole map in the table: every block that a ray can observe has a tag.  A
         // voxel that observes is within r + mu of the sensor, whatever the pose: with
         // k = |D|, the ray ends at k (r + mu), and eta >= -mu only up to (r + mu) / k)
         const bool all = v->nb <= kSeenAll && (g.maxd + g.mu) / (8.0 * g.s) <= kSeenRange;
         hipLaunchKernelGGL(all ? k_laser_accumulate<true> : k_laser_accumulate<false>, dim3(grid1(n), 2), dim3(256), 0,
                            st, g, pts, n, slots, v->hash_slots, v->hash_cap, reinterpret_cast<const int4 *>(v->coords),
-                           int(v->nb), scale, cnt, sum, total);
-        hipLaunchKernelGGL(k_laser_apply_sums, dim3(grid1(nvox)), dim3(256), 0, st, cnt, sum, nvox, inv, total,
+                           int(v->nb), ls, sums, total);
+        hipLaunchKernelGGL(k_laser_apply_sums, dim3(grid1(nvox)), dim3(256), 0, st, sums, nvox, ls, total,
                            v->prm.max_observations, report(v), v->f, v->w);
         DN_HIP(hipGetLastError());
         if ((rc = fetch_report(v, 1))) return rc;
