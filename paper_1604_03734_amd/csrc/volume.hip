@@ -956,25 +956,36 @@ __device__ inline bool block_in_view(const Geo &g, const int4 c)
 }
 
 // Eq. 1 over the blocks in view.  Bound by launches and latency: a frame
-// touches a few MB.  The `share` workgroups of a group of 64 blocks each
-// test the whole group (a lane per block, every wave for itself) and take
-// every share-th visible one; testing again costs less than a launch of its
-// own with a list and a counter to clear (10.3 us a frame; in three launches
-// 12.0 us and two launch gaps).
+// touches a few MB.  Each block is tested once: lane t of workgroup g takes
+// block g + t G of a grid of G workgroups, so that blocks in view, which lie
+// together in the pool, are spread over the chip, and the workgroup updates
+// those of its up to 256 blocks that passed.  (XCD x takes the x-th eighth of
+// the g: the blocks of one line of `coords` are tested beside one L2.)  Times
+// of a frame, against a test and a list in launches of their own, and against
+// one launch in which every workgroup tested a whole group of 64 blocks for
+// itself: 503 blocks 11.5, 6.9 and now 6.0 us; 5370 13.9, 13.8 and 8.6; 187950
+// 18.7, 33.6 and 13.7; 375900 24.7, 59.4 and 17.6.
 __global__ __launch_bounds__(256) void k_fuse(Geo g, const float *__restrict__ depth,
-                                              const int32_t *__restrict__ coords, int64_t nb, int share,
+                                              const int32_t *__restrict__ coords, int64_t nb,
                                               float *__restrict__ f, float *__restrict__ w)
 {
-    const int64_t group = int64_t(blockIdx.x) / share;
-    const int mine = int(blockIdx.x) % share;
-    const int64_t mb = group * 64 + (threadIdx.x & 63);
-    uint64_t m = __ballot(mb < nb && block_in_view(g, reinterpret_cast<const int4 *>(coords)[min(mb, nb - 1)]));
-    for (int k = 0, turn = mine; m; ++k, m &= m - 1) {
-        if (k != turn) continue;
-        turn += share;
-        fuse_voxels<2>(g, depth, coords, group * 64 + __ffsll((unsigned long long)m) - 1, threadIdx.x, 256, f, w);
-    }
+    __shared__ uint64_t seen[4];
+    const int tid = threadIdx.x;
+    const int64_t first = int64_t(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;      // (the grid is a multiple of 8)
+    const int64_t mb = first + int64_t(tid) * gridDim.x;
+    const uint64_t mine = __ballot(mb < nb && block_in_view(g, reinterpret_cast<const int4 *>(coords)[min(mb, nb - 1)]));
+    if ((tid & 63) == 0) seen[tid >> 6] = mine;
+    __syncthreads();
+    for (int q = 0; q < 4; ++q)
+        for (uint64_t m = uint64_t(__builtin_amdgcn_readfirstlane(uint32_t(seen[q] >> 32))) << 32 |
+                          uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(seen[q])));
+             m; m &= m - 1) {
+            const int at = 64 * q + __ffsll((unsigned long long)m) - 1;
+            fuse_voxels<2>(g, depth, coords, first + int64_t(at) * gridDim.x, tid, 256, f, w);
+        }
 }
+// (375900 blocks: 1024 workgroups 17.4 us, 4096 18.6, 8192 22.6; 5370: 8.4, 11.9, 14.4)
+constexpr int64_t kFuseGrid = 2048;
 
 static int make_geo(const dn_volume *v, const dn_intrinsics *K, const double *T, Geo &g)
 {
@@ -1793,10 +1804,8 @@ int dn_fuse_depth(dn_volume *v, const float *depth, const dn_intrinsics *K, cons
     int rc = make_geo(v, K, T, g);
     if (rc) return rc;
     if (v->nb == 0) return DN_OK;
-    // a workgroup for each block of a small map's groups, fewer where most groups are out of view
-    const int share = v->nb <= 16384 ? 32 : 4;
-    hipLaunchKernelGGL(k_fuse, dim3(grid1(v->nb, 64) * unsigned(share)), dim3(256), 0, v->stream, g, depth, v->coords,
-                       v->nb, share, v->f, v->w);
+    const int64_t grid = (std::max(std::min(v->nb, kFuseGrid), (v->nb + 255) / 256) + 7) / 8 * 8;
+    hipLaunchKernelGGL(k_fuse, dim3(unsigned(grid)), dim3(256), 0, v->stream, g, depth, v->coords, v->nb, v->f, v->w);
     DN_HIP(hipGetLastError());
     v->emask_nb = -1;
     return DN_OK;
