@@ -640,7 +640,21 @@ extern "C" int dn_regularize_batch(dn_volume *const *vols, int32_t n, const dn_r
             v0->acc_tau = th * v0->acc_tau;
             v0->acc_sigma = v0->acc_sigma / th;
         }
-    // the energies of all sub-maps, then one wait for them
+    // the energies of all sub-maps, then one wait for them; one wait each where
+    // volumes report to the same words
+    std::vector<const int64_t *> words(n);
+    for (int i = 0; i < n; ++i) words[i] = report(vols[i]);
+    std::sort(words.begin(), words.end());
+    bool shared = false;
+    for (int i = 1; i < n; ++i) shared = shared || words[i] < words[i - 1] + 2;
+    std::vector<double> ed(2 * size_t(n));
+    auto read = [&](int i) {
+        hipStream_t keep = vols[i]->stream;
+        vols[i]->stream = st;
+        const int erc = read_energy(vols[i], &ed[2 * i]);
+        vols[i]->stream = keep;
+        return erc;
+    };
     for (int i = 0; i < n; ++i) {
         dn_volume *v = vols[i];
         v->cur = (v->cur + prm->iters) & 1;
@@ -648,25 +662,19 @@ extern "C" int dn_regularize_batch(dn_volume *const *vols, int32_t n, const dn_r
         v->stream = st;
         rc = energy_current(v, prm->lambda, true, prm->data_term);
         v->stream = keep;
-        if (rc) return rc;
+        if (rc || (shared && (rc = read(i)))) return rc;
     }
     for (int i = 0; i < n; ++i) {
-        dn_volume *v = vols[i];
-        hipStream_t keep = v->stream;
-        v->stream = st;
-        double ed[2] = {0, 0};
-        rc = read_energy(v, ed);
-        v->stream = keep;
-        if (rc) return rc;
+        if (!shared && (rc = read(i))) return rc;
         if (out) {
             dn_reg_stats &s = out[i];
             s = dn_reg_stats{};
-            s.energy = ed[0];
-            s.dual = ed[1];
-            s.gap = ed[0] - ed[1];
-            s.rel_gap = ed[0] != 0.0 ? s.gap / ed[0] : 0.0;
+            s.energy = ed[2 * i];
+            s.dual = ed[2 * i + 1];
+            s.gap = s.energy - s.dual;
+            s.rel_gap = s.energy != 0.0 ? s.gap / s.energy : 0.0;
             s.iters_run = prm->iters;
-            s.converged = prm->gap_tol > 0 && s.gap <= prm->gap_tol * ed[0];
+            s.converged = prm->gap_tol > 0 && s.gap <= prm->gap_tol * s.energy;
             s.ms_loop = ms;
             s.kernel_used = ch.nt * 100 + ch.wg_per_cu;
             s.layout_used = (ch.pool ? 1 : 0) | (ch.xcd ? 0 : 2);
