@@ -172,6 +172,8 @@ int first_iteration(dn_volume *v, float tau, float lambda, float theta, int l1);
 int energy_current(dn_volume *v, double lambda, bool use_f32, int data_term);
 int read_energy(dn_volume *v, double out[2]);
 int reduce_pairs(dn_volume *v, int64_t n);
+// what DN_K_AUTO takes from now on for volumes of v's device and size (to a power of two)
+void remember_choice(const dn_volume *v, int storage, int kernel, int layout);
 // volume.hip
 int volume_sync(dn_volume *v);
 int read_back(dn_volume *v, const void *dev, size_t bytes);   // into v->host_stage, synchronises

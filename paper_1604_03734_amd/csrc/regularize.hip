@@ -743,7 +743,7 @@ struct AutoChoice { int kernel; int layout; };
 // 12 % behind) are not tried.
 constexpr int kTuned[] = {DN_K_FUSED, DN_K_FUSED256, DN_K_FUSED128, DN_K_FUSED64};
 // Keyed by (device, size bucket); the tuners of all threads share them.
-static std::map<int64_t, AutoChoice> g_auto_kernel;
+static std::map<int64_t, AutoChoice> g_auto_kernel, g_auto_lowp;     // FP32 state, 16-bit state
 static std::mutex g_auto_mutex;
 
 static int size_bucket(int64_t nb)
@@ -773,10 +773,11 @@ static bool find_choice(std::map<int64_t, AutoChoice> &m, int64_t key, AutoChoic
     return true;
 }
 
-static void store_choice(std::map<int64_t, AutoChoice> &m, int64_t key, AutoChoice c)
+void remember_choice(const dn_volume *v, int storage, int kernel, int layout)
 {
+    const bool low = storage != DN_F32;
     std::lock_guard<std::mutex> lk(g_auto_mutex);
-    m[key] = c;
+    (low ? g_auto_lowp : g_auto_kernel)[tune_key(v, (low ? storage * 64 : 0) + size_bucket(v->nb))] = AutoChoice{kernel, layout};
 }
 
 static int autotune_single(dn_volume *v, const dn_reg_params *prm, int *choice)
@@ -816,7 +817,7 @@ static int autotune_single(dn_volume *v, const dn_reg_params *prm, int *choice)
         }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    store_choice(g_auto_kernel, key, best);
+    remember_choice(v, DN_F32, best.kernel, best.layout);
     *choice = best.kernel;
     v->layout = best.layout;
     return zero_state(v);
@@ -825,7 +826,6 @@ static int autotune_single(dn_volume *v, const dn_reg_params *prm, int *choice)
 // The same choice for 16-bit state storage, timed on the 16-bit kernels.
 // It runs only on a state just demoted from FP32, or zero (the trials
 // overwrite the 16-bit buffers, which are then demoted again).
-static std::map<int64_t, AutoChoice> g_auto_lowp;
 
 template <class S> static int autotune_lowp(dn_volume *v, const dn_reg_params *prm, bool zero, int *choice)
 {
@@ -870,7 +870,7 @@ template <class S> static int autotune_lowp(dn_volume *v, const dn_reg_params *p
     v->cur = cur;
     v->lowp_iter = seed_iter;
     if (rc) return rc;
-    store_choice(g_auto_lowp, key, best);
+    remember_choice(v, storage, best.kernel, best.layout);
     *choice = best.kernel;
     v->layout = best.layout;
     return demote_state<S>(v);
