@@ -28,7 +28,7 @@ def _volume(D, nb, extent):
     rng = np.random.default_rng(nb)
     w[rng.random(nb) < 0.2] = 0
     w.reshape(-1, 32)[rng.random(nb * 16) < 0.3] = 0
-    gv = D.Volume(0.1, 0.3, 10.0, nb, 14, 256, max_points=0, max_candidates=max(nb, 64))
+    gv = D.Volume(0.1, 0.3, 10.0, nb, 16, 256, max_points=0, max_candidates=max(nb, 64))
     gv.insert_blocks(to_dev(coords.astype(np.int32)), keep_order=True)
     gv.load_fused(to_dev(np.asarray(f, np.float32).reshape(nb, 512)), to_dev(w))
     return gv, to_dev(np.asarray(f, np.float32).reshape(nb, 512)), w
