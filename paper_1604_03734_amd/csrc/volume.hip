@@ -455,7 +455,8 @@ __global__ __launch_bounds__(kBandPoints) void k_band(Band band, int64_t n, cons
         mine = (unsigned long long)band(i, [&](uint64_t key) {
             uint32_t h = key_mix(key) & (kBandSet - 1);
             for (int probe = 0; probe < 32; ++probe, h = (h + 1) & (kBandSet - 1)) {
-                unsigned long long old = set[h];
+                // (other waves fill slots meanwhile: a key is read as one)
+                unsigned long long old = __hip_atomic_load(set + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 if (old == kNoKey) old = atomicCAS(set + h, (unsigned long long)kNoKey, (unsigned long long)key);
                 if (old == key) return;
                 if (old == kNoKey) break;
