@@ -162,8 +162,9 @@ typedef struct {
     double ms_loop;          /* HIP-event time of the iteration loop on the
                                 volume's stream (gap checks included)        */
     int32_t kernel_used;     /* DN_K_* that ran (after autotuning), or 4, 5    */
-    int32_t layout_used;     /* bit 0: pool order (else Morton order); bit 1:
-                                plain workgroup map (else XCD chunks)        */
+    int32_t layout_used;     /* bit 0: pool order (else Morton order); the other
+                                bits are 0 (workgroups take blocks in XCD
+                                chunks)                                      */
 } dn_reg_stats;
 
 /* ------------------------------------------------------------ lifecycle */

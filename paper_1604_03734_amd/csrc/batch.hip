@@ -6,9 +6,9 @@
 // and p of the previous iteration).  The other candidate launches one
 // iteration of every sub-map per kernel, the launch boundary ordering the
 // iterations.  Either is captured in a HIP graph together with the reset
-// of the barrier state and replayed.  Kernel, grid size and the
-// item-to-workgroup mapping are picked by timing short trial runs
-// (autotuner), cached per problem size.
+// of the barrier state and replayed.  Kernel, grid size and the order of
+// the items are picked by timing short trial runs (autotuner), cached per
+// problem size.
 #include <cstring>
 #include <cstdlib>
 
@@ -40,7 +40,6 @@ struct BatchArgs {
     const int2 *items;        // (volume, block) in processing order
     int64_t n_items;
     int32_t iters;
-    int32_t xcd_chunks;       // 1: each XCD works on one contiguous item chunk
     float sigma, tau, lambda, theta;
     double gamma;             // > 0: accelerated schedule from (tau, sigma)
     double tau0, sigma0;      // schedule state at the start of the launch
@@ -165,7 +164,7 @@ __device__ __forceinline__ void item_args(const BatchArgs &a, const VolDesc *__r
     const int c = (__builtin_amdgcn_readfirstlane(d.cur) + it) & 1;
     const int64_t ps = int64_t(__builtin_amdgcn_readfirstlane(uint32_t(d.pstride))) |
                        (int64_t(__builtin_amdgcn_readfirstlane(uint32_t(uint64_t(d.pstride) >> 32))) << 32);
-    A.nb = 0; A.pstride = ps; A.nbr = uni(d.nbr); A.em4 = uni(d.em4); A.order = nullptr; A.xcd = 0;
+    A.nb = 0; A.pstride = ps; A.nbr = uni(d.nbr); A.em4 = uni(d.em4); A.order = nullptr;
     A.f = uni(d.f); A.w = uni(d.w); A.u = uni(d.u);
     A.ubar_in = uni(d.ubar[c]); A.ubar_out = uni(d.ubar[1 - c]);
     A.p_in = uni(d.p[c]); A.p_out = uni(d.p[1 - c]); A.u32 = nullptr; A.ubar32 = nullptr; A.p32 = nullptr;
@@ -204,7 +203,7 @@ __global__ __launch_bounds__(64 * kBatchWaves) __attribute__((amdgpu_waves_per_e
         }
         if (it < a.first) continue;
         int64_t lo = 0, hi = a.n_items, stride = G, cx = 0;
-        if (a.xcd_chunks && G >= 8) {
+        if (G >= 8) {
             // workgroup g runs on XCD g % 8; XCD x owns items [x*chunk, (x+1)*chunk)
             // and has exactly (G - x + 7) / 8 workgroups to stride over them
             const int64_t chunk = (a.n_items + 7) / 8;
@@ -263,7 +262,7 @@ __global__ __launch_bounds__(64 * kBatchWaves) void k_cp_batch_step(BatchArgs a,
                                                        float tau, float theta)
 {
     __shared__ CPShared<kBatchWaves> sh;
-    const int64_t slot = block_slot(blockIdx.x, a.n_items, a.xcd_chunks);
+    const int64_t slot = xcd_slot(blockIdx.x, a.n_items);
     if (slot >= a.n_items) return;
     const int2 bi = load_item(items, slot);
     CPArgs<SF32> A;
@@ -285,7 +284,7 @@ struct BatchCtx {
     // key of the captured graph
     const void *k_items = nullptr;
     int64_t k_n = -1;
-    int k_iters = -1, k_grid = -1, k_xcd = -1, k_nt = -1, k_l1 = -1, k_still = -1, k_first = -1;
+    int k_iters = -1, k_grid = -1, k_nt = -1, k_l1 = -1, k_still = -1, k_first = -1;
     float k_prm[4] = {0, 0, 0, 0};
     double k_acc[3] = {0, 0, 0};
     const void *vols_ptr = nullptr;
@@ -296,8 +295,8 @@ struct BatchCtx {
 static std::map<int, BatchCtx> g_batch;     // by device
 static std::mutex g_batch_mutex;             // held for a whole batched call
 
-// (kernel variant, workgroups per CU, XCD-chunked items, pool order)
-struct TuneChoice { int nt; int wg_per_cu; int xcd; int pool; };
+// (kernel variant, workgroups per CU, pool order)
+struct TuneChoice { int nt; int wg_per_cu; int pool; };
 static std::map<int64_t, TuneChoice> g_tuned;   // by (device, size bucket)
 
 // The workspace of one batched call: volume descriptors, work items and
@@ -374,7 +373,7 @@ static int launch_graph(BatchCtx &c, hipStream_t st, const BatchArgs &a, int gri
     }
     bool same = c.exec && c.k_items == a.items && c.k_n == a.n_items && c.k_iters == a.iters && c.k_grid == grid &&
                 c.k_nt == nt && c.k_l1 == a.l1 && c.k_still == a.still && c.k_first == a.first &&
-                c.k_xcd == a.xcd_chunks && c.k_prm[0] == a.sigma && c.k_prm[1] == a.tau &&
+                c.k_prm[0] == a.sigma && c.k_prm[1] == a.tau &&
                 c.k_prm[2] == a.lambda && c.k_prm[3] == a.theta && c.vols_ptr == a.vols && c.bar_ptr == a.bar &&
                 c.k_acc[0] == a.gamma && c.k_acc[1] == a.tau0 && c.k_acc[2] == a.sigma0;
     if (!same) {
@@ -389,7 +388,7 @@ static int launch_graph(BatchCtx &c, hipStream_t st, const BatchArgs &a, int gri
             return DN_E_DEVICE;
         }
         DN_HIP(hipGraphInstantiate(&c.exec, c.graph, nullptr, nullptr, 0));
-        c.k_items = a.items; c.k_n = a.n_items; c.k_iters = a.iters; c.k_grid = grid; c.k_xcd = a.xcd_chunks;
+        c.k_items = a.items; c.k_n = a.n_items; c.k_iters = a.iters; c.k_grid = grid;
         c.k_nt = nt;
         c.k_l1 = a.l1;
         c.k_still = a.still;
@@ -533,7 +532,6 @@ extern "C" int dn_regularize_batch(dn_volume *const *vols, int32_t n, const dn_r
     a.bar = ws.state;
     a.err = reinterpret_cast<int32_t *>(ws.state + 2 * kBarSlot);
     a.spin_limit = 1LL << 22;
-    a.xcd_chunks = 1;
     a.l1 = prm->data_term == DN_DATA_L1;
     a.still = 1;
     a.first = 0;
@@ -554,8 +552,8 @@ extern "C" int dn_regularize_batch(dn_volume *const *vols, int32_t n, const dn_r
     // DN_K_FUSED256: one launch of the fused kernel per iteration; other
     // explicit choices: the persistent kernel; both on the blocks in pool
     // order, XCD-chunked.  DN_K_AUTO: the tuned choice
-    TuneChoice ch = TuneChoice{kPersistent, per_cu, 1, 1};
-    if (prm->kernel == DN_K_FUSED256) ch = TuneChoice{kStepKernel, 1, 1, 1};
+    TuneChoice ch = TuneChoice{kPersistent, per_cu, 1};
+    if (prm->kernel == DN_K_FUSED256) ch = TuneChoice{kStepKernel, 1, 1};
     const int64_t key = (int64_t(v0->device) << 32) | size_bucket(total);
     auto it = g_tuned.find(key);
     const bool tuned = prm->kernel == DN_K_AUTO;
@@ -592,7 +590,7 @@ extern "C" int dn_regularize_batch(dn_volume *const *vols, int32_t n, const dn_r
                     DN_HIP(hipEventElapsedTime(&ms, e0, e1));
                     if (getenv("DN_VERBOSE"))
                         fprintf(stderr, "[denser] batch tune: variant %d wpc %d pool %d: %.3f ms\n", nt, wpc, pool, ms);
-                    if (ms < best) { best = ms; ch = TuneChoice{nt, wpc, 1, pool}; }
+                    if (ms < best) { best = ms; ch = TuneChoice{nt, wpc, pool}; }
                 }
             }
         }
@@ -602,7 +600,6 @@ extern "C" int dn_regularize_batch(dn_volume *const *vols, int32_t n, const dn_r
     }
     if ((rc = build_items(ch.pool))) return rc;
     a.iters = prm->iters;
-    a.xcd_chunks = ch.xcd;
     const int grid = int(std::max<int64_t>(
         1, std::min<int64_t>({int64_t(ch.wg_per_cu) * dev_cu, total, int64_t(kBarMaxGrid)})));
     hipEvent_t e0, e1;
@@ -677,7 +674,7 @@ extern "C" int dn_regularize_batch(dn_volume *const *vols, int32_t n, const dn_r
             s.converged = prm->gap_tol > 0 && s.gap <= prm->gap_tol * s.energy;
             s.ms_loop = ms;
             s.kernel_used = ch.nt * 100 + ch.wg_per_cu;
-            s.layout_used = (ch.pool ? 1 : 0) | (ch.xcd ? 0 : 2);
+            s.layout_used = ch.pool ? 1 : 0;
         }
     }
     return DN_OK;

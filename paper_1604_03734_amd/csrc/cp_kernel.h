@@ -100,7 +100,6 @@ template <class S> struct CPArgs {
     const int32_t *nbr;         // [nb][27]
     const uint32_t *em4;        // [nb][64] edge masks, see k_masks
     const int32_t *order;       // processing order or nullptr (pool order)
-    int32_t xcd;                // 1: XCD-chunked workgroup -> block map
     const float *f, *w;
     typename S::T *u;           // in place
     const typename S::T *ubar_in;
@@ -458,15 +457,6 @@ __device__ __forceinline__ void cp_block(const CPArgs<S> &A, int32_t b, CPShared
     }
 }
 
-// -1 face voxel e < 192: face 0 (-x), 1 (-y), 2 (-z)
-__device__ __forceinline__ void face_pos(int t, int &x, int &y, int &z)
-{
-    int f = t >> 6, i = t & 63, a = i & 7, b = i >> 3;
-    if (f == 0) { x = -1; y = a; z = b; }
-    else if (f == 1) { x = a; y = -1; z = b; }
-    else { x = a; y = b; z = -1; }
-}
-
 // The lane index, one that the compiler cannot hoist out of an enclosing
 // loop (the index arithmetic is redone per block instead of staying live).
 __device__ __forceinline__ unsigned opaque_lane()
@@ -494,11 +484,6 @@ __device__ __forceinline__ int64_t xcd_slot(int64_t wg, int64_t n)
 {
     int64_t per = (n + 7) / 8;
     return (wg % 8) * per + wg / 8;
-}
-
-__device__ __forceinline__ int64_t block_slot(int64_t wg, int64_t n, int xcd)
-{
-    return xcd ? xcd_slot(wg, n) : wg;
 }
 
 }  // namespace dn

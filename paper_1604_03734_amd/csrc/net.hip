@@ -27,12 +27,13 @@ constexpr int kC = 16;        // channels of a stored activation
 constexpr int kTaps = 27;
 constexpr int kWPack = kTaps * kC * kC;   // one packed layer: [tap][co][ci]
 constexpr int kMT = 63;       // 16-voxel row tiles covering 1000 voxels
-// Training layouts: an activation channel-first on the tile's 10^3 grid
-// padded by one zero voxel on every side (12^3 = 1728 entries per channel,
-// index (x+1) + 12 (y+1) + 144 (z+1)); a gradient channel-first on the
-// compact rows of that grid (the 100 rows (y, z) of 12 entries, padding
-// entries x = -1 and x = 10 zero, index (x+1) + 12 (10 z + y), 1216 entries
-// with the tail zero).
+// Training layouts: an activation on the tile's 10^3 grid padded by one zero
+// voxel on every side (12^3 = 1728 entries, index (x+1) + 12 (y+1) +
+// 144 (z+1)); a gradient on the compact rows of that grid (the 100 rows
+// (y, z) of 12 entries, padding entries x = -1 and x = 10 zero, index
+// (x+1) + 12 (10 z + y), 1216 entries with the tail zero).  The 16 channels of
+// an entry are contiguous; the layer-1 input has its two channels one after
+// the other, and d3 has one.
 constexpr int kPadVox = 1728;
 // offsets of the layers in the canonical 8241-float parameter vector
 constexpr int kW1 = 0, kB1 = 16 * 2 * 27, kW2 = kB1 + 16, kB2 = kW2 + 16 * 16 * 27, kW3 = kB2 + 16,
@@ -57,20 +58,17 @@ __device__ __forceinline__ int64_t halo_vox(const int32_t *nb27, int hx, int hy,
     return int64_t(id) * kBlockVox + ((hx - 8 * dx) + 8 * (hy - 8 * dy) + 64 * (hz - 8 * dz));
 }
 
-// Input tiles of blocks [first, first + n) of the list (or of the pool if
-// blocks == nullptr): channel 0 f, channel 1 log(1 + w) / log(101); 0 for
-// voxels of unallocated neighbours.  Either float [n][2][1000] or
-// bfloat16 channel-last [n][1000][16].
+// Input tiles of the n listed blocks, float [n][2][1000]: channel 0 f,
+// channel 1 log(1 + w) / log(101); 0 for voxels of unallocated neighbours.
 // perm exchanges the tile's x axis with the volume's y (1) or z (2) axis.
 __global__ void k_gather(const int32_t *__restrict__ nbr, const float *__restrict__ f, const float *__restrict__ w,
-                         const int32_t *__restrict__ blocks, int64_t first, int64_t n, float *__restrict__ tiles,
-                         uint16_t *__restrict__ X, int perm)
+                         const int32_t *__restrict__ blocks, int64_t n, float *__restrict__ tiles, int perm)
 {
     int64_t k = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (k >= n * kT) return;
     int64_t i = k / kT;
     int v = int(k % kT);
-    int64_t b = blocks ? blocks[first + i] : first + i;
+    int64_t b = blocks[i];
     int x = v % 10, y = (v / 10) % 10, z = v / 100;
     if (perm == 1) { int s = x; x = y; y = s; }
     if (perm == 2) { int s = x; x = z; z = s; }
@@ -80,25 +78,11 @@ __global__ void k_gather(const int32_t *__restrict__ nbr, const float *__restric
         fv = f[j];
         wv = float(log(1.0 + double(w[j])) / log(101.0));
     }
-    if (tiles) {
-        tiles[i * 2 * kT + v] = fv;
-        tiles[i * 2 * kT + kT + v] = wv;
-    }
-    if (X) {
-        uint16_t out[16];
-        out[0] = f2bf(fv);
-        out[1] = f2bf(wv);
-        for (int c = 2; c < 16; ++c) out[c] = 0;
-        uint4 *d = reinterpret_cast<uint4 *>(X + k * kC);
-        d[0] = *reinterpret_cast<uint4 *>(&out[0]);
-        d[1] = *reinterpret_cast<uint4 *>(&out[8]);
-    }
+    tiles[i * 2 * kT + v] = fv;
+    tiles[i * 2 * kT + kT + v] = wv;
 }
 
 
-// Number of mask entries set: workgroup g sums its 4096-entry chunk in a
-// fixed order (thread-strided, then a tree) into part[g]; then one
-// workgroup sums the parts in order.
 // The gradient of all 8241 parameters from the per-workgroup partials of
 // the three layers, written to the
 // canonical parameter layout and scaled by 1 / N (the partials are of the
@@ -257,7 +241,7 @@ constexpr int kLaneW = (2 * kL1M + kL2M + kL3M) * 64 * 8;
 struct NetWS {
     // training step (dn_net_loss_grad)
     uint16_t *lanew, *lanef, *gates, *x1cf, *h1cf, *h2cf, *d3cf, *d2cf, *d1cf;
-    float *rc, *d3, *parts;
+    float *d3, *parts;
     double *misc, *tl, *tc;
     int nparts;
 };
@@ -280,7 +264,6 @@ static NetWS carve_net(Bump &b, int64_t n, bool training)
     x.x1cf = b.take<uint16_t>(size_t(n) * 2 * kPadVox);
     x.h1cf = b.take<uint16_t>(size_t(n) * 16 * kPadVox);
     x.h2cf = b.take<uint16_t>(size_t(n) * 16 * kPadVox);
-    x.rc = b.take<float>(size_t(n) * kBlockVox);
     x.d3 = b.take<float>(size_t(n) * kBlockVox);
     x.d3cf = b.take<uint16_t>(size_t(n) * kRowVox);
     x.d2cf = b.take<uint16_t>(size_t(n) * 16 * kRowVox);
@@ -296,8 +279,8 @@ static NetWS carve_net(Bump &b, int64_t n, bool training)
 static bool ws_ok(const void *ws) { return ws && (reinterpret_cast<uintptr_t>(ws) & 255) == 0; }
 
 // Lane-ready weights [mfma][lane][8] (bfloat16).  The K slots of lane
-// group g = lane / 16, entry j, of MFMA m: layer 1 -> tap 16m + 4g + j/2,
-// channel j%2; layer 2 -> tap 2m + g/2, channel 8(g%2) + j; the output
+// group g = lane / 16, entry j, of MFMA m: layer 1 -> x tap j/2 (3: zero) of
+// the (y, z) tap pair 4m + g, channel j%2; layer 2 -> tap 2m + g/2, channel 8(g%2) + j; the output
 // column (output channel) is lane % 16.  Layer 3 has one output channel, so
 // its rows are taps instead: row n = 3 kz + ky (n < 9) is the (y, z) tap
 // pair, and the K slots of MFMA m, group g are x tap kx = 2m + g/2 (kx < 3),
@@ -517,8 +500,8 @@ __global__ void k_voxel_pairs(const float *__restrict__ f, const float *__restri
 // float tiles [n][2][1000]); the layer inputs are also written to global
 // memory on the zero-padded 12^3 grid for the backward pass (x1cf: the two
 // input channels channel-first, [n][2][1728]; h1cf, h2cf channel-last,
-// [n][1728][16]), and out receives the residual r on the centre, [n][512]
-// (voxel x + 8y + 64z).
+// [n][1728][16]), and the residual on the centre goes into the loss at once
+// (loss_of_tile), not to memory (out is null).
 __device__ __forceinline__ int pad_index(int x, int y, int z) { return (x + 1) + 12 * (y + 1) + 144 * (z + 1); }
 
 // Channel-last copy of an LDS activation (two planes of 8 channels) onto the
@@ -892,12 +875,11 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 }
 
 // ---------------------------------------------------------------------------
-// Training step kernels (after k_net_fwd<true>).
+// Training step kernels (after k_net_fwd<kTraining>).
 
 // Lane-ready weights of a training step: the forward's (as k_pack_lanes)
 // and those of the input gradient of layer 2, d1 = conv(d2, W') with
 // W'[ci][co][t] = W2[co][ci][26 - t] (the layer-2 map of k_pack_lanes).
-__device__ void pack_lane(const float *__restrict__ params, int k, uint16_t *__restrict__ out);
 __global__ void k_pack_train(const float *__restrict__ params, uint16_t *__restrict__ lw, uint16_t *__restrict__ out)
 {
     int k = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1256,7 +1238,6 @@ __device__ __forceinline__ void wgrad1_body(const uint16_t *__restrict__ X, cons
         __syncthreads();
     }
     // D[co][col]: lane holds column 16 q + i, rows co = 4g .. 4g + 3; the
-    // D[co][col]: lane holds column 16 q + i, rows co = 4g .. 4g + 3; the
     // eight waves' sums, then one partial per workgroup in [tap][co][ci]
     for (int q = 0; q < 4; ++q)
         for (int r = 0; r < 4; ++r) red[wave][4 * g + r][16 * q + i] = acc[q][r];
@@ -1578,7 +1559,7 @@ int dn_net_gather(dn_volume *v, const int32_t *blocks, int64_t n, int32_t perm, 
     DN_REQUIRE(v && blocks && tiles && n >= 0 && perm >= 0 && perm <= 2, "bad argument");
     if (n == 0) return DN_OK;
     hipLaunchKernelGGL(k_gather, dim3(grid1(n * kT)), dim3(256), 0, v->stream, v->nbr, v->f, v->w, blocks,
-                       int64_t(0), n, tiles, (uint16_t *)nullptr, int(perm));
+                       n, tiles, int(perm));
     DN_HIP(hipGetLastError());
     return DN_OK;
 }

@@ -32,7 +32,7 @@ template <class S, bool kRefine, bool kStream, bool kStill, int W>
 __global__ __launch_bounds__(64 * W) void k_cp_fused(CPArgs<S> A)
 {
     __shared__ CPShared<W> sh;
-    const int64_t slot = block_slot(blockIdx.x, A.nb, A.xcd);
+    const int64_t slot = xcd_slot(blockIdx.x, A.nb);
     if (slot >= A.nb) return;
     const int32_t b = A.order ? as_scalar(A.order)[slot] : int32_t(slot);
     cp_block<S, kRefine, kStream, kStill, W>(A, b, sh, wave_index(), threadIdx.x & 63u);
@@ -537,7 +537,6 @@ static CPArgs<S> make_args(dn_volume *v, const dn_reg_params *prm, typename S::T
     A.nbr = v->nbr;
     A.em4 = v->em4;
     A.order = v->layout & 1 ? nullptr : v->order;
-    A.xcd = (v->layout & 2) ? 0 : 1;
     A.f = v->f; A.w = v->w;
     A.u = u; A.ubar_in = ub_in; A.ubar_out = ub_out; A.p_in = p_in; A.p_out = p_out;
     A.u32 = nullptr; A.ubar32 = nullptr; A.p32 = nullptr;
@@ -575,15 +574,17 @@ static void launch_fused_w(hipStream_t st, const CPArgs<S> &A, int kernel)
 // blocks BF16: 179 and 232 us).
 template <class S, bool kRefine> static void launch_fused(hipStream_t st, const CPArgs<S> &A, int kernel, bool still)
 {
-    if (!kRefine && !streams_state(A.nb, sizeof(typename S::T))) {
-        launch_fused_w<S, kRefine, kRefine, false>(st, A, kernel);   // (kRefine: not reached)
-        return;
-    }
-    if constexpr (!kRefine && !S::kLow)
-        if (still && kernel != DN_K_FUSED) {
-            launch_fused_w<S, kRefine, true, true>(st, A, kernel);
+    if constexpr (!kRefine) {
+        if (!streams_state(A.nb, sizeof(typename S::T))) {
+            launch_fused_w<S, false, false, false>(st, A, kernel);
             return;
         }
+        if constexpr (!S::kLow)
+            if (still && kernel != DN_K_FUSED) {
+                launch_fused_w<S, false, true, true>(st, A, kernel);
+                return;
+            }
+    }
     launch_fused_w<S, kRefine, true, false>(st, A, kernel);
 }
 
@@ -732,7 +733,7 @@ template <class S> static int first_lowp(dn_volume *v, const dn_reg_params *prm)
 
 // Kernel choice for DN_K_AUTO: measured once per size bucket.  A choice is
 // (kernel variant, layout) with layout bit 0 = pool order instead of Morton
-// order, bit 1 = plain workgroup -> block map instead of XCD chunks.
+// order.
 struct AutoChoice { int kernel; int layout; };
 // The candidates: 8, 4, 2 and 1 waves per block in Morton and in pool order,
 // in XCD chunks.  Many waves are best where blocks are few (503 blocks: 4.9

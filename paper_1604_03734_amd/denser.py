@@ -367,8 +367,8 @@ NET_STATIC_TILES = 32
 
 
 def net_forward_static(tiles, params, out, stream=None):
-    """dn_net_forward_static: the forward pass with the library's static
-    scratch (no workspace; at most NET_STATIC_TILES tiles per call)."""
+    """dn_net_forward_static: the forward pass without a workspace (at most
+    NET_STATIC_TILES tiles per call)."""
     check(lib().dn_net_forward_static(_ptr(tiles), tiles.shape[0], _ptr(params), _ptr(out),
                                       _stream_handle(stream)))
 
