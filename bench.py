@@ -15,11 +15,11 @@ One step (timed, inputs already resident in HBM):
 value = allocated voxels x iterations / step time (voxel-iterations/s).
 
 The JSON line also carries the roofline of the dominant kernel (the fused
-iteration kernel, 48 algorithmic bytes per voxel-iteration, timed with HIP
-events on the volume's stream; moved_share is the share of the state's lines
-that an iteration moves, moved_gbs the rate of those alone), the FP64 CPU oracle timed on one street as
-the CPU baseline, and the time to a relative gap of 1e-3 of the plain and
-the warm-started solver.
+iteration kernel, timed with HIP events on the volume's stream: 48 algorithmic
+bytes per voxel of the lines that an iteration moves, moved_share of the
+state's; all_lines_gbs counts the resting ones too), the FP64 CPU oracle timed
+on one street as the CPU baseline, and the time to a relative gap of 1e-3 of
+the plain and the warm-started solver.
 """
 from __future__ import annotations
 
@@ -36,6 +36,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 ALG_BYTES_PER_VOXEL_ITER = 48  # u, ubar, p(3), f, w read; p(3), u, ubar written (FP32)
+ALG_BYTES_PER_VOXEL_ITER_16 = 28  # the same with u, ubar, p stored in 16 bits (f, w FP32)
+HBM_PEAK_GBS = 8000.0
 
 
 def moved_share(D, volumes, kernel_id):
@@ -48,8 +50,6 @@ def moved_share(D, volumes, kernel_id):
         return 1.0
     lines = sum(int((v.extract(D.DN_X_W) > 0).view(-1, 32).any(1).sum().item()) for v in volumes)
     return lines / (n * 16)
-ALG_BYTES_PER_VOXEL_ITER_16 = 28  # the same with u, ubar, p stored in 16 bits (f, w FP32)
-HBM_PEAK_GBS = 8000.0
 
 
 def parse():
@@ -107,8 +107,8 @@ TRAFFIC_FILES = {
 
 
 def load_traffic(nvox, workload, storage, kernel_id, layout=None):
-    """Bytes leaving L2 per launch of the iteration kernel, from the
-    committed counter summary, if it was taken on the current kernel source
+    """Bytes leaving L2 per launch of the iteration kernel on nvox voxels (of
+    lines that it moves), from the committed counter summary, if it was taken on the current kernel source
     and on the kernel variant (and, where the summary records it, the block
     order) that ran (else None)."""
     entry = TRAFFIC_FILES.get((workload, storage))
@@ -504,16 +504,16 @@ def batched_run(wl, submaps=64, iters=300, steps=2):
     per = float(np.mean(ms))
     kid = st.kernel_used // 100
     share = moved_share(D, bw.subs, 257 if kid == 257 else -1)
-    ach = ALG_BYTES_PER_VOXEL_ITER * nvox / (per / 1000.0) / 1e9
+    ach = ALG_BYTES_PER_VOXEL_ITER * nvox * share / (per / 1000.0) / 1e9
     out = {"submaps": submaps, "blocks": nvox // 512, "voxels": nvox, "iters": iters,
            "ms_per_iter": per, "voxel_iters_per_s": nvox / (per / 1000.0),
            "kernel": BATCH_KERNELS.get(kid, "k_cp_persistent"),
            "wg_per_cu": st.kernel_used % 100,
            "roofline": {"bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                         "frac": ach / HBM_PEAK_GBS,
-                        "traffic": load_traffic(nvox, "batched", "f32", kid, st.layout_used),
-                        "moved_share": share, "moved_gbs": ach * share,
-                        "alg_bytes_per_launch": ALG_BYTES_PER_VOXEL_ITER * nvox}}
+                        "traffic": load_traffic(nvox * share, "batched", "f32", kid, st.layout_used),
+                        "moved_share": share, "all_lines_gbs": ach / share,
+                        "alg_bytes_per_launch": ALG_BYTES_PER_VOXEL_ITER * nvox * share}}
     for v in bw.subs:
         v.close()
     return out
@@ -680,8 +680,8 @@ def main():
         batched = args.workload == "batched"
         share = moved_share(wl.D, wl.subs if batched else [wl.big],
                             (257 if kernel_id == 257 else -1) if batched else kernel_id)
-    achieved = alg_bytes * nvox / (kern_ms / 1000.0) / 1e9
-    traffic = load_traffic(nvox, args.workload, args.storage, kernel_id,
+    achieved = alg_bytes * nvox * share / (kern_ms / 1000.0) / 1e9
+    traffic = load_traffic(nvox * share, args.workload, args.storage, kernel_id,
                            st.layout_used if args.workload == "batched" else None)
     if args.workload == "batched":
         metric = f"voxel-iterations/s ({args.submaps} sub-maps, {args.iters} CP iterations, one HIP graph)"
@@ -715,8 +715,8 @@ def main():
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
                      "traffic": traffic,
-                     "moved_share": share, "moved_gbs": achieved * share,
-                     "alg_bytes_per_launch": alg_bytes * nvox,
+                     "moved_share": share, "all_lines_gbs": achieved / share,
+                     "alg_bytes_per_launch": alg_bytes * nvox * share,
                      "avg_launch_ms": kern_ms},
         "cp_voxel_iters_per_s": nvox / (kern_ms / 1000.0),
     }

@@ -1619,7 +1619,7 @@ int dn_net_loss_grad(const float *tiles, int64_t n, const float *params, const f
     // within 2 %: 512 tiles 130 us with 8, 129 with 4, 4096 696 and 710)
     const unsigned grid1w = unsigned(std::min<int64_t>(n, std::max(cus, 1)));
     // a loss word that the device can write (pinned) spares the copy: with that
-    // and the loss in the forward pass a step of 256 tiles 141.6 -> 114.0 us
+    // and the loss in the forward pass a step of 256 tiles 141.6 -> 103 to 114 us (it differs by process)
     double *host_loss = nullptr;
     if (loss_host) {
         hipPointerAttribute_t at{};

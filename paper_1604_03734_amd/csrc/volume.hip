@@ -380,8 +380,8 @@ static FieldSet field_set(const dn_volume *v)
 // whose first inserter lists the key.  The host reads the counts (the call's
 // one wait); new blocks then take three more launches, none of which sorts
 // or scans more than the new keys and the list of occupied slots.  Bound by
-// latency: 12 frames of 1242 x 375 take 0.82 ms, 3.72 ms with a full sort of
-// the pool and four waits per frame; four of 320 x 96 0.30 ms, 1.18 before.
+// latency: 12 frames of 1242 x 375 take 0.78 ms, 3.72 ms with a full sort of
+// the pool and four waits per frame; four of 320 x 96 0.29 ms, 1.18 before.
 // Points (threads) per workgroup: each workgroup adds to the same counters,
 // so on a large frame fewer, larger ones are quicker (1242 x 375: 256 points
 // 50 us, 512 30 us, 1024 28 us); a small frame needs them spread over the
@@ -1135,7 +1135,7 @@ __global__ void k_laser_obs_emit(LGeo g, const float *__restrict__ pts, int64_t 
 // wait for memory), and lanes in the same voxel add to its count once.
 // Against two walks with a lookup in memory per block and a sort of all
 // observations, 65536 returns into 1400 blocks: 0.90 ms a scan before
-// (allocation included), 0.21 ms now.
+// (allocation included), 0.22 ms now.
 constexpr int64_t kAccumBlocks = 16384;
 
 // The two words of a voxel's accumulator.  `fine` is the sum with F bits after
