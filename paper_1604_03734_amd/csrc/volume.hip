@@ -1157,7 +1157,7 @@ struct LaserSums {
         b = 1;
         while ((n >> b) > 0) ++b;
         F = std::min(60, 125 - 3 * b);      // n units of the coarse sum are less than 2^63 fine ones
-        q = std::min(25, 63 - 2 * b);       // n terms of the coarse sum fit its 64 - b bits, and 64 of them 32
+        q = std::min(24, 63 - 2 * b);       // n terms (each up to 2) of the coarse sum fit its 64 - b bits, 64 of them 32
     }
     // (not negative: psi < 1)
     __device__ __forceinline__ unsigned long long term(double psi) const

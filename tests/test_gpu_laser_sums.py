@@ -23,12 +23,13 @@ def _eta(z):
 
 
 @pytest.mark.parametrize("padding", [0, 1 << 16, 1 << 20])
-@pytest.mark.parametrize("case", ["tiny", "cancelling", "many"])
+@pytest.mark.parametrize("case", ["tiny", "cancelling", "many", "end of the band"])
 def test_sums_keep_the_digits_of_float64(case, padding):
     D = dn()
     centre, up = 10.5 * S, 2.0 ** -23         # up: one step of float32 there
     z = {"tiny": [centre + up], "cancelling": [centre + 3 * up, centre - 2 * up, centre - up, centre + up],
-         "many": centre + up * (np.arange(4001) % 7 - 3)}[case]
+         "many": centre + up * (np.arange(4001) % 7 - 3),
+         "end of the band": np.full(130, centre)}[case]        # psi = -1 exactly in voxel 13, in whole waves
     z = np.asarray(z, np.float32)
     # padding: more returns (not valid ones) of the same scan
     pts = np.full((len(z) + padding, 3), np.nan, np.float32)
