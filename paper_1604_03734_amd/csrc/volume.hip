@@ -1126,53 +1126,43 @@ __global__ void k_laser_obs_emit(LGeo g, const float *__restrict__ pts, int64_t 
 
 // Fusion of a scan into a map of up to kAccumBlocks blocks: every voxel has
 // an accumulator in the scratch: a count of its observations and the sum of
-// mu - eta over those in the band (in free space psi = 1), in fixed point, so
+// 1 - psi over those in the band (in free space psi = 1), in fixed point, so
 // that the result does not depend on the order of the additions (LaserSums).
-// Bound by latency along each ray: one lane walks a ray and looks a block up
-// when it enters it, in LDS, where a map of up to kSeenAll blocks lies whole (a
-// larger one's table keeps the blocks that its workgroup met: neighbouring rays
-// pass the same ones, but each costs one wait for memory), and lanes in the
-// same voxel add to its count once.
+// Bound by latency along each ray: one lane walks a ray
+// and looks a block up when it enters it, in LDS, where a map of up to
+// kSeenAll blocks lies whole (a larger one's table keeps the blocks that its
+// workgroup met: neighbouring rays pass the same ones, but each costs one
+// wait for memory), and lanes in the same voxel add to its count once.
 // Against two walks with a lookup in memory per block and a sort of all
 // observations, 65536 returns into 1400 blocks: 0.90 ms a scan before
 // (allocation included), 0.22 ms now.
 constexpr int64_t kAccumBlocks = 16384;
 
-// The two words of a voxel's accumulator.  An observation in the band adds the
-// term mu - eta, a whole number of units of 2^-F of the power of two that mu
-// does not exceed; sum of psi = (count mu - sum of the terms) / mu, divided once
-// per voxel.  `fine` is the sum of the terms modulo 2^64; `coarse` the count in
-// its upper b bits (n < 2^b returns) and below it the sum of the same terms cut
-// by F - q bits.  Each term, up to 2^(F + 1), loses less than one unit there, so
-// the whole sum is the coarse one plus less than n units, and `fine` tells how
-// much: it is exact.  With 60 bits (56 for the largest scans) a term keeps the
-// digits of eta in float64 up to the rounding of the distances; one word of
-// 63 - b bits lost them (f near the surface had 3 of float32's 7 digits after a
-// scan of 10^6 returns).  Coarse parts are added up over a run of lanes first:
-// for 65536 returns that is 132 us a scan, 129 with the one word (and a division
-// per observation), 139 with an atomic per observation for the coarse parts.
+// The two words of a voxel's accumulator.  `fine` is the sum with F bits after
+// the point, modulo 2^64; `coarse` the count in its upper b bits (n < 2^b
+// returns) and below it the sum of the same terms cut to q bits after the
+// point.  Each term, in [0, 2], loses less than one unit there, so the whole
+// sum is the coarse one plus less than n units, and `fine` tells how much: it
+// is exact.  With 60 bits (56 for the largest scans) a term keeps the digits
+// of psi in float64 up to the rounding of the distances; one word of 63 - b
+// bits lost them (f near the surface had 3 of float32's 7 digits after a scan
+// of 10^6 returns), and was 4 us of 130 quicker for 65536 returns.  Coarse
+// parts are added up over a run of lanes first: an atomic per observation for
+// them cost 4 us more.
 struct LaserSums {
     int b, q, F;
-    double units;           // per metre
-    int64_t mu;             // in units
     static constexpr int kMaxB = 23;
-    LaserSums(int64_t n, double mu_m)
+    explicit LaserSums(int64_t n)
     {
         b = 1;
         while ((n >> b) > 0) ++b;
         F = std::min(60, 125 - 3 * b);      // n units of the coarse sum are less than 2^63 fine ones
         q = std::min(24, 63 - 2 * b);       // n terms (each up to 2) of the coarse sum fit its 64 - b bits, 64 of them 32
-        int e = 0;
-        std::frexp(mu_m, &e);
-        units = std::ldexp(1.0, F - e);
-        mu = int64_t(mu_m * units);
     }
-    // (every power of two above is a normal number)
-    static bool takes(int64_t n, double mu_m) { return (n >> kMaxB) == 0 && mu_m > 1e-200 && mu_m < 1e200; }
-    // (positive: eta < mu)
-    __device__ __forceinline__ unsigned long long term(double eta) const
+    // (not negative: psi < 1)
+    __device__ __forceinline__ unsigned long long term(double psi) const
     {
-        return (unsigned long long)(mu - int64_t(eta * units));
+        return (1ull << F) - (unsigned long long)(int64_t)(psi * double(1ull << F));
     }
     __device__ __forceinline__ uint32_t cut(unsigned long long term) const { return uint32_t(term >> (F - q)); }
     // of up to 64 observations, given the sum of their cut terms
@@ -1184,11 +1174,13 @@ struct LaserSums {
     // the sum of psi over all observations
     __device__ __forceinline__ double psi(unsigned long long c, unsigned long long fine) const
     {
-        const unsigned long long cut = c & ((1ull << (64 - b)) - 1ull), less = fine - (cut << (F - q));
-        const __int128 sum = __int128(count(c)) * mu - (__int128(cut) << (F - q)) - __int128(less);
-        const int64_t hi = int64_t(sum >> 64), lo = int64_t(sum);
-        const double units_sum = hi == lo >> 63 ? double(lo) : double(hi) * 0x1p64 + double((unsigned long long)lo);
-        return units_sum / double(mu);
+        const unsigned long long cut = c & ((1ull << (64 - b)) - 1ull);
+        const int64_t a = (int64_t(count(c)) << q) - int64_t(cut);          // at least the sum, in 2^-q
+        const int64_t less = int64_t(fine - (cut << (F - q)));              // by that, in 2^-F
+        const int64_t top = int64_t(1) << (62 - (F - q));
+        const double unit = 1.0 / double(1ull << F);
+        if (a < top && a > -top) return double((a << (F - q)) - less) * unit;
+        return double(a) / double(1ull << q) - double(less) * unit;
     }
 };
 constexpr int kSeen = 8192, kSeenAll = kSeen / 2;   // entries of the table
@@ -1320,7 +1312,7 @@ __global__ __launch_bounds__(256) void k_laser_accumulate(LGeo g, const float *_
                     const double eta = r - rho;
                     hit = eta >= g.mu;
                     if (!hit && eta >= -g.mu) {
-                        const unsigned long long term = ls.term(eta);
+                        const unsigned long long term = ls.term(eta / g.mu);
                         atomicAdd(&sums[vox].y, term);
                         cut = ls.cut(term);
                         hit = true;
@@ -1859,8 +1851,8 @@ int dn_fuse_laser(dn_volume *v, const float *pts, int64_t n, const double T[16])
     Bump bump(v->scratch, v->scratch_bytes);
     const int64_t nvox = v->nb * int64_t(kBlockVox);
     ulonglong2 *sums = bump.take<ulonglong2>(size_t(nvox));
-    if (v->nb <= kAccumBlocks && LaserSums::takes(n, g.mu) && bump.fits()) {
-        const LaserSums ls(n, g.mu);
+    const LaserSums ls(n);
+    if (v->nb <= kAccumBlocks && ls.b <= LaserSums::kMaxB && bump.fits()) {
         int64_t *total = v->misc + kMiscObs;
         hipLaunchKernelGGL(k_laser_clear, dim3(grid1(nvox / 4)), dim3(256), 0, st, sums, nvox, total);
         // (the whole map in the table: every block that a ray can observe has a tag.  A
